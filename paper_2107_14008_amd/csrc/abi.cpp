@@ -647,8 +647,8 @@ int do_upload(pmfmm_ctx* ctx, const double* pos, const double* mass, int32_t on_
     if ((rc = upload(ctx->d.js, js, s))) return rc;
     if ((rc = upload_boxes(ctx, s))) return rc;
     HIP_TRY(ctx->d.counter.ensure(pmfmm::kQueueSegs * pmfmm::kCounterStride * 4));
-    HIP_TRY(ctx->d.x64.ensure((size_t)n * 32));
-    HIP_TRY(ctx->d.x32.ensure((size_t)n * 16));
+    HIP_TRY(ctx->d.x64.ensure((size_t)n * 32 + pmfmm::kReadAhead));
+    HIP_TRY(ctx->d.x32.ensure((size_t)n * 16 + pmfmm::kReadAhead));
     const double* src_pos = pos;
     const double* src_mass = mass;
     if (!on_device) {
@@ -707,6 +707,14 @@ int default_wg_waves(int mode) {
             mode == pmfmm::kFP64R2)
                ? 16
                : 4;
+}
+
+// Workgroups of a persistent launch: the caller's, or as many as are resident
+// (`resident`), but no more than there are items in every queue segment.
+int launch_grid(const pmfmm_ctx* ctx, int resident) {
+    if (ctx->p.grid_wgs > 0) return ctx->p.grid_wgs;
+    const int64_t per_seg = (ctx->n_items + pmfmm::kQueueSegs - 1) / pmfmm::kQueueSegs;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(resident, pmfmm::kQueueSegs * per_seg));
 }
 
 pmfmm::FarArgs far_args(pmfmm_ctx* ctx) {
@@ -1202,8 +1210,7 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
     const size_t lds = tab ? ctx->table_host.size() : 0;
     const int wg = std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : default_wg_waves(mode),
                             pmfmm::p2p_max_threads(mode) / 64);
-    int grid = ctx->p.grid_wgs;
-    if (grid <= 0) grid = ctx->n_cu * pmfmm::p2p_blocks_per_cu(mode, wg, lds);
+    const int grid = launch_grid(ctx, ctx->n_cu * pmfmm::p2p_blocks_per_cu(mode, wg, lds));
     HIP_TRY(pmfmm::launch_p2p(mode, a, wg, grid, lds, s));
     if (timing) HIP_TRY(hipEventRecord(ctx->ev[2], s));
     pmfmm::ReduceArgs r{ctx->d.leaf.as<int4>(), ctx->d.leaf_slot.as<int32_t>(), partial,
@@ -1518,8 +1525,8 @@ int pmfmm_adjoint(pmfmm_ctx* ctx, const double* w, double* grad_pos, double* gra
     // within 2 % of the same time with 4, 8 or 16.
     const int wg = std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : (a.table != nullptr ? 8 : 4),
                             pmfmm::adjoint_max_threads(mode) / 64);
-    int grid = ctx->p.grid_wgs;
-    if (grid <= 0) grid = ctx->n_cu * pmfmm::adjoint_blocks_per_cu(mode, wg, a.table != nullptr);
+    const int grid =
+        launch_grid(ctx, ctx->n_cu * pmfmm::adjoint_blocks_per_cu(mode, wg, a.table != nullptr));
     HIP_TRY(pmfmm::launch_adjoint(mode, a, wg, grid, s));
     if (timing) {
         HIP_TRY(hipEventRecord(ctx->ev[5], s));

@@ -162,19 +162,11 @@ adjoint_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
         __syncthreads();
     }
     const int lane = threadIdx.x & 63;
-    int seg = (int)(blockIdx.x % kQueueSegs), done = 0;
+    ItemCursor cur = item_cursor();
     for (;;) {
-        const int beg = queue_seg_begin(seg, n_items);
-        int q = 0;
-        if (lane == 0) q = atomicAdd(counter + seg * kCounterStride, 1);
-        q = uni(q);
-        if (q >= queue_seg_begin(seg + 1, n_items) - beg) {
-            // this segment is exhausted (for good: its counter only grows)
-            if (++done == kQueueSegs) break;
-            seg = seg + 1 == kQueueSegs ? 0 : seg + 1;
-            continue;
-        }
-        const int slot = uni(queue[beg + q]);
+        const int q = take_item(cur, lane, n_items, counter);
+        if (q < 0) break;
+        const int slot = uni(queue[q]);
         const int4 it = items[slot];
         const int il = uni(it.x), t0 = uni(it.y), t1 = uni(it.z);
         const int4 li = leaf[il];
@@ -206,7 +198,7 @@ adjoint_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                 const int nj = uni(lj.y);
                 float a[3] = {0.f, 0.f, 0.f}, b[3] = {0.f, 0.f, 0.f}, g = 0.f;
                 const uint64_t live =
-                    live_f32(src, nj, lane, make_float3(lo.x - offx, lo.y - offy, lo.z - offz),
+                    live_f32(src[lane < nj ? lane : 0], nj, lane, make_float3(lo.x - offx, lo.y - offy, lo.z - offz),
                              make_float3(hi.x - offx, hi.y - offy, hi.z - offz), bx.rc2_f);
                 if constexpr (TAB) {
                     // boff = -(row of 2^kAdjEmin) * 8 mod 2^32, kept opaque (an

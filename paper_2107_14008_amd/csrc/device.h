@@ -151,9 +151,9 @@ __device__ inline double truncation_T_f64(double x, double* ex) {
 // source with a pair inside r_cut always survives.
 
 // float32, in the j leaf's frame: targets p = pv - off in [plo, phi].
-__device__ inline uint64_t live_f32(const float4* __restrict__ src, int nj, int lane,
-                                             float3 plo, float3 phi, float rc2) {
-    const float4 q = src[lane < nj ? lane : 0];
+// Lane k holds source k in q.
+__device__ __forceinline__ uint64_t live_f32(const float4 q, int nj, int lane, float3 plo,
+                                             float3 phi, float rc2) {
     const float bx = fmaxf(fmaxf(plo.x - q.x, q.x - phi.x), 0.f);
     const float by = fmaxf(fmaxf(plo.y - q.y, q.y - phi.y), 0.f);
     const float bz = fmaxf(fmaxf(plo.z - q.z, q.z - phi.z), 0.f);
@@ -189,6 +189,47 @@ __device__ inline uint64_t live_f64(const double4* __restrict__ src, int nj, int
     return __ballot((lane < nj) & (d2 < rc2));
 }
 
+// What an item's tasks need of their j leaves, read by 64 lanes at once (lane
+// k: task tb + k of the item) and handed to the wave task by task with
+// readlane: the loads of a task index, its leaf and its centre hang on each
+// other, and one task at a time waited for all three (and formed the float64
+// centre offset in every lane) before each j leaf.
+struct TaskLanes {
+    int first, count;      // particles of the j leaf
+    float ox, oy, oz;      // its centre minus the i leaf's, images included, times sigma
+    float mass;            // the mass all its particles have, or 0
+};
+
+__device__ __forceinline__ void image_shift(int s, double L, double& sx, double& sy, double& sz) {
+    sx = (double)(s % 3 - 1) * L;
+    sy = (double)((s / 3) % 3 - 1) * L;
+    sz = (double)(s / 9 - 1) * L;
+}
+
+__device__ __forceinline__ TaskLanes load_tasks(const int32_t* __restrict__ p2p_js, int t,
+                                                const int4* __restrict__ leaf,
+                                                const double4* __restrict__ leafc,
+                                                const double4& ci, double L, double sigma) {
+    const int js = p2p_js[t];
+    const int4 lj = leaf[js >> 5];
+    const double4 cj = leafc[js >> 5];
+    double sx, sy, sz;
+    image_shift(js & 31, L, sx, sy, sz);
+    TaskLanes o;
+    o.first = lj.x;
+    o.count = lj.y;
+    o.ox = (float)(((cj.x - ci.x) + sx) * sigma);
+    o.oy = (float)(((cj.y - ci.y) + sy) * sigma);
+    o.oz = (float)(((cj.z - ci.z) + sz) * sigma);
+    o.mass = (float)cj.w;
+    return o;
+}
+
+__device__ __forceinline__ int lane_of(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
+__device__ __forceinline__ float lane_of(float v, int k) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), k));
+}
+
 template <class T3>
 __device__ inline void wave_box(T3& lo, T3& hi) {
     for (int o = 32; o > 0; o >>= 1) {
@@ -201,10 +242,59 @@ __device__ inline void wave_box(T3& lo, T3& hi) {
     }
 }
 
+// The pair loops read the sources of a leaf in groups of four, up to three
+// records past the leaf (never evaluated): the particle arrays are this many
+// bytes longer than their particles.
+constexpr size_t kReadAhead = 128;
+
 // First queue position of segment x of a queue of n items (segments and
 // counters: kQueueSegs in plan.h).
 __device__ inline int32_t queue_seg_begin(int x, int32_t n) {
     return (int32_t)(((int64_t)x * n + kQueueSegs - 1) / kQueueSegs);
+}
+
+// A wave's next item of the persistent launch (its position in the queue), or
+// -1 when the queue is empty.  Workgroup b starts on segment b % kQueueSegs
+// and takes items from the segment's counter, one device-scope atomic each;
+// when a launch has no more items than waves, each wave takes the one item
+// that its place in the grid gives it and no counter is read.  A foreign
+// segment's counter is read before it is added to: every wave looks at all
+// segments before it ends, and 8,192 waves adding to the same eight words
+// took about 100 us per launch (16^3 P2P: 137 us however finely it was cut,
+// now 44 us).
+struct ItemCursor {
+    int seg, done;
+};
+
+__device__ __forceinline__ ItemCursor item_cursor() {
+    return ItemCursor{(int)(blockIdx.x % kQueueSegs), 0};
+}
+
+__device__ __forceinline__ int take_item(ItemCursor& c, int lane, int32_t n_items,
+                                         int32_t* __restrict__ counter) {
+    const int wgs = (int)(gridDim.x / kQueueSegs);   // at least this many per segment
+    if ((n_items + kQueueSegs - 1) / kQueueSegs <= wgs * (int)(blockDim.x >> 6)) {
+        if (c.done++ != 0 || (int)(blockIdx.x / kQueueSegs) >= wgs) return -1;
+        const int q = queue_seg_begin(c.seg, n_items) +
+                      __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * wgs +
+                      (int)(blockIdx.x / kQueueSegs);
+        return q < queue_seg_begin(c.seg + 1, n_items) ? q : -1;
+    }
+    for (;;) {
+        const int beg = queue_seg_begin(c.seg, n_items);
+        const int size = queue_seg_begin(c.seg + 1, n_items) - beg;
+        int32_t* cnt = counter + c.seg * kCounterStride;
+        int q = 0;
+        if (lane == 0) {
+            if (c.done > 0) q = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (q < size) q = atomicAdd(cnt, 1);
+        }
+        q = __builtin_amdgcn_readfirstlane(q);
+        if (q < size) return beg + q;
+        // this segment is exhausted (for good: its counter only grows)
+        if (++c.done == kQueueSegs) return -1;
+        c.seg = c.seg + 1 == kQueueSegs ? 0 : c.seg + 1;
+    }
 }
 
 // Per-box constants.  The float32 forms work on offsets scaled by sigma

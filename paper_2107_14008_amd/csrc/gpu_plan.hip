@@ -1565,8 +1565,8 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
                        d.chi.as<double>(), d.cell.as<int4>(), d.cell_aux.as<int4>(),
                        d.cellc.as<double4>(), d.wcell.as<WalkCell>(), d.leafc.as<double4>());
     TRY(hipGetLastError());
-    TRY(d.x64.ensure(n * 32));
-    TRY(d.x32.ensure(n * 16));
+    TRY(d.x64.ensure(n * 32 + kReadAhead));
+    TRY(d.x32.ensure(n * 16 + kReadAhead));
     GatherArgs g{pos, mass, d.perm.as<int32_t>(), d.leaf.as<int4>(), d.leafc.as<double4>(),
                  d.boxes.as<BoxDev>(), d.x64.as<double4>(), d.x32.as<float4>(), (int32_t)nl};
     // With a side stream the particle records are gathered there, beside the
@@ -1863,7 +1863,7 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
 std::string gpu_make_items(DevPlan& d, const Plan& topo, int64_t n_p2p, int chunk, hipStream_t s,
                            PlanCounts& out) {
     const int64_t nl = (int64_t)topo.leaf_cell.size();
-    if (chunk <= 0) chunk = kAutoChunk;
+    if (chunk <= 0) chunk = auto_chunk(n_p2p, nl);
     TRY(d.cost.ensure((nl + 1) * 4));
     TRY(d.leaf_slot.ensure((nl + 1) * 4));
     TRY(d.tile_sums.ensure(sort_tiles(nl + 1) * 4 + 16));

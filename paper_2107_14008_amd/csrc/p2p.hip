@@ -32,12 +32,6 @@ constexpr float kTwoOverSqrtPiF = 1.12837916709551257390f;
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-__device__ __forceinline__ void shift_of(int s, double L, double& sx, double& sy, double& sz) {
-    sx = (double)(s % 3 - 1) * L;
-    sy = (double)((s / 3) % 3 - 1) * L;
-    sz = (double)(s / 9 - 1) * L;
-}
-
 // Wrap into [0, L); identical steps to the host plan (no contraction).
 __device__ __forceinline__ double wrap_coord(double x, double L) {
 #pragma clang fp contract(off)
@@ -303,8 +297,7 @@ __device__ __forceinline__ void leaf_f32_r2(const float4* __restrict__ src, int 
                                             float& ay, float& az, uint64_t near = 0,
                                             float sfloor = 0.f, float tiny = 0.f,
                                             float alpha = 0.f) {
-    int k = 0;
-    for (; k + 4 <= nj; k += 4) {
+    for (int k = 0; k < nj; k += 4) {
         const uint32_t g4 = (uint32_t)(live >> k) & 0xFu;
         if (g4 == 0) continue;
         const Src4<float4> b = *reinterpret_cast<const Src4<float4>*>(src + k);
@@ -315,10 +308,6 @@ __device__ __forceinline__ void leaf_f32_r2(const float4* __restrict__ src, int 
                 pair_f32_r2<LEVEL, UNI, BITS>(b.v[u], px, py, pz, smax, smin, shift, boff, tab, ax,
                                               ay, az);
     }
-    for (; k < nj; ++k)
-        if ((live >> k) & 1u)
-            pair_f32_r2<LEVEL, UNI, BITS>(src[k], px, py, pz, smax, smin, shift, boff, tab, ax, ay,
-                                          az);
     if constexpr (LEVEL == 1) {
         for (uint64_t m = near; m != 0; m &= m - 1)
             pair_f32_close<UNI>(src[__builtin_ctzll(m)], px, py, pz, sfloor, tiny, alpha, ax, ay,
@@ -328,10 +317,9 @@ __device__ __forceinline__ void leaf_f32_r2(const float4* __restrict__ src, int 
 
 // live_f32's cull, plus the sources whose squared distance to the targets'
 // box is below near2 (in `near`).
-__device__ __forceinline__ uint64_t live_near_f32(const float4* __restrict__ src, int nj, int lane,
-                                                  float3 plo, float3 phi, float rc2, float near2,
+__device__ __forceinline__ uint64_t live_near_f32(const float4 q, int nj, int lane, float3 plo,
+                                                  float3 phi, float rc2, float near2,
                                                   uint64_t& near) {
-    const float4 q = src[lane < nj ? lane : 0];
     const float bx = fmaxf(fmaxf(plo.x - q.x, q.x - phi.x), 0.f);
     const float by = fmaxf(fmaxf(plo.y - q.y, q.y - phi.y), 0.f);
     const float bz = fmaxf(fmaxf(plo.z - q.z, q.z - phi.z), 0.f);
@@ -480,19 +468,11 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
     const int lane = threadIdx.x & 63;
     const int dmax = n_tab - 1;
 
-    int seg = (int)(blockIdx.x % kQueueSegs), done = 0;
+    ItemCursor cur = item_cursor();
     for (;;) {
-        const int beg = queue_seg_begin(seg, n_items);
-        int q = 0;
-        if (lane == 0) q = atomicAdd(counter + seg * kCounterStride, 1);
-        q = uni(q);
-        if (q >= queue_seg_begin(seg + 1, n_items) - beg) {
-            // this segment is exhausted (for good: its counter only grows)
-            if (++done == kQueueSegs) break;
-            seg = seg + 1 == kQueueSegs ? 0 : seg + 1;
-            continue;
-        }
-        const int slot = uni(queue[beg + q]);
+        const int q = take_item(cur, lane, n_items, counter);
+        if (q < 0) break;
+        const int slot = uni(queue[q]);
         const int4 it = items[slot];
         const int il = uni(it.x), t0 = uni(it.y), t1 = uni(it.z);
         const int4 li = leaf[il];
@@ -533,47 +513,54 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
             wave_box(lo, hi);
             // compensated float32 item sums (accum32): s + c
             float3 s32 = make_float3(0.f, 0.f, 0.f), c32 = s32;
-            for (int t = t0; t < t1; ++t) {
-                const int js = uni(p2p_js[t]);
-                const int jl = js >> 5;
-                const int4 lj = leaf[jl];
-                const double4 cj = leafc[jl];
-                double sx, sy, sz;
-                shift_of(js & 31, bx.L, sx, sy, sz);
-                const float offx = (float)(((cj.x - ci.x) + sx) * sig);
-                const float offy = (float)(((cj.y - ci.y) + sy) * sig);
-                const float offz = (float)(((cj.z - ci.z) + sz) * sig);
+            for (int tb = t0; tb < t1; tb += 64) {
+              const int nt = min(64, t1 - tb);
+              const TaskLanes tl =
+                  load_tasks(p2p_js, tb + min(lane, nt - 1), leaf, leafc, ci, bx.L, sig);
+              // each task's sources, one per lane for the cull, are loaded one
+              // task ahead
+              int jn = lane_of(tl.first, 0), nn = lane_of(tl.count, 0);
+              float4 qn = x32[jn + min(lane, nn - 1)];
+              for (int k = 0; k < nt; ++k) {
+                const float4 ql = qn;
+                const float4* __restrict__ src = x32 + jn;
+                const int nj = nn;
+                if (k + 1 < nt) {
+                    jn = lane_of(tl.first, k + 1);
+                    nn = lane_of(tl.count, k + 1);
+                    qn = x32[jn + min(lane, nn - 1)];
+                }
+                const float offx = lane_of(tl.ox, k), offy = lane_of(tl.oy, k),
+                            offz = lane_of(tl.oz, k);
+                const float mu = lane_of(tl.mass, k);
                 const float px = pv.x - offx;
                 const float py = pv.y - offy;
                 const float pz = pv.z - offz;
-                const float4* __restrict__ src = x32 + uni(lj.x);
-                const int nj = uni(lj.y);
                 float fx = 0.f, fy = 0.f, fz = 0.f;
                 // targets in this frame: [lo - off, hi - off] per axis
                 // (exact: the shift is monotonic)
                 uint64_t near = 0;
                 const float3 blo = make_float3(lo.x - offx, lo.y - offy, lo.z - offz);
                 const float3 bhi = make_float3(hi.x - offx, hi.y - offy, hi.z - offz);
-                const uint64_t live = kLin ? live_near_f32(src, nj, lane, blo, bhi, rc2, near2, near)
-                                           : live_f32(src, nj, lane, blo, bhi, rc2);
+                const uint64_t live = kLin ? live_near_f32(ql, nj, lane, blo, bhi, rc2, near2, near)
+                                           : live_f32(ql, nj, lane, blo, bhi, rc2);
                 if constexpr (MODE == kFP32Exact) {
-                    for (int k = 0; k < nj; ++k)
-                        if ((live >> k) & 1u)
-                            pair_f32_exact(src[k], px, py, pz, rc2, tiny, bx.alpha_f, fx, fy, fz);
+                    for (int u = 0; u < nj; ++u)
+                        if ((live >> u) & 1u)
+                            pair_f32_exact(src[u], px, py, pz, rc2, tiny, bx.alpha_f, fx, fy, fz);
                 } else if constexpr (MODE == kFP32Table) {
 #pragma unroll 4
-                    for (int k = 0; k < nj; ++k)
-                        if ((live >> k) & 1u)
-                            pair_f32_table<LEVEL>(src[k], px, py, pz, rc2, tiny, bx.tab_scale_f,
+                    for (int u = 0; u < nj; ++u)
+                        if ((live >> u) & 1u)
+                            pair_f32_table<LEVEL>(src[u], px, py, pz, rc2, tiny, bx.tab_scale_f,
                                                   rnd, t03, t4, fx, fy, fz);
-                } else if (cj.w != 0.0) {
-                    // every source of the j leaf has mass cj.w (the gather
+                } else if (mu != 0.f) {
+                    // every source of the j leaf has mass mu (the gather
                     // marks such leaves): one multiplication per leaf
                     // instead of one per pair
                     leaf_f32_r2<LEVEL, true, BITS>(src, nj, live, px, py, pz, rc2, smin, r2shift,
                                                    r2boff, lds, fx, fy, fz, near, sfloor, tiny,
                                                    bx.alpha_f);
-                    const float mu = (float)cj.w;
                     fx *= mu;
                     fy *= mu;
                     fz *= mu;
@@ -591,6 +578,7 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                     ay += (double)fy;
                     az += (double)fz;
                 }
+              }
             }
             if constexpr (ACC32) {
                 ax = (double)s32.x + (double)c32.x;
@@ -630,7 +618,7 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                 const int s = js & 31;
                 const int4 lj = leaf[jl];
                 double sx, sy, sz;
-                shift_of(s, bx.L, sx, sy, sz);
+                image_shift(s, bx.L, sx, sy, sz);
                 const double4* __restrict__ src = x64 + uni(lj.x);
                 const int nj = uni(lj.y);
                 const uint64_t live =

@@ -7,6 +7,8 @@
 // contraction.
 #pragma once
 
+#include <algorithm>
+#include <cmath>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -84,14 +86,31 @@ std::string make_plan(Plan& plan, const std::vector<BoxParams>& boxes,
 void make_topology(Plan& plan, const std::vector<BoxParams>& boxes,
                    const std::vector<int64_t>& counts);
 
-// Tasks per work item when the caller leaves the choice to the library: an
-// item then holds at most 32 x 64 x 64 pair evaluations, a small part of a
-// wavefront's share of a large launch, so the longest-first queue ends with
-// little idle time, while the per-item partial sums (1.5 KB each, read by
-// the ordered reduction) stay few (measured at 128^3 and 256^3: 16 to 48
-// tasks give the same P2P time within 1 %, 8 is 20 % slower, whole rows
-// leave a tail).
+// Tasks per work item when the caller leaves the choice to the library.  At
+// most kAutoChunk: an item then holds at most 32 x 64 x 64 pair evaluations, a
+// small part of a wavefront's share of a large launch, so the longest-first
+// queue ends with little idle time, while the per-item partial sums (1.5 KB
+// each, read by the ordered reduction) stay few (measured at 128^3 and 256^3:
+// 16 to 48 tasks give the same P2P time within 1 %, 8 is 20 % slower, whole
+// rows leave a tail).  A smaller plan is cut finer, or a few long items bound
+// the launch while most waves idle; the best cut grows like the square root
+// of the task count.  Forward in us, best of 1 to 64 against 32: 16^3 float32
+// (5,158 tasks) 44 at 2 / 191; 24^3 (21,128) 59 at 4 / 196; 32^3 (40,452)
+// 101 at 4 to 8 / 231; 48^3 (178,646) 211 at 8 / 287; 64^3 (338,632) 364 at
+// 12 / 396; float64 exact 40^3 (81,020) 551 at 4 / 917.
+// A cut below kAutoChunk never gives more than kAutoItems items (each row
+// adds at most one to tasks / chunk): their partial sums then stay within
+// the scratch of pmfmm_forward_static.
 constexpr int kAutoChunk = 32;
+constexpr int64_t kAutoItems = 32768;
+
+inline int auto_chunk(int64_t n_tasks, int64_t n_leaves) {
+    if (n_leaves >= kAutoItems) return kAutoChunk;
+    const int64_t room = kAutoItems - n_leaves;
+    const int64_t least = (n_tasks + room - 1) / room;
+    const int64_t c = std::max<int64_t>(least, (int64_t)(std::sqrt((double)n_tasks) / 56.0 + 0.5));
+    return (int)std::min<int64_t>(kAutoChunk, std::max<int64_t>(c, 2));
+}
 
 // (Re)cuts the P2P rows into work items of at most `chunk` tasks
 // (0 = automatic) and orders the queue by decreasing pair count.
