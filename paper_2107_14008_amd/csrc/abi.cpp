@@ -121,6 +121,16 @@ int mode_of(const pmfmm_params& p) {
     return p.trunc == PMFMM_TRUNC_TABLE ? pmfmm::kFP32Table : pmfmm::kFP32Exact;
 }
 
+// The float64 exact form takes F from its table (device.h) when r_cut <= 6 r_s
+// in every box, and the polynomial of truncation_T_f64 otherwise.
+bool exact64(const pmfmm_params& p) { return p.precision == PMFMM_FP64 && p.trunc == PMFMM_TRUNC_EXACT; }
+
+bool within_f_table(const std::vector<pmfmm::BoxParams>& boxes) {
+    for (const auto& b : boxes)
+        if (!(b.r_cut / (2.0 * b.r_s) <= pmfmm::kFXcMax)) return false;
+    return true;
+}
+
 bool uses_r2(const pmfmm_params& p) { return p.precision == PMFMM_FP32 && p.trunc == PMFMM_TRUNC_R2; }
 // Either r^2 table: one x_c = r_cut / 2 r_s for all boxes, rebuilt when it changes.
 bool r2_table(const pmfmm_params& p) { return p.trunc == PMFMM_TRUNC_R2; }
@@ -341,6 +351,77 @@ std::vector<unsigned char> build_r2_table64(int per_octave, int deg, double xc) 
     return out;
 }
 
+// The F table of the float64 exact form (layout and ranges: device.h), built
+// once per process.  Per segment, with v = t / half width in [-1, 1]: the
+// Taylor coefficients of F about the middle to order kN from the equation
+//   y F' = -(3/2) F - (2 / sqrt(pi)) exp(-y)
+// (one erfc and one exp per segment, in long double), cut to degree 6 by
+// dropping the Chebyshev terms above it.
+const std::vector<unsigned char>& f_table() {
+    static const std::vector<unsigned char> table = [] {
+        constexpr int kN = 14, kD = 6;
+        using ld = long double;
+        // cheb[k][j]: coefficient of v^j in T_k; to_cheb: v^m in Chebyshev terms
+        ld cheb[kN + 1][kN + 1] = {}, low[kD + 1][kN + 1] = {};
+        cheb[0][0] = 1;
+        cheb[1][1] = 1;
+        for (int k = 2; k <= kN; ++k)
+            for (int j = 0; j <= kN; ++j)
+                cheb[k][j] = (j > 0 ? 2 * cheb[k - 1][j - 1] : 0) - cheb[k - 2][j];
+        for (int m = 0; m <= kN; ++m) {
+            // v^m = 2^(1-m) sum_q C(m, q) T_(m-2q), the T_0 term halved
+            ld binom = 1;
+            for (int q = 0; 2 * q <= m; ++q) {
+                const int k = m - 2 * q;
+                const ld w = std::ldexp(binom, 1 - m) * (k == 0 ? 0.5L : 1.0L);
+                if (k <= kD)
+                    for (int j = 0; j <= kD; ++j) low[j][m] += w * cheb[k][j];
+                binom = binom * (m - q) / (q + 1);
+            }
+        }
+        std::vector<unsigned char> out((size_t)pmfmm::kFAdjTableBytes, 0);
+        const ld two_sqrt_pi = 1.128379167095512573896158903121545172L;
+        for (int r = 0; r < pmfmm::kFUsedRows; ++r) {
+            const int e = pmfmm::kFEmin + (r >> pmfmm::kFBits), j = r & ((1 << pmfmm::kFBits) - 1);
+            const ld per = (ld)(1 << pmfmm::kFBits);
+            const ld y = std::ldexp(1 + (j + 0.5L) / per, e), half = std::ldexp(0.5L / per, e);
+            const ld x = std::sqrt(y), ey = std::exp(-y);
+            ld f[kN + 1];
+            f[0] = (std::erfc(x) + two_sqrt_pi * x * ey) / (y * x);
+            // (n + 1) f_(n+1) y = -(n + 3/2) f_n - (2 / sqrt(pi)) (-1)^n exp(-y) / n!
+            ld en = two_sqrt_pi * ey;
+            for (int n = 0; n < kN; ++n) {
+                f[n + 1] = -((n + 1.5L) * f[n] + en) / ((n + 1) * y);
+                en = -en / (n + 1);
+            }
+            ld hp = 1;
+            for (int n = 0; n <= kN; ++n) {
+                f[n] *= hp;
+                hp *= half;
+            }
+            hp = 1;
+            for (int k = 0; k <= kD; ++k) {
+                ld c = 0;
+                for (int n = 0; n <= kN; ++n) c += low[k][n] * f[n];
+                c /= hp;
+                hp *= half;
+                unsigned char* slot = out.data() + (size_t)8 * r;
+                if (k < 4) {
+                    const double v = (double)c;
+                    std::memcpy(slot + (size_t)(k + 2) * pmfmm::kFPlane, &v, 8);
+                } else {
+                    const float v = (float)c;
+                    std::memcpy(slot + (size_t)(k < 6 ? 0 : 1) * pmfmm::kFPlane + (k == 5 ? 4 : 0), &v, 4);
+                }
+            }
+            const double em = (double)ey;
+            std::memcpy(out.data() + (size_t)8 * r + (size_t)6 * pmfmm::kFPlane, &em, 8);
+        }
+        return out;
+    }();
+    return table;
+}
+
 std::vector<unsigned char> build_table(const pmfmm_params& p, double xc) {
     if (uses_r2(p)) return build_r2_table(p.table_size, p.table_level, xc);
     if (r2_table(p)) return build_r2_table64(p.table_size, p.table_level, xc);
@@ -557,9 +638,37 @@ int upload_items(pmfmm_ctx* ctx, hipStream_t s) {
     return PMFMM_OK;
 }
 
+int form_mode(const pmfmm_ctx* ctx) {
+    if (exact64(ctx->p) && within_f_table(ctx->plan.boxes)) return pmfmm::kFP64F;
+    return mode_of(ctx->p);
+}
+
+// The F table, on the device from its first use by the context on.
+int upload_f_table(pmfmm_ctx* ctx, hipStream_t s) {
+    if (ctx->d.ftable.p != nullptr) return PMFMM_OK;
+    const unsigned char* t = nullptr;
+    try {
+        t = f_table().data();
+    } catch (const std::bad_alloc&) {
+        return fail(PMFMM_ENOMEM, "host allocation failed while building the F table");
+    }
+    constexpr size_t bytes = pmfmm::kFAdjTableBytes;
+    HIP_TRY(ctx->d.ftable.ensure(bytes));
+    const hipError_t e = hipMemcpyAsync(ctx->d.ftable.p, t, bytes, hipMemcpyHostToDevice, s);
+    const hipError_t e2 = e != hipSuccess ? e : hipStreamSynchronize(s);
+    if (e2 != hipSuccess) ctx->d.ftable.release();
+    HIP_TRY(e2);
+    return PMFMM_OK;
+}
+
 // (Re)builds the table when the evaluation parameters changed, or, for the
 // r^2 table, the boxes' r_cut / r_s.
 int upload_table(pmfmm_ctx* ctx, hipStream_t s) {
+    if (exact64(ctx->p)) {
+        const int rc = form_mode(ctx) == pmfmm::kFP64F ? upload_f_table(ctx, s) : PMFMM_OK;
+        if (rc == PMFMM_OK) ctx->table_dirty = false;
+        return rc;
+    }
     const double xc = ctx->plan.boxes.empty() ? ctx->p.r_cut / (2.0 * ctx->p.r_s)
                                               : ctx->plan.boxes[0].r_cut / (2.0 * ctx->plan.boxes[0].r_s);
     if (!ctx->table_dirty && (!r2_table(ctx->p) || xc == ctx->table_xc)) return PMFMM_OK;
@@ -1176,7 +1285,7 @@ namespace {
 int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter, double* partial,
                    bool timing) {
     const pmfmm::Plan& pl = ctx->plan;
-    const int mode = mode_of(ctx->p);
+    const int mode = form_mode(ctx);
     int rc;
     if (timing) HIP_TRY(hipEventRecord(ctx->ev[0], s));
     if (ctx->far) {
@@ -1200,16 +1309,19 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
     a.counter = counter;
     a.partial = partial;
     a.boxes = ctx->d.boxes.as<pmfmm::BoxDev>();
-    a.table = ctx->d.table.p;
+    a.table = mode == pmfmm::kFP64F ? ctx->d.ftable.p : ctx->d.table.p;
     a.n_tab = ctx->p.table_size;
     a.level = ctx->p.table_level;
     a.round_floor = ctx->p.table_round == PMFMM_ROUND_FLOOR;
     a.accum32 = ctx->p.accum == PMFMM_ACCUM_FP32_TWOSUM;
     const bool tab = mode == pmfmm::kFP32Table || mode == pmfmm::kFP64Table || mode == pmfmm::kFP32R2 ||
                      mode == pmfmm::kFP64R2;
-    const size_t lds = tab ? ctx->table_host.size() : 0;
-    const int wg = std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : default_wg_waves(mode),
-                            pmfmm::p2p_max_threads(mode) / 64);
+    const size_t lds = mode == pmfmm::kFP64F ? (size_t)pmfmm::kFTableBytes : tab ? ctx->table_host.size() : 0;
+    // one workgroup of the F table's size fits a CU: it always has 16 waves
+    const int wg = mode == pmfmm::kFP64F
+                       ? 16
+                       : std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : default_wg_waves(mode),
+                                  pmfmm::p2p_max_threads(mode) / 64);
     const int grid = launch_grid(ctx, ctx->n_cu * pmfmm::p2p_blocks_per_cu(mode, wg, lds));
     HIP_TRY(pmfmm::launch_p2p(mode, a, wg, grid, lds, s));
     if (timing) HIP_TRY(hipEventRecord(ctx->ev[2], s));
@@ -1228,6 +1340,7 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
 
 // The table the build uploaded still matches the evaluation parameters.
 bool table_current(const pmfmm_ctx* ctx) {
+    if (form_mode(ctx) == pmfmm::kFP64F && ctx->d.ftable.p == nullptr) return false;
     const double xc = ctx->plan.boxes.empty() ? ctx->p.r_cut / (2.0 * ctx->p.r_s)
                                               : ctx->plan.boxes[0].r_cut / (2.0 * ctx->plan.boxes[0].r_s);
     return !ctx->table_dirty && (!r2_table(ctx->p) || xc == ctx->table_xc);

@@ -246,8 +246,8 @@ adjoint_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                 const double4* __restrict__ wsrc = w64 + uni(lj.x);
                 const int nj = uni(lj.y);
                 const uint64_t live =
-                    s == 13 ? live_f64<false>(src, nj, lane, lo, hi, 0.0, 0.0, 0.0, bx.rc2)
-                            : live_f64<true>(src, nj, lane, lo, hi, sx, sy, sz, bx.rc2);
+                    s == 13 ? live_f64<false>(src[lane < nj ? lane : 0], nj, lane, lo, hi, 0.0, 0.0, 0.0, bx.rc2)
+                            : live_f64<true>(src[lane < nj ? lane : 0], nj, lane, lo, hi, sx, sy, sz, bx.rc2);
                 if (s == 13) {
                     for (int k = 0; k < nj; ++k)
                         if ((live >> k) & 1u)

@@ -28,7 +28,8 @@ enum Mode : int {
     kFP32Exact = 2,
     kFP32Table = 3,
     kFP32R2 = 4,    // float32, segment table over r^2 (cutoff at the last row)
-    kFP64R2 = 5     // float64, segment table over r^2 (closest pairs evaluated exactly)
+    kFP64R2 = 5,    // float64, segment table over r^2 (closest pairs evaluated exactly)
+    kFP64F = 6      // float64 exact for r_cut <= 6 r_s, from the segment table of F(y)
 };
 
 constexpr bool is_fp32(int mode) {
@@ -36,9 +37,9 @@ constexpr bool is_fp32(int mode) {
 }
 
 // Largest workgroup of the P2P kernel: 16 waves share one LDS copy of a
-// table; the float64 exact form keeps its polynomial's coefficients and
-// a source record in registers and is compiled for 4-wave workgroups
-// (up to 512 VGPRs per lane instead of 128).
+// table; the polynomial float64 form keeps its coefficients and a source
+// record in registers and is compiled for 4-wave workgroups (up to 512 VGPRs
+// per lane instead of 128).
 constexpr int p2p_max_threads(int mode) { return mode == kFP64Exact ? 256 : 1024; }
 // Waves per SIMD the float32 forms must leave room for: two 16-wave
 // workgroups per CU (their tables fit twice in LDS), so at most 64 VGPRs and
@@ -84,6 +85,77 @@ constexpr int kAdjEmin = -26;
 constexpr int kAdjPlane = 1216;
 static_assert(((kR2Emax - kAdjEmin) << kAdjBits) + 1 <= kAdjPlane, "adjoint table rows");
 constexpr int kAdjTableBytes = 6 * kAdjPlane * 4;
+
+// Float64 exact form for cutoffs r_cut <= 6 r_s (x_c <= 3): with y = x^2 =
+// (r / 2 r_s)^2, T(x) / r^3 = F(y) / (2 r_s)^3, F(y) = T(sqrt(y)) y^(-3/2), one
+// function of y for every box.  F is tabulated on 2^kFBits segments per
+// octave of y from 2^kFEmin to 9 (indexed by the high word of y), each a
+// degree-6 polynomial in t = y - (segment middle) with c0 .. c3 in float64
+// and c4 .. c6 in float32: the terms from t^4 on are below 2e-8 of F (|t| <=
+// y / 256), so their float32 rounding is below 1e-15 / 1000 of F.  Measured
+// against 40-digit values the table gives F within 2.6e-16 (relative; rms
+// 7e-17) up to y = 8 and 3.4e-15 at y = 9, where T = 4e-4; the polynomial of
+// truncation_T_f64 with its square roots and products stays within 2e-15.
+// Layout: six arrays of kFRows eight-byte slots, (c4, c5), (c6, 0), (c0),
+// (c1), (c2) and (c3), a multiple of 512 bytes apart, so that a lookup is an
+// 8-byte, a 4-byte and two two-address LDS reads, all from one address
+// register; a seventh holds exp(-(segment middle)) for the adjoint.  Pairs closer than y = 2^kFEmin take
+// the series of F about y = 0.
+constexpr int kFBits = 7;
+constexpr int kFEmin = -16;
+constexpr int kFRows = 2496;
+constexpr int kFPlane = kFRows * 8;
+constexpr int kFTableBytes = 6 * kFPlane;
+constexpr int kFAdjTableBytes = 7 * kFPlane;
+constexpr int kFUsedRows = ((3 - kFEmin) << kFBits) + (1 << kFBits) / 8 + 1;   // y up to 9 and one more
+constexpr double kFXcMax = 3.0;
+static_assert(kFUsedRows <= kFRows && kFPlane % 512 == 0, "rows of the F table");
+
+struct FTab {
+    const unsigned char* tab;   // LDS
+    double rc2, a2;             // r_cut^2, 1 / (2 r_s)^2
+    uint32_t boff;              // -8 times the row of 2^kFEmin, mod 2^32
+    uint32_t mid;               // the bit that makes a segment's start its middle
+};
+
+// The two constants are kept opaque (an empty asm on their registers): the
+// address is then one shift and one shift-add, with the arrays' offsets in
+// the reads themselves, and the segment middle one bit-field insert.
+__device__ __forceinline__ FTab f_tab(const unsigned char* lds, double rc2, double alpha) {
+    FTab T{lds, rc2, alpha * alpha, 0u - (((uint32_t)(1023 + kFEmin) << kFBits) << 3),
+           1u << (19 - kFBits)};
+    asm volatile("" : "+s"(T.boff));
+    asm volatile("" : "+v"(T.mid));
+    return T;
+}
+
+// F(y) for 2^kFEmin <= y <= 9; hi: high word of y.  *t, *row as used.
+__device__ __forceinline__ double f_lookup(const FTab& T, double y, uint32_t hi, double* t_out,
+                                           const unsigned char** row_out) {
+    constexpr int sh = 20 - kFBits;
+    constexpr uint32_t m = ~((1u << sh) - 1u);
+    const unsigned char* __restrict__ c = T.tab + (((hi >> sh) << 3) + T.boff);
+    const double yc = __hiloint2double((int)((hi & m) | (T.mid & ~m)), 0);
+    const double t = y - yc;
+    const float tf = (float)t;
+    const float2 c45 = *reinterpret_cast<const float2*>(c);
+    const float c6 = *reinterpret_cast<const float*>(c + kFPlane);
+    double F = (double)fmaf(fmaf(c6, tf, c45.y), tf, c45.x);
+    F = fma(F, t, *reinterpret_cast<const double*>(c + 5 * kFPlane));
+    F = fma(F, t, *reinterpret_cast<const double*>(c + 4 * kFPlane));
+    F = fma(F, t, *reinterpret_cast<const double*>(c + 3 * kFPlane));
+    F = fma(F, t, *reinterpret_cast<const double*>(c + 2 * kFPlane));
+    *t_out = t;
+    *row_out = c;
+    return F;
+}
+
+// F(y) = y^(-3/2) - (4 / sqrt(pi)) (1/3 - y/5 + y^2/14 - ..) for 0 < y < 2^kFEmin
+// (the terms left out are below 1e-17 of F).
+__device__ __forceinline__ double f_close(double y) {
+    const double i = rsqrt(y);
+    return fma(i * i, i, 2.25675833419102514780 * fma(y, 0.2, -1.0 / 3.0));
+}
 
 // ------------------------------------------------------ truncation factor
 //
@@ -151,7 +223,7 @@ __device__ inline double truncation_T_f64(double x, double* ex) {
 // source with a pair inside r_cut always survives.
 
 // float32, in the j leaf's frame: targets p = pv - off in [plo, phi].
-// Lane k holds source k in q.
+// Lane k holds source k in q (also in live_f64).
 __device__ __forceinline__ uint64_t live_f32(const float4 q, int nj, int lane, float3 plo,
                                              float3 phi, float rc2) {
     const float bx = fmaxf(fmaxf(plo.x - q.x, q.x - phi.x), 0.f);
@@ -163,10 +235,9 @@ __device__ __forceinline__ uint64_t live_f32(const float4 q, int nj, int lane, f
 
 // float64: targets x in [lo, hi]; d = (q - x) + s as in the pair forms.
 template <bool SHIFTED>
-__device__ inline uint64_t live_f64(const double4* __restrict__ src, int nj, int lane,
+__device__ inline uint64_t live_f64(const double4& q, int nj, int lane,
                                              const double3& lo, const double3& hi, double sx,
                                              double sy, double sz, double rc2) {
-    const double4 q = src[lane < nj ? lane : 0];
     double d2;
     {
 #pragma clang fp contract(off)
@@ -223,6 +294,20 @@ __device__ __forceinline__ TaskLanes load_tasks(const int32_t* __restrict__ p2p_
     o.oz = (float)(((cj.z - ci.z) + sz) * sigma);
     o.mass = (float)cj.w;
     return o;
+}
+
+// The float64 forms' part: the j leaf and the image code.
+struct TaskLanes64 {
+    int first, count_code;      // count << 5 | code
+    float mass_flag;            // 1: all particles of the leaf have one mass
+};
+
+__device__ __forceinline__ TaskLanes64 load_tasks64(const int32_t* __restrict__ p2p_js, int t,
+                                                    const int4* __restrict__ leaf,
+                                                    const double4* __restrict__ leafc) {
+    const int js = p2p_js[t];
+    const int4 lj = leaf[js >> 5];
+    return TaskLanes64{lj.x, (lj.y << 5) | (js & 31), leafc[js >> 5].w != 0.0 ? 1.f : 0.f};
 }
 
 __device__ __forceinline__ int lane_of(int v, int k) { return __builtin_amdgcn_readlane(v, k); }

@@ -58,7 +58,7 @@ struct DevBuf {
 struct DevPlan {
     // used by the forward / adjoint passes
     DevBuf perm, leaf, leafc, js, items, queue, leaf_slot, partial, counter, boxes, table,
-        adj_table;
+        adj_table, ftable;
     DevBuf x64, x32, stage_pos, stage_mass, far;
     DevBuf cell, cell_aux, cellc, M, Lc, Lt, m2l_row, m2l_src, m2l_shift, level_cells;
     DevBuf w64, w32, fargrad;
@@ -100,7 +100,7 @@ struct DevPlan {
         fork_ev = m2l_done = geom_ev = gather_ev = nullptr;
         for (DevBuf* b : {&rowcnt_m2l, &tile_sums_m2l, &longrows_m2l}) b->release();
         for (DevBuf* b : {&perm, &leaf, &leafc, &js, &items, &queue, &leaf_slot, &partial, &counter,
-                          &boxes, &table, &x64, &x32, &stage_pos, &stage_mass, &far, &cell,
+                          &boxes, &table, &adj_table, &ftable, &x64, &x32, &stage_pos, &stage_mass, &far, &cell,
                           &cell_aux, &cellc, &M, &Lc, &Lt, &m2l_row, &m2l_src, &m2l_shift, &level_cells,
                           &w64, &w32, &fargrad, &p2p_row, &wpos, &keys, &keys_tmp, &plist, &plist_tmp, &hist,
                           &flag, &lv_first, &tile_sums, &pc, &pc_tmp, &clo, &chi, &wcell,

@@ -436,7 +436,53 @@ __device__ __forceinline__ void leaf_f64_r2(const double4* __restrict__ src, int
                 pair_f64_r2_close<SHIFTED>(src[k], xi, yi, zi, sx, sy, sz, T, ax, ay, az);
 }
 
+// float64 exact form from the F table (device.h).  The displacement, r^2 and
+// the cutoff test are those of pair_f64_exact; only lanes inside the cutoff
+// read the table.  UNI: the j leaf's sources share one mass, applied once per
+// leaf.  The item's sums are multiplied by 1 / (2 r_s)^3 at the end.
+template <bool UNI, bool SHIFTED>
+__device__ __forceinline__ void pair_f64_F(const double4 q, double xi, double yi, double zi,
+                                           double sx, double sy, double sz, const FTab& T,
+                                           double& ax, double& ay, double& az) {
+    double dx, dy, dz;
+    const double r2 = disp_r2<SHIFTED>(q, xi, yi, zi, sx, sy, sz, dx, dy, dz);
+    if (r2 < T.rc2) {
+        const double y = r2 * T.a2;
+        const uint32_t hi = (uint32_t)__double2hiint(y);
+        double F = 0.0;
+        if (hi >= (uint32_t)(1023 + kFEmin) << 20) {
+            double t;
+            const unsigned char* row;
+            F = f_lookup(T, y, hi, &t, &row);
+        } else if (r2 > 0.0) {
+            F = f_close(y);
+        }
+        const double g = UNI ? F : q.w * F;
+        ax = fma(g, dx, ax);
+        ay = fma(g, dy, ay);
+        az = fma(g, dz, az);
+    }
+}
+
+template <bool UNI, bool SHIFTED>
+__device__ __forceinline__ void leaf_f64_F(const double4* __restrict__ src, int nj, uint64_t live,
+                                           double xi, double yi, double zi, double sx, double sy,
+                                           double sz, const FTab& T, double& ax, double& ay,
+                                           double& az) {
+    for (int k = 0; k < nj; k += 4) {
+        const uint32_t g4 = (uint32_t)(live >> k) & 0xFu;
+        if (g4 == 0) continue;
+        const Src4<double4> b = *reinterpret_cast<const Src4<double4>*>(src + k);
+        pin(b);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (g4 & (1u << u))
+                pair_f64_F<UNI, SHIFTED>(b.v[u], xi, yi, zi, sx, sy, sz, T, ax, ay, az);
+    }
+}
+
 // LDS table layouts (bytes), matching the host builder in abi.cpp:
+//   float64 F table: device.h
 //   float64 r^2 table: double c0 .. c(NC-1) per row [16 2^bits rows]
 //   float32 r^2 table: float2 (c0, c1) [r2_rows(bits)] at 0, then
 //                      float2 (c2, 0) [r2_rows(bits)] at r2_plane_c2(bits)
@@ -463,7 +509,7 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
            int32_t round_floor) {
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr bool kTable = (MODE == kFP64Table) || (MODE == kFP32Table) || (MODE == kFP32R2) ||
-                            (MODE == kFP64R2);
+                            (MODE == kFP64R2) || (MODE == kFP64F);
     if constexpr (kTable) load_table(lds, table, table_bytes);
     const int lane = threadIdx.x & 63;
     const int dmax = n_tab - 1;
@@ -589,6 +635,60 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
             ax *= s2;
             ay *= s2;
             az *= s2;
+        } else if constexpr (MODE == kFP64F) {
+            const double4 pv = x64[pi];
+            const FTab T = f_tab(lds, bx.rc2, bx.alpha);
+            double3 lo = make_double3(pv.x, pv.y, pv.z), hi = lo;
+            wave_box(lo, hi);
+            for (int tb = t0; tb < t1; tb += 64) {
+                const int nt = min(64, t1 - tb);
+                const TaskLanes64 tl = load_tasks64(p2p_js, tb + min(lane, nt - 1), leaf, leafc);
+                int jn = lane_of(tl.first, 0), cn = lane_of(tl.count_code, 0);
+                double4 qn = x64[jn + min(lane, (cn >> 5) - 1)];
+                for (int k = 0; k < nt; ++k) {
+                    const double4 ql = qn;
+                    const double4* __restrict__ src = x64 + jn;
+                    const int nj = cn >> 5, s = cn & 31;
+                    const bool uni_mass = lane_of(tl.mass_flag, k) != 0.f;
+                    if (k + 1 < nt) {
+                        jn = lane_of(tl.first, k + 1);
+                        cn = lane_of(tl.count_code, k + 1);
+                        qn = x64[jn + min(lane, (cn >> 5) - 1)];
+                    }
+                    double fx = 0.0, fy = 0.0, fz = 0.0;
+                    if (s == 13) {
+                        const uint64_t live =
+                            live_f64<false>(ql, nj, lane, lo, hi, 0.0, 0.0, 0.0, T.rc2);
+                        if (uni_mass)
+                            leaf_f64_F<true, false>(src, nj, live, pv.x, pv.y, pv.z, 0.0, 0.0, 0.0,
+                                                    T, fx, fy, fz);
+                        else
+                            leaf_f64_F<false, false>(src, nj, live, pv.x, pv.y, pv.z, 0.0, 0.0,
+                                                     0.0, T, ax, ay, az);
+                    } else {
+                        double sx, sy, sz;
+                        image_shift(s, bx.L, sx, sy, sz);
+                        const uint64_t live =
+                            live_f64<true>(ql, nj, lane, lo, hi, sx, sy, sz, T.rc2);
+                        if (uni_mass)
+                            leaf_f64_F<true, true>(src, nj, live, pv.x, pv.y, pv.z, sx, sy, sz, T,
+                                                   fx, fy, fz);
+                        else
+                            leaf_f64_F<false, true>(src, nj, live, pv.x, pv.y, pv.z, sx, sy, sz, T,
+                                                    ax, ay, az);
+                    }
+                    if (uni_mass) {
+                        const double mu = src[0].w;
+                        ax = fma(mu, fx, ax);
+                        ay = fma(mu, fy, ay);
+                        az = fma(mu, fz, az);
+                    }
+                }
+            }
+            const double a3 = T.a2 * bx.alpha;
+            ax *= a3;
+            ay *= a3;
+            az *= a3;
         } else {
             const double4 pv = x64[pi];
             const double rc2 = bx.rc2;
@@ -622,8 +722,8 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                 const double4* __restrict__ src = x64 + uni(lj.x);
                 const int nj = uni(lj.y);
                 const uint64_t live =
-                    s == 13 ? live_f64<false>(src, nj, lane, lo, hi, 0.0, 0.0, 0.0, rc2)
-                            : live_f64<true>(src, nj, lane, lo, hi, sx, sy, sz, rc2);
+                    s == 13 ? live_f64<false>(src[lane < nj ? lane : 0], nj, lane, lo, hi, 0.0, 0.0, 0.0, rc2)
+                            : live_f64<true>(src[lane < nj ? lane : 0], nj, lane, lo, hi, sx, sy, sz, rc2);
                 if constexpr (MODE == kFP64R2) {
                     if (s == 13)
                         leaf_f64_r2<LEVEL + 1, false>(src, nj, live, pv.x, pv.y, pv.z, 0.0, 0.0,
@@ -815,6 +915,7 @@ hipError_t launch_p2p(int mode, const P2PArgs& a, int wg_waves, int grid_wgs, si
     if (a.n_items == 0) return hipSuccess;
     switch (mode) {
         case kFP64Exact: return launch_one<kFP64Exact, 0>(a, wg_waves, grid_wgs, 0, s);
+        case kFP64F: return launch_one<kFP64F, 0>(a, wg_waves, grid_wgs, lds, s);
         case kFP32Exact: return launch_one<kFP32Exact, 0>(a, wg_waves, grid_wgs, 0, s);
         case kFP32Table:
             switch (a.level) {
@@ -848,6 +949,7 @@ hipError_t launch_p2p(int mode, const P2PArgs& a, int wg_waves, int grid_wgs, si
 int p2p_blocks_per_cu(int mode, int wg_waves, size_t lds) {
     switch (mode) {
         case kFP64Exact: return occ_one<kFP64Exact, 0>(wg_waves, 0);
+        case kFP64F: return occ_one<kFP64F, 0>(wg_waves, lds);
         case kFP32Exact: return occ_one<kFP32Exact, 0>(wg_waves, 0);
         case kFP32Table: return occ_one<kFP32Table, 2>(wg_waves, lds);
         case kFP32R2: return occ_one<kFP32R2, 2>(wg_waves, lds);
