@@ -107,10 +107,10 @@ typedef struct pmfmm_params {
     /* scheduling of the P2P work (no effect on results) */
     int32_t chunk;       /* j-leaves per work item, 0 = automatic                 */
     int32_t wg_waves;    /* wavefronts per workgroup of the P2P and adjoint launches,
-                            0 = auto; the float64 exact P2P runs 16 for r_cut <=
-                            6 r_s whatever is asked (its table takes a compute
-                            unit's LDS) and at most 4 beyond, every float64
-                            adjoint at most 4                                  */
+                            0 = auto; the float64 exact P2P and every float64
+                            adjoint run 16 for r_cut <= 6 r_s whatever is asked
+                            (their table takes a compute unit's LDS) and at
+                            most 4 beyond                                      */
     int32_t grid_wgs;    /* workgroups of the persistent launch, 0 = auto         */
     int32_t timing;      /* 1: time each phase with HIP events (see get_timings)  */
     int32_t threads;     /* host threads of the host planner, 0 = all             */

@@ -1600,8 +1600,8 @@ int pmfmm_adjoint(pmfmm_ctx* ctx, const double* w, double* grad_pos, double* gra
     }
     const pmfmm::Plan& pl = ctx->plan;
     const int64_t n = pl.n;
-    HIP_TRY(ctx->d.w64.ensure((size_t)n * 32));
-    HIP_TRY(ctx->d.w32.ensure((size_t)n * 16));
+    HIP_TRY(ctx->d.w64.ensure((size_t)n * 32 + pmfmm::kReadAhead));
+    HIP_TRY(ctx->d.w32.ensure((size_t)n * 16 + pmfmm::kReadAhead));
     HIP_TRY(pmfmm::launch_gather_w(w, ctx->d.perm.as<int32_t>(), ctx->d.w64.as<double4>(), ctx->d.w32.as<float4>(),
                                    (int32_t)n, s));
     HIP_TRY(pmfmm::launch_zero_i32(ctx->d.counter.as<int32_t>(), pmfmm::kQueueSegs * pmfmm::kCounterStride, s));
@@ -1626,18 +1626,26 @@ int pmfmm_adjoint(pmfmm_ctx* ctx, const double* w, double* grad_pos, double* gra
     a.partial = ctx->d.partial.as<double>();
     a.boxes = ctx->d.boxes.as<pmfmm::BoxDev>();
     const int mode = mode_of(ctx->p);
+    const bool f_form = ctx->p.precision == PMFMM_FP64 && within_f_table(pl.boxes);
     if (uses_r2(ctx->p)) {
         // the float32 r^2 form: g and h from tables as well
         int rc = upload_adj_table(ctx, s);
         if (rc) return rc;
         a.table = ctx->d.adj_table.p;
+    } else if (f_form) {
+        // every float64 form evaluates g and h exactly
+        int rc = upload_f_table(ctx, s);
+        if (rc) return rc;
+        a.table = ctx->d.ftable.p;
     }
     // 8 waves per workgroup share the tables of the r^2 form (measured on
     // the 64^3 clustered workload: 1.02 ms against 1.13 ms with 4 and
     // 1.06 ms with 16; same results bit for bit).  The exact forms take
-    // within 2 % of the same time with 4, 8 or 16.
-    const int wg = std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : (a.table != nullptr ? 8 : 4),
-                            pmfmm::adjoint_max_threads(mode) / 64);
+    // within 2 % of the same time with 4, 8 or 16; the F table's one
+    // workgroup per CU always has 16.
+    const int wg = f_form ? 16
+                          : std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : (a.table != nullptr ? 8 : 4),
+                                     pmfmm::is_fp32(mode) ? 16 : 4);
     const int grid =
         launch_grid(ctx, ctx->n_cu * pmfmm::adjoint_blocks_per_cu(mode, wg, a.table != nullptr));
     HIP_TRY(pmfmm::launch_adjoint(mode, a, wg, grid, s));

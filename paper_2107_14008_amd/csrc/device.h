@@ -45,9 +45,6 @@ constexpr int p2p_max_threads(int mode) { return mode == kFP64Exact ? 256 : 1024
 // workgroups per CU (their tables fit twice in LDS), so at most 64 VGPRs and
 // the matching scalar registers per wave.
 constexpr int p2p_min_waves_per_simd(int mode) { return is_fp32(mode) ? 8 : 1; }
-// The same for the adjoint: every float64 form evaluates g and h exactly.
-constexpr int adjoint_max_threads(int mode) { return is_fp32(mode) ? 1024 : 256; }
-
 // r^2 table form: scaled r^2 covers [2^kR2Emin, 2^kR2Emax) (r_cut^2 = 2^kR2Emax).
 constexpr int kR2Emin = -35;
 constexpr int kR2Emax = 11;
@@ -269,6 +266,7 @@ struct TaskLanes {
     int first, count;      // particles of the j leaf
     float ox, oy, oz;      // its centre minus the i leaf's, images included, times sigma
     float mass;            // the mass all its particles have, or 0
+    int same;              // 1: that mass is also the i leaf's
 };
 
 __device__ __forceinline__ void image_shift(int s, double L, double& sx, double& sy, double& sz) {
@@ -293,21 +291,24 @@ __device__ __forceinline__ TaskLanes load_tasks(const int32_t* __restrict__ p2p_
     o.oy = (float)(((cj.y - ci.y) + sy) * sigma);
     o.oz = (float)(((cj.z - ci.z) + sz) * sigma);
     o.mass = (float)cj.w;
+    o.same = cj.w != 0.0 && cj.w == ci.w;
     return o;
 }
 
 // The float64 forms' part: the j leaf and the image code.
 struct TaskLanes64 {
     int first, count_code;      // count << 5 | code
-    float mass_flag;            // 1: all particles of the leaf have one mass
+    int mass;                   // 0: mixed masses, 1: one mass, 2: that of the i leaf
 };
 
 __device__ __forceinline__ TaskLanes64 load_tasks64(const int32_t* __restrict__ p2p_js, int t,
                                                     const int4* __restrict__ leaf,
-                                                    const double4* __restrict__ leafc) {
+                                                    const double4* __restrict__ leafc,
+                                                    double mass_i) {
     const int js = p2p_js[t];
     const int4 lj = leaf[js >> 5];
-    return TaskLanes64{lj.x, (lj.y << 5) | (js & 31), leafc[js >> 5].w != 0.0 ? 1.f : 0.f};
+    const double m = leafc[js >> 5].w;
+    return TaskLanes64{lj.x, (lj.y << 5) | (js & 31), m == 0.0 ? 0 : m == mass_i ? 2 : 1};
 }
 
 __device__ __forceinline__ int lane_of(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
@@ -483,7 +484,7 @@ struct AdjArgs {
     int32_t* counter;
     double* partial;            // (slot, 4, 64): grad x, y, z, m
     const BoxDev* boxes;
-    const void* table;          // float32 r^2 adjoint tables in device memory, or null
+    const void* table;          // tables of the form (launch_adjoint), or null
 };
 
 struct AdjReduceArgs {
@@ -523,8 +524,8 @@ hipError_t launch_rescale_x32(const int4* leaf, const double4* leafc, const BoxD
                               const double4* x64, float4* x32, int32_t n_leaves, hipStream_t s);
 hipError_t launch_gather_w(const double* w, const int32_t* perm, double4* w64,
                            float4* w32, int32_t n, hipStream_t s);
-// a.table: the float32 r^2 adjoint tables (float32 modes), or null for
-// the exact erfc / exp form.
+// a.table: the float32 r^2 adjoint tables (float32 modes) or the F table
+// (float64 modes), or null for the erfc / exp forms.
 hipError_t launch_adjoint(int mode, const AdjArgs& a, int wg_waves, int grid_wgs, hipStream_t s);
 hipError_t launch_adj_reduce(const AdjReduceArgs& a, hipStream_t s);
 

@@ -642,14 +642,14 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
             wave_box(lo, hi);
             for (int tb = t0; tb < t1; tb += 64) {
                 const int nt = min(64, t1 - tb);
-                const TaskLanes64 tl = load_tasks64(p2p_js, tb + min(lane, nt - 1), leaf, leafc);
+                const TaskLanes64 tl = load_tasks64(p2p_js, tb + min(lane, nt - 1), leaf, leafc, ci.w);
                 int jn = lane_of(tl.first, 0), cn = lane_of(tl.count_code, 0);
                 double4 qn = x64[jn + min(lane, (cn >> 5) - 1)];
                 for (int k = 0; k < nt; ++k) {
                     const double4 ql = qn;
                     const double4* __restrict__ src = x64 + jn;
                     const int nj = cn >> 5, s = cn & 31;
-                    const bool uni_mass = lane_of(tl.mass_flag, k) != 0.f;
+                    const bool uni_mass = lane_of(tl.mass, k) != 0;
                     if (k + 1 < nt) {
                         jn = lane_of(tl.first, k + 1);
                         cn = lane_of(tl.count_code, k + 1);
