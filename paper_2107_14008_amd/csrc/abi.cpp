@@ -121,8 +121,8 @@ int mode_of(const pmfmm_params& p) {
     return p.trunc == PMFMM_TRUNC_TABLE ? pmfmm::kFP32Table : pmfmm::kFP32Exact;
 }
 
-// The float64 exact form takes F from its table (device.h) when r_cut <= 6 r_s
-// in every box, and the polynomial of truncation_T_f64 otherwise.
+// The float64 exact form takes F from a table (device.h) when r_cut <= 6 r_s in
+// every box, and the polynomial of truncation_T_f64 otherwise.
 bool exact64(const pmfmm_params& p) { return p.precision == PMFMM_FP64 && p.trunc == PMFMM_TRUNC_EXACT; }
 
 bool within_f_table(const std::vector<pmfmm::BoxParams>& boxes) {
@@ -638,9 +638,14 @@ int upload_items(pmfmm_ctx* ctx, hipStream_t s) {
     return PMFMM_OK;
 }
 
+// The pair form the current plan is evaluated with.  The float64 r^2 form
+// reads the F table as well: its lookup (44 bytes) costs no more LDS than any
+// r^2 row but the smallest (40 to 56 bytes), it covers closer pairs, and it is
+// closer to the exact factor than any r^2 table that can be asked for (128^3
+// forward 6.9 ms with degree-6 rows, 5.67 ms from F).
 int form_mode(const pmfmm_ctx* ctx) {
-    if (exact64(ctx->p) && within_f_table(ctx->plan.boxes)) return pmfmm::kFP64F;
-    return mode_of(ctx->p);
+    const bool f = ctx->p.precision == PMFMM_FP64 && ctx->p.trunc != PMFMM_TRUNC_TABLE;
+    return f && within_f_table(ctx->plan.boxes) ? (int)pmfmm::kFP64F : mode_of(ctx->p);
 }
 
 // The F table, on the device from its first use by the context on.
@@ -664,9 +669,13 @@ int upload_f_table(pmfmm_ctx* ctx, hipStream_t s) {
 // (Re)builds the table when the evaluation parameters changed, or, for the
 // r^2 table, the boxes' r_cut / r_s.
 int upload_table(pmfmm_ctx* ctx, hipStream_t s) {
-    if (exact64(ctx->p)) {
-        const int rc = form_mode(ctx) == pmfmm::kFP64F ? upload_f_table(ctx, s) : PMFMM_OK;
-        if (rc == PMFMM_OK) ctx->table_dirty = false;
+    const bool f_form = form_mode(ctx) == pmfmm::kFP64F;
+    if (f_form || exact64(ctx->p)) {
+        const int rc = f_form ? upload_f_table(ctx, s) : PMFMM_OK;
+        if (rc == PMFMM_OK) {
+            ctx->table_dirty = false;
+            ctx->table_xc = -1.0;   // d.table is not of these parameters
+        }
         return rc;
     }
     const double xc = ctx->plan.boxes.empty() ? ctx->p.r_cut / (2.0 * ctx->p.r_s)
@@ -1340,7 +1349,7 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
 
 // The table the build uploaded still matches the evaluation parameters.
 bool table_current(const pmfmm_ctx* ctx) {
-    if (form_mode(ctx) == pmfmm::kFP64F && ctx->d.ftable.p == nullptr) return false;
+    if (form_mode(ctx) == pmfmm::kFP64F) return !ctx->table_dirty && ctx->d.ftable.p != nullptr;
     const double xc = ctx->plan.boxes.empty() ? ctx->p.r_cut / (2.0 * ctx->p.r_s)
                                               : ctx->plan.boxes[0].r_cut / (2.0 * ctx->plan.boxes[0].r_s);
     return !ctx->table_dirty && (!r2_table(ctx->p) || xc == ctx->table_xc);
