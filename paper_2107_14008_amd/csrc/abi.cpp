@@ -475,12 +475,17 @@ std::vector<unsigned char> build_table(const pmfmm_params& p, double xc) {
             }
             for (int k = 0; k < 5; ++k) a[5 * (size_t)i + k] = ck[k];
         }
+        // (c0, c1) pairs, (c2, c3) pairs, then c4
         out.resize((size_t)20 * m + 16);
-        float* f4 = reinterpret_cast<float*>(out.data());
-        float* f1 = reinterpret_cast<float*>(out.data() + 16 * (size_t)m);
+        float* f01 = reinterpret_cast<float*>(out.data());
+        float* f23 = f01 + 2 * (size_t)m;
+        float* f4 = f23 + 2 * (size_t)m;
         for (int i = 0; i < m; ++i) {
-            for (int k = 0; k < 4; ++k) f4[4 * i + k] = (float)a[5 * (size_t)i + k];
-            f1[i] = (float)a[5 * (size_t)i + 4];
+            for (int k = 0; k < 2; ++k) {
+                f01[2 * i + k] = (float)a[5 * (size_t)i + k];
+                f23[2 * i + k] = (float)a[5 * (size_t)i + 2 + k];
+            }
+            f4[i] = (float)a[5 * (size_t)i + 4];
         }
     } else {
         out.resize((size_t)40 * n + 16);

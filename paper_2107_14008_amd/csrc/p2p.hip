@@ -144,53 +144,65 @@ __device__ __forceinline__ void pair_f32_exact(const float4 q, float px, float p
                                                float& ay, float& az) {
     const float dx = q.x - px, dy = q.y - py, dz = q.z - pz;
     const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-    const bool ok = r2 < rc2;
-    const float r2c = __builtin_amdgcn_fmed3f(r2, tiny, rc2);
-    const float idr = __builtin_amdgcn_rsqf(r2c);
-    const float x = r2c * idr * alpha;
-    const float T = erfcf(x) + kTwoOverSqrtPiF * x * expf(-x * x);
-    const float g = ok ? q.w * T * (idr * idr * idr) : 0.f;
-    ax = fmaf(g, dx, ax);
-    ay = fmaf(g, dy, ay);
-    az = fmaf(g, dz, az);
+    if (r2 < rc2) {
+        const float r2c = fmaxf(r2, tiny);
+        const float idr = __builtin_amdgcn_rsqf(r2c);
+        const float x = r2c * idr * alpha;
+        const float T = erfcf(x) + kTwoOverSqrtPiF * x * expf(-x * x);
+        const float g = q.w * T * (idr * idr * idr);
+        ax = fmaf(g, dx, ax);
+        ay = fmaf(g, dy, ay);
+        az = fmaf(g, dz, az);
+    }
 }
 
 // Table form: u = x n_tab / 3 + rnd with rnd = 1/2 (nearest node) or 0
 // (node below); node d = floor(u), offset e = frac(u) in [0, 1).  The host
 // stores each node's Eq. (int) polynomial re-expanded in e (for the nearest
 // node it is centred at u = d + 1/2), so no clamp or float conversion of d
-// is needed; the table carries one node past x = 3.
-template <int LEVEL>
+// is needed; the table carries one node past x = 3.  Only lanes inside the
+// cutoff form 1/r and read the table (as in the r^2 form): at 90^3 the forward
+// took 1.42 ms with every pair evaluated and masked, 1.35 ms with the
+// branch, the arrays of eight-byte slots in place of 16-byte rows, and one
+// mass per leaf.  off23, off4: bytes from (c0, c1) of a node to its (c2, c3)
+// and c4 (two 8-byte slots and a 4-byte one per node).
+template <int LEVEL, bool UNI>
 __device__ __forceinline__ void pair_f32_table(const float4 q, float px, float py, float pz,
                                                float rc2, float tiny, float scale, float rnd,
-                                               const float4* __restrict__ t03,
-                                               const float* __restrict__ t4, float& ax, float& ay,
+                                               const unsigned char* __restrict__ tab,
+                                               uint32_t off23, uint32_t off4, float& ax, float& ay,
                                                float& az) {
     const float dx = q.x - px, dy = q.y - py, dz = q.z - pz;
     const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-    const bool ok = r2 < rc2;
-    const float r2c = __builtin_amdgcn_fmed3f(r2, tiny, rc2);
-    const float idr = __builtin_amdgcn_rsqf(r2c);
-    const float u = fmaf(r2c * idr, scale, rnd);
-    const int d = (int)u;
-    const float e = __builtin_amdgcn_fractf(u);
-    const float4 c = t03[d];
-    float T;
-    if constexpr (LEVEL == 0) {
-        T = c.x;
-    } else if constexpr (LEVEL == 1) {
-        T = fmaf(c.y, e, c.x);
-    } else if constexpr (LEVEL == 2) {
-        T = fmaf(fmaf(c.z, e, c.y), e, c.x);
-    } else if constexpr (LEVEL == 3) {
-        T = fmaf(fmaf(fmaf(c.w, e, c.z), e, c.y), e, c.x);
-    } else {
-        T = fmaf(fmaf(fmaf(fmaf(t4[d], e, c.w), e, c.z), e, c.y), e, c.x);
+    if (r2 < rc2) {
+        const float r2c = fmaxf(r2, tiny);
+        const float idr = __builtin_amdgcn_rsqf(r2c);
+        const float u = fmaf(r2c * idr, scale, rnd);
+        const uint32_t d = (uint32_t)u;
+        const float e = __builtin_amdgcn_fractf(u);
+        const float2 c01 = *reinterpret_cast<const float2*>(tab + 8 * d);
+        float T;
+        if constexpr (LEVEL == 0) {
+            T = c01.x;
+        } else if constexpr (LEVEL == 1) {
+            T = fmaf(c01.y, e, c01.x);
+        } else if constexpr (LEVEL == 2) {
+            const float c2 = *reinterpret_cast<const float*>(tab + (off23 + 8 * d));
+            T = fmaf(fmaf(c2, e, c01.y), e, c01.x);
+        } else {
+            const float2 c23 = *reinterpret_cast<const float2*>(tab + (off23 + 8 * d));
+            if constexpr (LEVEL == 3) {
+                T = fmaf(fmaf(fmaf(c23.y, e, c23.x), e, c01.y), e, c01.x);
+            } else {
+                const float c4 = *reinterpret_cast<const float*>(tab + (off4 + 4 * d));
+                T = fmaf(fmaf(fmaf(fmaf(c4, e, c23.y), e, c23.x), e, c01.y), e, c01.x);
+            }
+        }
+        const float g = (UNI ? T : q.w * T) * (idr * idr * idr);
+        ax = fmaf(g, dx, ax);
+        ay = fmaf(g, dy, ay);
+        az = fmaf(g, dz, az);
     }
-    const float g = ok ? q.w * T * (idr * idr * idr) : 0.f;
-    ax = fmaf(g, dx, ax);
-    ay = fmaf(g, dy, ay);
-    az = fmaf(g, dz, az);
 }
 
 // s + c += x with Knuth's TwoSum: the rounding error of s + x, recovered
@@ -285,6 +297,20 @@ __device__ __forceinline__ void pair_f32_close(const float4 q, float px, float p
     }
 }
 
+// The sources of a j leaf in `live`, four per 64-byte scalar load.
+template <class F>
+__device__ __forceinline__ void leaf_f32(const float4* __restrict__ src, int nj, uint64_t live, F pair) {
+    for (int k = 0; k < nj; k += 4) {
+        const uint32_t g4 = (uint32_t)(live >> k) & 0xFu;
+        if (g4 == 0) continue;
+        const Src4<float4> b = *reinterpret_cast<const Src4<float4>*>(src + k);
+        pin(b);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (g4 & (1u << u)) pair(b.v[u]);
+    }
+}
+
 // The pairs of one j leaf in the float32 r^2 form: four sources per 64-byte
 // scalar load, ahead of the masked table reads.  With a linear table
 // (LEVEL 1), the sources in `near` (those that may come closer than the
@@ -297,17 +323,9 @@ __device__ __forceinline__ void leaf_f32_r2(const float4* __restrict__ src, int 
                                             float& ay, float& az, uint64_t near = 0,
                                             float sfloor = 0.f, float tiny = 0.f,
                                             float alpha = 0.f) {
-    for (int k = 0; k < nj; k += 4) {
-        const uint32_t g4 = (uint32_t)(live >> k) & 0xFu;
-        if (g4 == 0) continue;
-        const Src4<float4> b = *reinterpret_cast<const Src4<float4>*>(src + k);
-        pin(b);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (g4 & (1u << u))
-                pair_f32_r2<LEVEL, UNI, BITS>(b.v[u], px, py, pz, smax, smin, shift, boff, tab, ax,
-                                              ay, az);
-    }
+    leaf_f32(src, nj, live, [&](const float4 q) {
+        pair_f32_r2<LEVEL, UNI, BITS>(q, px, py, pz, smax, smin, shift, boff, tab, ax, ay, az);
+    });
     if constexpr (LEVEL == 1) {
         for (uint64_t m = near; m != 0; m &= m - 1)
             pair_f32_close<UNI>(src[__builtin_ctzll(m)], px, py, pz, sfloor, tiny, alpha, ax, ay,
@@ -488,7 +506,8 @@ __device__ __forceinline__ void leaf_f64_F(const double4* __restrict__ src, int 
 //                      float2 (c2, 0) [r2_rows(bits)] at r2_plane_c2(bits)
 //   linear float32 r^2 table: float2 (c0, c1) [r2_rows_lin(bits)], the
 //                      first and the last row zero
-//   float32: float4 c0..c3 [n_tab + 1], then float c4 [n_tab + 1]
+//   float32: float2 (c0, c1) [n_tab + 1], float2 (c2, c3) [n_tab + 1], then
+//            float c4 [n_tab + 1]
 //   float64: double2 (c0, c1) [n_tab], double2 (c2, c3) [n_tab], double c4 [n_tab]
 __device__ __forceinline__ void load_table(unsigned char* lds, const void* __restrict__ table,
                                            int bytes) {
@@ -533,8 +552,7 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
             const float rc2 = bx.rc2_f, tiny = bx.tiny_f;
             const double sig = bx.sigma;
             const float rnd = round_floor ? 0.f : 0.5f;
-            const float4* t03 = reinterpret_cast<const float4*>(lds);
-            const float* t4 = reinterpret_cast<const float*>(lds + 16 * (n_tab + 1));
+            const uint32_t off23 = 8u * (uint32_t)(n_tab + 1), off4 = 2u * off23;
             // r^2 table: n_tab = segments per octave = 2^bits (runtime values,
             // so that the address is one shift and one shift-add)
             const uint32_t r2bits = 31u - (uint32_t)__builtin_clz((uint32_t)n_tab);
@@ -591,15 +609,24 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                 const uint64_t live = kLin ? live_near_f32(ql, nj, lane, blo, bhi, rc2, near2, near)
                                            : live_f32(ql, nj, lane, blo, bhi, rc2);
                 if constexpr (MODE == kFP32Exact) {
-                    for (int u = 0; u < nj; ++u)
-                        if ((live >> u) & 1u)
-                            pair_f32_exact(src[u], px, py, pz, rc2, tiny, bx.alpha_f, fx, fy, fz);
+                    leaf_f32(src, nj, live, [&](const float4 q) {
+                        pair_f32_exact(q, px, py, pz, rc2, tiny, bx.alpha_f, fx, fy, fz);
+                    });
                 } else if constexpr (MODE == kFP32Table) {
-#pragma unroll 4
-                    for (int u = 0; u < nj; ++u)
-                        if ((live >> u) & 1u)
-                            pair_f32_table<LEVEL>(src[u], px, py, pz, rc2, tiny, bx.tab_scale_f,
-                                                  rnd, t03, t4, fx, fy, fz);
+                    if (mu != 0.f) {
+                        leaf_f32(src, nj, live, [&](const float4 q) {
+                            pair_f32_table<LEVEL, true>(q, px, py, pz, rc2, tiny, bx.tab_scale_f, rnd,
+                                                        lds, off23, off4, fx, fy, fz);
+                        });
+                        fx *= mu;
+                        fy *= mu;
+                        fz *= mu;
+                    } else {
+                        leaf_f32(src, nj, live, [&](const float4 q) {
+                            pair_f32_table<LEVEL, false>(q, px, py, pz, rc2, tiny, bx.tab_scale_f, rnd,
+                                                         lds, off23, off4, fx, fy, fz);
+                        });
+                    }
                 } else if (mu != 0.f) {
                     // every source of the j leaf has mass mu (the gather
                     // marks such leaves): one multiplication per leaf
