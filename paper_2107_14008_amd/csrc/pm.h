@@ -6,6 +6,7 @@
 #include <hipfft/hipfft.h>
 
 #include <cstdint>
+#include <vector>
 
 namespace pmfmm {
 
@@ -16,6 +17,12 @@ struct PMPlan {
     double* rk = nullptr;         // (n, n, n / 2 + 1) complex spectrum
     double* gk[3] = {nullptr, nullptr, nullptr};     // gradient spectra
     double* field[3] = {nullptr, nullptr, nullptr};  // (n, n, n) accelerations
+    // block deposit: sorted records, caller indices, bin counts and offsets,
+    // tiles; grown to the largest particle count seen
+    void* blk[4] = {nullptr, nullptr, nullptr, nullptr};
+    size_t blk_bytes[4] = {0, 0, 0, 0};
+    bool blk_cleared = false;     // the bin counts are zero
+    std::vector<void*> retired;   // outgrown buffers, freed by pm_release
 };
 
 // (Re)allocates the mesh and plans for n nodes per axis (kept while n stays

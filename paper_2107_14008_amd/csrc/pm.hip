@@ -70,6 +70,189 @@ __global__ void pm_deposit(const double* __restrict__ pos, const double* __restr
     }
 }
 
+// ---- Deposit by blocks of the mesh (pm_deposit above is the direct form)
+//
+// Eight float64 atomics per particle on a mesh shared by eight XCDs ran at
+// 37 G/s whatever the particles' order: 451 us of the 690 us call at 2.1 M
+// particles on 128^3.  Instead the particles are binned by block of the mesh
+// (one counting sort into at most kPmBins bins), each workgroup sums one
+// block's particles into an LDS tile (LDS atomics), writes the tile out
+// plainly, and each node adds the tiles that hold it.  A block with more than
+// kPmChunk particles is cut into several workgroups and tiles.
+constexpr int kPmBins = 4096;
+constexpr int kPmPer = 4096;      // particles of one workgroup of the sort
+constexpr int kPmChunk = 8192;    // particles of one workgroup of the deposit
+
+// Blocks of e[0] x e[1] x e[2] cells (the last ones of an axis may be
+// smaller), nb[a] per axis; a tile holds (e[0] + 1)(e[1] + 1)(e[2] + 1) nodes.
+struct PmBlocks {
+    int n, e[3], nb[3], tile;
+    __host__ __device__ int count() const { return nb[0] * nb[1] * nb[2]; }
+};
+
+__device__ __forceinline__ int pm_bin(const PmBlocks& b, int gx, int gy, int gz) {
+    return (gx / b.e[0] * b.nb[1] + gy / b.e[1]) * b.nb[2] + gz / b.e[2];
+}
+
+__device__ __forceinline__ int pm_bin_of(const PmBlocks& b, const double* __restrict__ pos, int64_t i,
+                                         double L) {
+    int g[3];
+    double w0, w1;
+    for (int a = 0; a < 3; ++a) cic_axis(pos[3 * i + a], L, b.n, g[a], w0, w1);
+    return pm_bin(b, g[0], g[1], g[2]);
+}
+
+// Particles per bin; base[wg bins + bin]: the workgroup's first slot in the
+// bin (written for the bins it has particles of).
+__global__ void __launch_bounds__(256)
+pm_bin_count(const double* __restrict__ pos, int64_t np, double L, PmBlocks b,
+             uint32_t* __restrict__ count, uint32_t* __restrict__ base) {
+    __shared__ uint32_t h[kPmBins];
+    const int bins = b.count();
+    for (int k = threadIdx.x; k < bins; k += 256) h[k] = 0u;
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * kPmPer;
+    for (int r = 0; r < kPmPer; r += 256) {
+        const int64_t i = i0 + r + threadIdx.x;
+        if (i < np) atomicAdd(&h[pm_bin_of(b, pos, i, L)], 1u);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < bins; k += 256)
+        if (h[k]) base[(size_t)blockIdx.x * bins + k] = atomicAdd(&count[k], h[k]);
+}
+
+// start[k]: first sorted particle of bin k; cstart[k]: first deposit chunk of
+// bin k (both with a total at [bins]); clears count for the next call.  One
+// workgroup, four bins per thread.
+__global__ void __launch_bounds__(1024)
+pm_bin_scan(int bins, uint32_t* __restrict__ count, uint32_t* __restrict__ start,
+            uint32_t* __restrict__ cstart) {
+    __shared__ uint64_t part[1024];
+    const int t = threadIdx.x;
+    uint64_t v[kPmBins / 1024], sum = 0;
+    for (int j = 0; j < kPmBins / 1024; ++j) {
+        const int k = t * (kPmBins / 1024) + j;
+        const uint32_t c = k < bins ? count[k] : 0u;
+        v[j] = (uint64_t)c | ((uint64_t)((c + kPmChunk - 1) / kPmChunk) << 32);
+        sum += v[j];
+        if (k < bins) count[k] = 0u;
+    }
+    part[t] = sum;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const uint64_t x = t >= off ? part[t - off] : 0ull;
+        __syncthreads();
+        part[t] += x;
+        __syncthreads();
+    }
+    uint64_t run = part[t] - sum;
+    for (int j = 0; j < kPmBins / 1024; ++j) {
+        const int k = t * (kPmBins / 1024) + j;
+        if (k <= bins) {
+            start[k] = (uint32_t)run;
+            cstart[k] = (uint32_t)(run >> 32);
+        }
+        run += v[j];
+        if (k + 1 == kPmBins && bins == kPmBins) {
+            start[bins] = (uint32_t)run;
+            cstart[bins] = (uint32_t)(run >> 32);
+        }
+    }
+}
+
+// Particle records (x, y, z, m) and caller indices in bin order.
+__global__ void __launch_bounds__(256)
+pm_bin_scatter(const double* __restrict__ pos, const double* __restrict__ mass, int64_t np, double L,
+               PmBlocks b, const uint32_t* __restrict__ start, const uint32_t* __restrict__ base,
+               double4* __restrict__ rec, uint32_t* __restrict__ idx) {
+    __shared__ uint32_t off[kPmBins];
+    const int bins = b.count();
+    for (int k = threadIdx.x; k < bins; k += 256)
+        off[k] = start[k] + base[(size_t)blockIdx.x * bins + k];   // unused bins: any value
+    __syncthreads();
+    const int64_t i0 = (int64_t)blockIdx.x * kPmPer;
+    for (int r = 0; r < kPmPer; r += 256) {
+        const int64_t i = i0 + r + threadIdx.x;
+        if (i >= np) continue;
+        const uint32_t s = atomicAdd(&off[pm_bin_of(b, pos, i, L)], 1u);
+        rec[s] = make_double4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]);
+        idx[s] = (uint32_t)i;
+    }
+}
+
+// One chunk of a block's particles into its tile.
+__global__ void __launch_bounds__(256)
+pm_tile_deposit(const double4* __restrict__ rec, double L, PmBlocks b,
+                const uint32_t* __restrict__ start, const uint32_t* __restrict__ cstart,
+                double* __restrict__ tiles) {
+    extern __shared__ double tile[];
+    const int bins = b.count();
+    const uint32_t c = blockIdx.x;
+    if (c >= cstart[bins]) return;
+    int lo = 0, hi = bins - 1;   // the bin whose chunks hold c
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (cstart[mid] <= c) lo = mid; else hi = mid - 1;
+    }
+    const int bz = lo % b.nb[2], by = lo / b.nb[2] % b.nb[1], bx = lo / (b.nb[2] * b.nb[1]);
+    const int o[3] = {bx * b.e[0], by * b.e[1], bz * b.e[2]};
+    for (int k = threadIdx.x; k < b.tile; k += 256) tile[k] = 0.0;
+    __syncthreads();
+    const uint32_t p0 = start[lo] + (c - cstart[lo]) * kPmChunk;
+    const uint32_t p1 = min(start[lo + 1], p0 + kPmChunk);
+    const double inv_cell = (double)b.n / L;
+    const int sy = b.e[2] + 1, sx = (b.e[1] + 1) * sy;
+    for (uint32_t p = p0 + threadIdx.x; p < p1; p += 256) {
+        const double4 q = rec[p];
+        int gx, gy, gz;
+        double wx[2], wy[2], wz[2];
+        cic_axis(q.x, L, b.n, gx, wx[0], wx[1]);
+        cic_axis(q.y, L, b.n, gy, wy[0], wy[1]);
+        cic_axis(q.z, L, b.n, gz, wz[0], wz[1]);
+        const double mi = q.w * inv_cell * inv_cell * inv_cell;
+        double* t0 = tile + (gx - o[0]) * sx + (gy - o[1]) * sy + (gz - o[2]);
+        for (int dx = 0; dx < 2; ++dx)
+            for (int dy = 0; dy < 2; ++dy)
+                for (int dz = 0; dz < 2; ++dz)
+                    atomicAdd(t0 + dx * sx + dy * sy + dz, mi * wx[dx] * wy[dy] * wz[dz]);
+    }
+    __syncthreads();
+    double* out = tiles + (size_t)c * b.tile;
+    for (int k = threadIdx.x; k < b.tile; k += 256) out[k] = tile[k];
+}
+
+// rho of every node: its own block's tiles, and, on a block's lower face, the
+// upper face of the blocks below (periodic).
+__global__ void __launch_bounds__(256)
+pm_tile_sum(PmBlocks b, const uint32_t* __restrict__ cstart, const double* __restrict__ tiles,
+            double* __restrict__ rho) {
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int n = b.n;
+    if (q >= (int64_t)n * n * n) return;
+    const int g[3] = {(int)(q / ((int64_t)n * n)), (int)(q / n % n), (int)(q % n)};
+    int blk[3][2], loc[3][2], m[3];
+    for (int a = 0; a < 3; ++a) {
+        blk[a][0] = g[a] / b.e[a];
+        loc[a][0] = g[a] - blk[a][0] * b.e[a];
+        m[a] = 1;
+        if (loc[a][0] == 0) {
+            blk[a][1] = blk[a][0] == 0 ? b.nb[a] - 1 : blk[a][0] - 1;
+            loc[a][1] = min(b.e[a], n - blk[a][1] * b.e[a]);
+            m[a] = 2;
+        }
+    }
+    double s = 0.0;
+    for (int x = 0; x < m[0]; ++x)
+        for (int y = 0; y < m[1]; ++y)
+            for (int z = 0; z < m[2]; ++z) {
+                const int k = (blk[0][x] * b.nb[1] + blk[1][y]) * b.nb[2] + blk[2][z];
+                const int at = (loc[0][x] * (b.e[1] + 1) + loc[1][y]) * (b.e[2] + 1) + loc[2][z];
+                const uint32_t c1 = cstart[k + 1];
+                for (uint32_t c = cstart[k]; c < c1; ++c) s += tiles[(size_t)c * b.tile + at];
+            }
+    rho[q] = s;
+}
+
 __device__ __forceinline__ double sinc(double x) { return x == 0.0 ? 1.0 : sin(x) / x; }
 
 // One thread per mode of the half spectrum (n, n, n / 2 + 1): the three
@@ -114,14 +297,28 @@ __global__ void pm_green(const double2* __restrict__ rk, int n, double L, double
     az[q] = make_double2(kzz * pi, -kzz * pr);
 }
 
-__global__ void pm_interp(const double* __restrict__ pos, int64_t np, double L, int n,
+// SORTED: the particles' records in bin order (their nodes then come from a
+// few lines that stay in the L2), written to the caller's places by idx.
+template <bool SORTED>
+__global__ void pm_interp(const double* __restrict__ pos, const double4* __restrict__ rec,
+                          const uint32_t* __restrict__ idx, int64_t np, double L, int n,
                           const double* __restrict__ fx, const double* __restrict__ fy,
                           const double* __restrict__ fz, double* __restrict__ acc) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= np) return;
     int g[3];
     double w[3][2];
-    for (int a = 0; a < 3; ++a) cic_axis(pos[3 * i + a], L, n, g[a], w[a][0], w[a][1]);
+    double x[3];
+    if constexpr (SORTED) {
+        const double4 q = rec[i];
+        x[0] = q.x;
+        x[1] = q.y;
+        x[2] = q.z;
+        i = (int64_t)idx[i];
+    } else {
+        for (int a = 0; a < 3; ++a) x[a] = pos[3 * i + a];
+    }
+    for (int a = 0; a < 3; ++a) cic_axis(x[a], L, n, g[a], w[a][0], w[a][1]);
     double s[3] = {0.0, 0.0, 0.0};
     for (int dx = 0; dx < 2; ++dx) {
         const int x = g[0] + dx < n ? g[0] + dx : 0;
@@ -143,6 +340,63 @@ __global__ void pm_interp(const double* __restrict__ pos, int64_t np, double L, 
 }
 
 inline unsigned blocks_of(int64_t m) { return (unsigned)((m + 255) / 256); }
+
+}  // namespace
+
+namespace {
+
+// Block edges for an n^3 mesh: at most kPmBins blocks, enough of them for the
+// 256 CUs where the mesh allows it, tiles of 6 to 39 KB.
+PmBlocks pm_blocks(int n) {
+    PmBlocks b{};
+    b.n = n;
+    b.e[0] = n <= 128 ? 8 : 16;
+    b.e[1] = b.e[2] = n <= 64 ? 8 : 16;
+    b.tile = 1;
+    for (int a = 0; a < 3; ++a) {
+        b.nb[a] = (n + b.e[a] - 1) / b.e[a];
+        b.tile *= b.e[a] + 1;
+    }
+    return b;
+}
+
+// The block form's buffers for np particles; false when the direct form is to
+// be used: meshes beyond 256^3 (more blocks than kPmBins), few particles (the
+// whole call at 32^3 particles and mesh: 92 us by blocks, 98 us direct; the
+// gain shrinks with the particles), no memory, or buffers to grow while the
+// stream is being captured.
+constexpr int64_t kPmMinParticles = 16384;
+
+bool pm_block_buffers(PMPlan& p, int64_t np, hipStream_t s) {
+    if (p.n > 256 || np < kPmMinParticles || np > (int64_t)UINT32_MAX) return false;
+    const PmBlocks b = pm_blocks(p.n);
+    const size_t bins = (size_t)b.count(), wgs = (size_t)((np + kPmPer - 1) / kPmPer);
+    const size_t chunks = bins + (size_t)(np / kPmChunk) + 1;
+    const size_t words = 3 * (bins + 8) + wgs * bins;
+    const size_t bytes[4] = {(size_t)np * 32, (size_t)np * 4, words * 4, chunks * b.tile * 8};
+    bool fits = true;
+    for (int k = 0; k < 4; ++k) fits = fits && p.blk_bytes[k] >= bytes[k];
+    if (fits) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    for (int k = 0; k < 4; ++k) {
+        if (p.blk_bytes[k] >= bytes[k]) continue;
+        // half as much again, and the old buffer kept until pm_release: a
+        // graph captured with it stays valid (all of them together take at
+        // most twice the newest)
+        const size_t want = p.blk[k] ? bytes[k] + bytes[k] / 2 : bytes[k];
+        void* q = nullptr;
+        if (hipMalloc(&q, want) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if (p.blk[k]) p.retired.push_back(p.blk[k]);
+        p.blk[k] = q;
+        p.blk_bytes[k] = want;
+        if (k == 2) p.blk_cleared = false;
+    }
+    return true;
+}
 
 }  // namespace
 
@@ -177,6 +431,13 @@ void pm_release(PMPlan& p) {
     if (p.rk) (void)hipFree(p.rk);
     p.rho = nullptr;
     p.rk = nullptr;
+    for (int k = 0; k < 4; ++k) {
+        if (p.blk[k]) (void)hipFree(p.blk[k]);
+        p.blk[k] = nullptr;
+        p.blk_bytes[k] = 0;
+    }
+    for (void* q : p.retired) (void)hipFree(q);
+    p.retired.clear();
     for (int a = 0; a < 3; ++a) {
         if (p.gk[a]) (void)hipFree(p.gk[a]);
         if (p.field[a]) (void)hipFree(p.field[a]);
@@ -190,11 +451,39 @@ hipError_t pm_long_range(PMPlan& p, const double* pos, const double* mass, int64
                          double r_s, double G, double* acc, hipStream_t s) {
     const int n = p.n;
     const int64_t n3 = (int64_t)n * n * n, nh = (int64_t)n * n * (n / 2 + 1);
-    hipLaunchKernelGGL(pm_zero, dim3(blocks_of(n3)), dim3(256), 0, s, p.rho, n3);
-    if (np > 0)
-        hipLaunchKernelGGL(pm_deposit, dim3(blocks_of(np)), dim3(256), 0, s, pos, mass, np, L, n, p.rho);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    hipError_t e;
+    const bool blocks = pm_block_buffers(p, np, s);
+    double4* rec = static_cast<double4*>(p.blk[0]);
+    uint32_t* idx = static_cast<uint32_t*>(p.blk[1]);
+    if (blocks) {
+        const PmBlocks b = pm_blocks(n);
+        const int bins = b.count();
+        uint32_t* count = static_cast<uint32_t*>(p.blk[2]);
+        uint32_t* start = count + bins + 8;
+        uint32_t* cstart = start + bins + 8;
+        uint32_t* base = cstart + bins + 8;
+        const unsigned wgs = (unsigned)((np + kPmPer - 1) / kPmPer);
+        const unsigned chunks = (unsigned)(bins + np / kPmChunk + 1);
+        if (!p.blk_cleared)
+            hipLaunchKernelGGL(pm_zero, dim3(blocks_of((bins + 8) / 2 + 1)), dim3(256), 0, s,
+                               reinterpret_cast<double*>(count), (int64_t)((bins + 1) / 2));
+        hipLaunchKernelGGL(pm_bin_count, dim3(wgs), dim3(256), 0, s, pos, np, L, b, count, base);
+        hipLaunchKernelGGL(pm_bin_scan, dim3(1), dim3(1024), 0, s, bins, count, start, cstart);
+        hipLaunchKernelGGL(pm_bin_scatter, dim3(wgs), dim3(256), 0, s, pos, mass, np, L, b, start, base,
+                           rec, idx);
+        hipLaunchKernelGGL(pm_tile_deposit, dim3(chunks), dim3(256), (size_t)b.tile * 8, s, rec, L, b,
+                           start, cstart, static_cast<double*>(p.blk[3]));
+        hipLaunchKernelGGL(pm_tile_sum, dim3(blocks_of(n3)), dim3(256), 0, s, b, cstart,
+                           static_cast<const double*>(p.blk[3]), p.rho);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        p.blk_cleared = true;   // pm_bin_scan leaves the counts zero
+    } else {
+        hipLaunchKernelGGL(pm_zero, dim3(blocks_of(n3)), dim3(256), 0, s, p.rho, n3);
+        if (np > 0)
+            hipLaunchKernelGGL(pm_deposit, dim3(blocks_of(np)), dim3(256), 0, s, pos, mass, np, L, n,
+                               p.rho);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
     if (hipfftExecD2Z(p.fwd, p.rho, reinterpret_cast<hipfftDoubleComplex*>(p.rk)) != HIPFFT_SUCCESS)
         return hipErrorUnknown;
     hipLaunchKernelGGL(pm_green, dim3(blocks_of(nh)), dim3(256), 0, s,
@@ -206,9 +495,12 @@ hipError_t pm_long_range(PMPlan& p, const double* pos, const double* mass, int64
         if (hipfftExecZ2D(p.inv, reinterpret_cast<hipfftDoubleComplex*>(p.gk[a]), p.field[a]) !=
             HIPFFT_SUCCESS)
             return hipErrorUnknown;
-    if (np > 0)
-        hipLaunchKernelGGL(pm_interp, dim3(blocks_of(np)), dim3(256), 0, s, pos, np, L, n, p.field[0],
-                           p.field[1], p.field[2], acc);
+    if (np > 0 && blocks)
+        hipLaunchKernelGGL(pm_interp<true>, dim3(blocks_of(np)), dim3(256), 0, s, nullptr, rec, idx, np,
+                           L, n, p.field[0], p.field[1], p.field[2], acc);
+    else if (np > 0)
+        hipLaunchKernelGGL(pm_interp<false>, dim3(blocks_of(np)), dim3(256), 0, s, pos, nullptr, nullptr,
+                           np, L, n, p.field[0], p.field[1], p.field[2], acc);
     return hipGetLastError();
 }
 
