@@ -81,43 +81,64 @@ __global__ void pm_deposit(const double* __restrict__ pos, const double* __restr
 // kPmChunk particles is cut into several workgroups and tiles.
 constexpr int kPmBins = 4096;
 constexpr int kPmPer = 4096;      // particles of one workgroup of the sort
-constexpr int kPmChunk = 8192;    // particles of one workgroup of the deposit
+constexpr int kPmChunk = 4096;    // particles of one workgroup of the deposit
 
 // Blocks of e[0] x e[1] x e[2] cells (the last ones of an axis may be
 // smaller), nb[a] per axis; a tile holds (e[0] + 1)(e[1] + 1)(e[2] + 1) nodes.
 struct PmBlocks {
-    int n, e[3], nb[3], tile;
+    int n, e[3], sh[3], nb[3], tile;   // e[a] = 1 << sh[a]
     __host__ __device__ int count() const { return nb[0] * nb[1] * nb[2]; }
 };
 
 __device__ __forceinline__ int pm_bin(const PmBlocks& b, int gx, int gy, int gz) {
-    return (gx / b.e[0] * b.nb[1] + gy / b.e[1]) * b.nb[2] + gz / b.e[2];
+    return ((gx >> b.sh[0]) * b.nb[1] + (gy >> b.sh[1])) * b.nb[2] + (gz >> b.sh[2]);
 }
 
-__device__ __forceinline__ int pm_bin_of(const PmBlocks& b, const double* __restrict__ pos, int64_t i,
-                                         double L) {
-    int g[3];
-    double w0, w1;
-    for (int a = 0; a < 3; ++a) cic_axis(pos[3 * i + a], L, b.n, g[a], w0, w1);
-    return pm_bin(b, g[0], g[1], g[2]);
+// The particles of one workgroup of the sort, kPmEach per thread: all their
+// positions are loaded before the first is binned (16 waves per workgroup;
+// with 4 waves and one load in flight the two passes took 84 us at 2.1 M
+// particles, now 67 us: 20 to count, 47 to scatter the 36-byte records).
+constexpr int kPmThreads = 1024;
+constexpr int kPmEach = kPmPer / kPmThreads;
+
+struct PmSlice {
+    double x[kPmEach][3];
+    int bin[kPmEach];    // -1 past the end
+};
+
+__device__ __forceinline__ PmSlice pm_slice(const PmBlocks& b, const double* __restrict__ pos,
+                                            int64_t np, double L) {
+    PmSlice s;
+    const int64_t i0 = (int64_t)blockIdx.x * kPmPer + threadIdx.x;
+#pragma unroll
+    for (int r = 0; r < kPmEach; ++r) {
+        const int64_t i = i0 + r * kPmThreads;
+        for (int a = 0; a < 3; ++a) s.x[r][a] = i < np ? pos[3 * i + a] : 0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < kPmEach; ++r) {
+        int g[3];
+        double w0, w1;
+        for (int a = 0; a < 3; ++a) cic_axis(s.x[r][a], L, b.n, g[a], w0, w1);
+        s.bin[r] = i0 + r * kPmThreads < np ? pm_bin(b, g[0], g[1], g[2]) : -1;
+    }
+    return s;
 }
 
 // Particles per bin; base[wg bins + bin]: the workgroup's first slot in the
 // bin (written for the bins it has particles of).
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kPmThreads)
 pm_bin_count(const double* __restrict__ pos, int64_t np, double L, PmBlocks b,
              uint32_t* __restrict__ count, uint32_t* __restrict__ base) {
     __shared__ uint32_t h[kPmBins];
     const int bins = b.count();
-    for (int k = threadIdx.x; k < bins; k += 256) h[k] = 0u;
+    const PmSlice s = pm_slice(b, pos, np, L);
+    for (int k = threadIdx.x; k < bins; k += kPmThreads) h[k] = 0u;
     __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * kPmPer;
-    for (int r = 0; r < kPmPer; r += 256) {
-        const int64_t i = i0 + r + threadIdx.x;
-        if (i < np) atomicAdd(&h[pm_bin_of(b, pos, i, L)], 1u);
-    }
+    for (int r = 0; r < kPmEach; ++r)
+        if (s.bin[r] >= 0) atomicAdd(&h[s.bin[r]], 1u);
     __syncthreads();
-    for (int k = threadIdx.x; k < bins; k += 256)
+    for (int k = threadIdx.x; k < bins; k += kPmThreads)
         if (h[k]) base[(size_t)blockIdx.x * bins + k] = atomicAdd(&count[k], h[k]);
 }
 
@@ -161,48 +182,65 @@ pm_bin_scan(int bins, uint32_t* __restrict__ count, uint32_t* __restrict__ start
 }
 
 // Particle records (x, y, z, m) and caller indices in bin order.
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kPmThreads)
 pm_bin_scatter(const double* __restrict__ pos, const double* __restrict__ mass, int64_t np, double L,
                PmBlocks b, const uint32_t* __restrict__ start, const uint32_t* __restrict__ base,
                double4* __restrict__ rec, uint32_t* __restrict__ idx) {
     __shared__ uint32_t off[kPmBins];
     const int bins = b.count();
-    for (int k = threadIdx.x; k < bins; k += 256)
+    const PmSlice s = pm_slice(b, pos, np, L);
+    for (int k = threadIdx.x; k < bins; k += kPmThreads)
         off[k] = start[k] + base[(size_t)blockIdx.x * bins + k];   // unused bins: any value
     __syncthreads();
-    const int64_t i0 = (int64_t)blockIdx.x * kPmPer;
-    for (int r = 0; r < kPmPer; r += 256) {
-        const int64_t i = i0 + r + threadIdx.x;
-        if (i >= np) continue;
-        const uint32_t s = atomicAdd(&off[pm_bin_of(b, pos, i, L)], 1u);
-        rec[s] = make_double4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], mass[i]);
-        idx[s] = (uint32_t)i;
+    const int64_t i0 = (int64_t)blockIdx.x * kPmPer + threadIdx.x;
+    for (int r = 0; r < kPmEach; ++r) {
+        if (s.bin[r] < 0) continue;
+        const int64_t i = i0 + r * kPmThreads;
+        const uint32_t at = atomicAdd(&off[s.bin[r]], 1u);
+        rec[at] = make_double4(s.x[r][0], s.x[r][1], s.x[r][2], mass[i]);
+        idx[at] = (uint32_t)i;
     }
 }
 
-// One chunk of a block's particles into its tile.
-__global__ void __launch_bounds__(256)
-pm_tile_deposit(const double4* __restrict__ rec, double L, PmBlocks b,
-                const uint32_t* __restrict__ start, const uint32_t* __restrict__ cstart,
-                double* __restrict__ tiles) {
-    extern __shared__ double tile[];
+// The block and the particles [p0, p1) of deposit chunk c; false past the last.
+struct PmChunk {
+    int o[3];
+    uint32_t p0, p1;
+};
+
+__device__ __forceinline__ bool pm_chunk(const PmBlocks& b, uint32_t c, const uint32_t* __restrict__ start,
+                                         const uint32_t* __restrict__ cstart, PmChunk& k) {
     const int bins = b.count();
-    const uint32_t c = blockIdx.x;
-    if (c >= cstart[bins]) return;
+    if (c >= cstart[bins]) return false;
     int lo = 0, hi = bins - 1;   // the bin whose chunks hold c
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (cstart[mid] <= c) lo = mid; else hi = mid - 1;
     }
-    const int bz = lo % b.nb[2], by = lo / b.nb[2] % b.nb[1], bx = lo / (b.nb[2] * b.nb[1]);
-    const int o[3] = {bx * b.e[0], by * b.e[1], bz * b.e[2]};
-    for (int k = threadIdx.x; k < b.tile; k += 256) tile[k] = 0.0;
+    k.o[0] = lo / (b.nb[2] * b.nb[1]) << b.sh[0];
+    k.o[1] = lo / b.nb[2] % b.nb[1] << b.sh[1];
+    k.o[2] = lo % b.nb[2] << b.sh[2];
+    k.p0 = start[lo] + (c - cstart[lo]) * kPmChunk;
+    k.p1 = min(start[lo + 1], k.p0 + kPmChunk);
+    return true;
+}
+
+// One chunk of a block's particles into its tile.  Bound by the LDS's float64
+// atomics: eight per particle.
+constexpr int kPmTileThreads = 512;
+
+__global__ void __launch_bounds__(kPmTileThreads)
+pm_tile_deposit(const double4* __restrict__ rec, double L, PmBlocks b,
+                const uint32_t* __restrict__ start, const uint32_t* __restrict__ cstart,
+                double* __restrict__ tiles) {
+    extern __shared__ double tile[];
+    PmChunk k;
+    if (!pm_chunk(b, blockIdx.x, start, cstart, k)) return;
+    for (int q = threadIdx.x; q < b.tile; q += kPmTileThreads) tile[q] = 0.0;
     __syncthreads();
-    const uint32_t p0 = start[lo] + (c - cstart[lo]) * kPmChunk;
-    const uint32_t p1 = min(start[lo + 1], p0 + kPmChunk);
     const double inv_cell = (double)b.n / L;
     const int sy = b.e[2] + 1, sx = (b.e[1] + 1) * sy;
-    for (uint32_t p = p0 + threadIdx.x; p < p1; p += 256) {
+    for (uint32_t p = k.p0 + threadIdx.x; p < k.p1; p += kPmTileThreads) {
         const double4 q = rec[p];
         int gx, gy, gz;
         double wx[2], wy[2], wz[2];
@@ -210,47 +248,104 @@ pm_tile_deposit(const double4* __restrict__ rec, double L, PmBlocks b,
         cic_axis(q.y, L, b.n, gy, wy[0], wy[1]);
         cic_axis(q.z, L, b.n, gz, wz[0], wz[1]);
         const double mi = q.w * inv_cell * inv_cell * inv_cell;
-        double* t0 = tile + (gx - o[0]) * sx + (gy - o[1]) * sy + (gz - o[2]);
+        double* t0 = tile + (gx - k.o[0]) * sx + (gy - k.o[1]) * sy + (gz - k.o[2]);
         for (int dx = 0; dx < 2; ++dx)
             for (int dy = 0; dy < 2; ++dy)
                 for (int dz = 0; dz < 2; ++dz)
                     atomicAdd(t0 + dx * sx + dy * sy + dz, mi * wx[dx] * wy[dy] * wz[dz]);
     }
     __syncthreads();
-    double* out = tiles + (size_t)c * b.tile;
-    for (int k = threadIdx.x; k < b.tile; k += 256) out[k] = tile[k];
+    double* out = tiles + (size_t)blockIdx.x * b.tile;
+    for (int q = threadIdx.x; q < b.tile; q += kPmTileThreads) out[q] = tile[q];
+}
+
+// One chunk of a block's particles from tiles of the three fields in LDS,
+// written to the callers' places.  Bound by those scattered writes: 71 us at
+// 2.1 M particles in any order; reading the fields directly in the caller's
+// order takes 66 us where that order is the mesh's, and about 410 us in a
+// random order.
+__global__ void __launch_bounds__(kPmTileThreads)
+pm_tile_interp(const double4* __restrict__ rec, const uint32_t* __restrict__ idx, double L, PmBlocks b,
+               const uint32_t* __restrict__ start, const uint32_t* __restrict__ cstart,
+               const double* __restrict__ fx, const double* __restrict__ fy,
+               const double* __restrict__ fz, double* __restrict__ acc) {
+    extern __shared__ double tile[];
+    PmChunk k;
+    if (!pm_chunk(b, blockIdx.x, start, cstart, k)) return;
+    const int n = b.n, sy = b.e[2] + 1, sx = (b.e[1] + 1) * sy;
+    const double* __restrict__ f[3] = {fx, fy, fz};
+    for (int q = threadIdx.x; q < b.tile; q += kPmTileThreads) {
+        const int lx = q / sx, ly = (q - lx * sx) / sy, lz = q - lx * sx - ly * sy;
+        // (a smaller last block's tile repeats nodes past its own upper face)
+        int x = k.o[0] + lx, y = k.o[1] + ly, z = k.o[2] + lz;
+        x -= x >= n ? n : 0;
+        y -= y >= n ? n : 0;
+        z -= z >= n ? n : 0;
+        if (x < n && y < n && z < n) {
+            const int64_t node = ((int64_t)x * n + y) * n + z;
+            for (int a = 0; a < 3; ++a) tile[a * b.tile + q] = f[a][node];
+        }
+    }
+    __syncthreads();
+    for (uint32_t p = k.p0 + threadIdx.x; p < k.p1; p += kPmTileThreads) {
+        const double4 q = rec[p];
+        const int64_t i = (int64_t)idx[p];
+        int gx, gy, gz;
+        double wx[2], wy[2], wz[2];
+        cic_axis(q.x, L, n, gx, wx[0], wx[1]);
+        cic_axis(q.y, L, n, gy, wy[0], wy[1]);
+        cic_axis(q.z, L, n, gz, wz[0], wz[1]);
+        const double* t0 = tile + (gx - k.o[0]) * sx + (gy - k.o[1]) * sy + (gz - k.o[2]);
+        double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int dx = c >> 2, dy = (c >> 1) & 1, dz = c & 1;
+            const double wt = wx[dx] * wy[dy] * wz[dz];
+            const double* t = t0 + dx * sx + dy * sy + dz;
+            s[0] += wt * t[0];
+            s[1] += wt * t[b.tile];
+            s[2] += wt * t[2 * b.tile];
+        }
+        acc[3 * i] = s[0];
+        acc[3 * i + 1] = s[1];
+        acc[3 * i + 2] = s[2];
+    }
 }
 
 // rho of every node: its own block's tiles, and, on a block's lower face, the
 // upper face of the blocks below (periodic).
-__global__ void __launch_bounds__(256)
+// One workgroup per (x, y) line of nodes.
+__global__ void __launch_bounds__(128)
 pm_tile_sum(PmBlocks b, const uint32_t* __restrict__ cstart, const double* __restrict__ tiles,
             double* __restrict__ rho) {
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int n = b.n;
-    if (q >= (int64_t)n * n * n) return;
-    const int g[3] = {(int)(q / ((int64_t)n * n)), (int)(q / n % n), (int)(q % n)};
+    const int g[2] = {(int)blockIdx.y, (int)blockIdx.x};
     int blk[3][2], loc[3][2], m[3];
-    for (int a = 0; a < 3; ++a) {
-        blk[a][0] = g[a] / b.e[a];
-        loc[a][0] = g[a] - blk[a][0] * b.e[a];
+    auto place = [&](int a, int v) {
+        blk[a][0] = v >> b.sh[a];
+        loc[a][0] = v - (blk[a][0] << b.sh[a]);
         m[a] = 1;
         if (loc[a][0] == 0) {
             blk[a][1] = blk[a][0] == 0 ? b.nb[a] - 1 : blk[a][0] - 1;
-            loc[a][1] = min(b.e[a], n - blk[a][1] * b.e[a]);
+            loc[a][1] = min(b.e[a], n - (blk[a][1] << b.sh[a]));
             m[a] = 2;
         }
+    };
+    place(0, g[0]);
+    place(1, g[1]);
+    for (int v = threadIdx.x; v < n; v += 128) {
+        place(2, v);
+        double s = 0.0;
+        for (int x = 0; x < m[0]; ++x)
+            for (int y = 0; y < m[1]; ++y)
+                for (int z = 0; z < m[2]; ++z) {
+                    const int k = (blk[0][x] * b.nb[1] + blk[1][y]) * b.nb[2] + blk[2][z];
+                    const int at = (loc[0][x] * (b.e[1] + 1) + loc[1][y]) * (b.e[2] + 1) + loc[2][z];
+                    const uint32_t c1 = cstart[k + 1];
+                    for (uint32_t c = cstart[k]; c < c1; ++c) s += tiles[(size_t)c * b.tile + at];
+                }
+        rho[((int64_t)g[0] * n + g[1]) * n + v] = s;
     }
-    double s = 0.0;
-    for (int x = 0; x < m[0]; ++x)
-        for (int y = 0; y < m[1]; ++y)
-            for (int z = 0; z < m[2]; ++z) {
-                const int k = (blk[0][x] * b.nb[1] + blk[1][y]) * b.nb[2] + blk[2][z];
-                const int at = (loc[0][x] * (b.e[1] + 1) + loc[1][y]) * (b.e[2] + 1) + loc[2][z];
-                const uint32_t c1 = cstart[k + 1];
-                for (uint32_t c = cstart[k]; c < c1; ++c) s += tiles[(size_t)c * b.tile + at];
-            }
-    rho[q] = s;
 }
 
 __device__ __forceinline__ double sinc(double x) { return x == 0.0 ? 1.0 : sin(x) / x; }
@@ -297,28 +392,14 @@ __global__ void pm_green(const double2* __restrict__ rk, int n, double L, double
     az[q] = make_double2(kzz * pi, -kzz * pr);
 }
 
-// SORTED: the particles' records in bin order (their nodes then come from a
-// few lines that stay in the L2), written to the caller's places by idx.
-template <bool SORTED>
-__global__ void pm_interp(const double* __restrict__ pos, const double4* __restrict__ rec,
-                          const uint32_t* __restrict__ idx, int64_t np, double L, int n,
+__global__ void pm_interp(const double* __restrict__ pos, int64_t np, double L, int n,
                           const double* __restrict__ fx, const double* __restrict__ fy,
                           const double* __restrict__ fz, double* __restrict__ acc) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= np) return;
     int g[3];
     double w[3][2];
-    double x[3];
-    if constexpr (SORTED) {
-        const double4 q = rec[i];
-        x[0] = q.x;
-        x[1] = q.y;
-        x[2] = q.z;
-        i = (int64_t)idx[i];
-    } else {
-        for (int a = 0; a < 3; ++a) x[a] = pos[3 * i + a];
-    }
-    for (int a = 0; a < 3; ++a) cic_axis(x[a], L, n, g[a], w[a][0], w[a][1]);
+    for (int a = 0; a < 3; ++a) cic_axis(pos[3 * i + a], L, n, g[a], w[a][0], w[a][1]);
     double s[3] = {0.0, 0.0, 0.0};
     for (int dx = 0; dx < 2; ++dx) {
         const int x = g[0] + dx < n ? g[0] + dx : 0;
@@ -350,10 +431,11 @@ namespace {
 PmBlocks pm_blocks(int n) {
     PmBlocks b{};
     b.n = n;
-    b.e[0] = n <= 128 ? 8 : 16;
-    b.e[1] = b.e[2] = n <= 64 ? 8 : 16;
+    b.sh[0] = n <= 128 ? 3 : 4;
+    b.sh[1] = b.sh[2] = n <= 64 ? 3 : 4;
     b.tile = 1;
     for (int a = 0; a < 3; ++a) {
+        b.e[a] = 1 << b.sh[a];
         b.nb[a] = (n + b.e[a] - 1) / b.e[a];
         b.tile *= b.e[a] + 1;
     }
@@ -362,13 +444,16 @@ PmBlocks pm_blocks(int n) {
 
 // The block form's buffers for np particles; false when the direct form is to
 // be used: meshes beyond 256^3 (more blocks than kPmBins), few particles (the
-// whole call at 32^3 particles and mesh: 92 us by blocks, 98 us direct; the
-// gain shrinks with the particles), no memory, or buffers to grow while the
-// stream is being captured.
+// whole call at 32^3 particles and mesh: 68 us by blocks, 100 us direct; the
+// gain shrinks with the particles), far fewer particles than nodes (every
+// node's tiles are moved twice: 100^3 particles on 256^3 nodes took 1497 us by
+// blocks, 1457 direct), no memory, or buffers to grow while the stream is
+// being captured.
 constexpr int64_t kPmMinParticles = 16384;
 
 bool pm_block_buffers(PMPlan& p, int64_t np, hipStream_t s) {
     if (p.n > 256 || np < kPmMinParticles || np > (int64_t)UINT32_MAX) return false;
+    if (4 * np < (int64_t)p.n * p.n * p.n) return false;
     const PmBlocks b = pm_blocks(p.n);
     const size_t bins = (size_t)b.count(), wgs = (size_t)((np + kPmPer - 1) / kPmPer);
     const size_t chunks = bins + (size_t)(np / kPmChunk) + 1;
@@ -411,12 +496,19 @@ hipError_t pm_plan(PMPlan& p, int n, hipStream_t s) {
     hipError_t e;
     if ((e = hipMalloc(&p.rho, n3 * sizeof(double))) != hipSuccess) return e;
     if ((e = hipMalloc(&p.rk, nh * 2 * sizeof(double))) != hipSuccess) return e;
-    for (int a = 0; a < 3; ++a) {
-        if ((e = hipMalloc(&p.gk[a], nh * 2 * sizeof(double))) != hipSuccess) return e;
-        if ((e = hipMalloc(&p.field[a], n3 * sizeof(double))) != hipSuccess) return e;
+    // the three spectra and the three fields, each set in one piece for the
+    // batched inverse transform
+    if ((e = hipMalloc(&p.gk[0], 3 * nh * 2 * sizeof(double))) != hipSuccess) return e;
+    if ((e = hipMalloc(&p.field[0], 3 * n3 * sizeof(double))) != hipSuccess) return e;
+    for (int a = 1; a < 3; ++a) {
+        p.gk[a] = p.gk[0] + a * nh * 2;
+        p.field[a] = p.field[0] + a * n3;
     }
     if (hipfftPlan3d(&p.fwd, n, n, n, HIPFFT_D2Z) != HIPFFT_SUCCESS) return hipErrorUnknown;
-    if (hipfftPlan3d(&p.inv, n, n, n, HIPFFT_Z2D) != HIPFFT_SUCCESS) return hipErrorUnknown;
+    int dims[3] = {n, n, n}, real_dims[3] = {n, n, n}, half_dims[3] = {n, n, n / 2 + 1};
+    if (hipfftPlanMany(&p.inv, 3, dims, half_dims, 1, (int)nh, real_dims, 1, (int)n3, HIPFFT_Z2D, 3) !=
+        HIPFFT_SUCCESS)
+        return hipErrorUnknown;
     if (hipfftSetStream(p.fwd, s) != HIPFFT_SUCCESS || hipfftSetStream(p.inv, s) != HIPFFT_SUCCESS)
         return hipErrorUnknown;
     p.n = n;
@@ -438,9 +530,9 @@ void pm_release(PMPlan& p) {
     }
     for (void* q : p.retired) (void)hipFree(q);
     p.retired.clear();
+    if (p.gk[0]) (void)hipFree(p.gk[0]);
+    if (p.field[0]) (void)hipFree(p.field[0]);
     for (int a = 0; a < 3; ++a) {
-        if (p.gk[a]) (void)hipFree(p.gk[a]);
-        if (p.field[a]) (void)hipFree(p.field[a]);
         p.gk[a] = nullptr;
         p.field[a] = nullptr;
     }
@@ -467,13 +559,13 @@ hipError_t pm_long_range(PMPlan& p, const double* pos, const double* mass, int64
         if (!p.blk_cleared)
             hipLaunchKernelGGL(pm_zero, dim3(blocks_of((bins + 8) / 2 + 1)), dim3(256), 0, s,
                                reinterpret_cast<double*>(count), (int64_t)((bins + 1) / 2));
-        hipLaunchKernelGGL(pm_bin_count, dim3(wgs), dim3(256), 0, s, pos, np, L, b, count, base);
+        hipLaunchKernelGGL(pm_bin_count, dim3(wgs), dim3(kPmThreads), 0, s, pos, np, L, b, count, base);
         hipLaunchKernelGGL(pm_bin_scan, dim3(1), dim3(1024), 0, s, bins, count, start, cstart);
-        hipLaunchKernelGGL(pm_bin_scatter, dim3(wgs), dim3(256), 0, s, pos, mass, np, L, b, start, base,
+        hipLaunchKernelGGL(pm_bin_scatter, dim3(wgs), dim3(kPmThreads), 0, s, pos, mass, np, L, b, start, base,
                            rec, idx);
-        hipLaunchKernelGGL(pm_tile_deposit, dim3(chunks), dim3(256), (size_t)b.tile * 8, s, rec, L, b,
+        hipLaunchKernelGGL(pm_tile_deposit, dim3(chunks), dim3(kPmTileThreads), (size_t)b.tile * 8, s, rec, L, b,
                            start, cstart, static_cast<double*>(p.blk[3]));
-        hipLaunchKernelGGL(pm_tile_sum, dim3(blocks_of(n3)), dim3(256), 0, s, b, cstart,
+        hipLaunchKernelGGL(pm_tile_sum, dim3(n, n), dim3(128), 0, s, b, cstart,
                            static_cast<const double*>(p.blk[3]), p.rho);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         p.blk_cleared = true;   // pm_bin_scan leaves the counts zero
@@ -491,16 +583,18 @@ hipError_t pm_long_range(PMPlan& p, const double* pos, const double* mass, int64
                        reinterpret_cast<double2*>(p.gk[0]), reinterpret_cast<double2*>(p.gk[1]),
                        reinterpret_cast<double2*>(p.gk[2]));
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int a = 0; a < 3; ++a)
-        if (hipfftExecZ2D(p.inv, reinterpret_cast<hipfftDoubleComplex*>(p.gk[a]), p.field[a]) !=
-            HIPFFT_SUCCESS)
-            return hipErrorUnknown;
-    if (np > 0 && blocks)
-        hipLaunchKernelGGL(pm_interp<true>, dim3(blocks_of(np)), dim3(256), 0, s, nullptr, rec, idx, np,
-                           L, n, p.field[0], p.field[1], p.field[2], acc);
-    else if (np > 0)
-        hipLaunchKernelGGL(pm_interp<false>, dim3(blocks_of(np)), dim3(256), 0, s, pos, nullptr, nullptr,
-                           np, L, n, p.field[0], p.field[1], p.field[2], acc);
+    if (hipfftExecZ2D(p.inv, reinterpret_cast<hipfftDoubleComplex*>(p.gk[0]), p.field[0]) != HIPFFT_SUCCESS)
+        return hipErrorUnknown;
+    if (blocks) {
+        const PmBlocks b = pm_blocks(n);
+        const uint32_t* start = static_cast<const uint32_t*>(p.blk[2]) + b.count() + 8;
+        hipLaunchKernelGGL(pm_tile_interp, dim3((unsigned)(b.count() + np / kPmChunk + 1)),
+                           dim3(kPmTileThreads), (size_t)b.tile * 24, s, rec, idx, L, b, start,
+                           start + b.count() + 8, p.field[0], p.field[1], p.field[2], acc);
+    } else if (np > 0) {
+        hipLaunchKernelGGL(pm_interp, dim3(blocks_of(np)), dim3(256), 0, s, pos, np, L, n, p.field[0],
+                           p.field[1], p.field[2], acc);
+    }
     return hipGetLastError();
 }
 

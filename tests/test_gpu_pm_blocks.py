@@ -14,14 +14,14 @@ from paper_2107_14008_amd import inputs
 pytestmark = pytest.mark.gpu
 
 BOX = 100.0
-N = 60_000         # above the block form's smallest particle count
+N = 600_000        # enough particles for the block form up to 130^3
 
 
 def _positions(kind):
     rng = np.random.default_rng(8)
     x = rng.uniform(0, BOX, (N, 3))
     if kind == "clump":            # one block with many chunks
-        x[: N // 2] = 37.0 + rng.normal(0, 0.4, (N // 2, 3))
+        x[:40000] = 37.0 + rng.normal(0, 0.4, (40000, 3))
     if kind == "faces":            # on nodes, at the box edge and beyond it
         x[:4000] = np.round(x[:4000] / 12.5) * 12.5
         x[4000:8000] += BOX * rng.integers(-2, 3, (4000, 3))
