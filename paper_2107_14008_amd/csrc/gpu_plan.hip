@@ -428,12 +428,35 @@ k_level_move(int64_t n, const int32_t* __restrict__ pc, int32_t* __restrict__ pc
 // level loop does (first floor(n/2) of the split axis left, stable), then
 // each leaf's particles are written to perm in ascending caller index.
 // Bounds of every cell of the subtree are written to clo / chi.
-constexpr int kFuseM = 8192;
-constexpr int kFuseC = 1024;
+//
+// Bound by LDS instructions.  A thread owns the same positions k of the three
+// lists at every level (64 consecutive ones per wave and round) and keeps
+// their cell (id, first position, count) in registers; a cell's position
+// range changes by halving alone, so none of it is looked up.  The left marks
+// before a cell's first position are the same in the three lists and follow
+// from the marks of the split axis's own list, which depend on positions
+// alone: marks before k minus those of the cell up to k.  A list entry then
+// costs about three LDS instructions per level (its id, its mark, its new
+// place) instead of twelve, and one buffer per list does, since all entries
+// are in registers before the first is written.  2.1 M particles (256
+// subtrees of 8192): 204 -> 131 us; 16.7 M: 1744 -> 1171 us; 4,096 particles
+// (one subtree): 89 -> 55 us.
+constexpr int kFuseRounds = 8;
 constexpr int kFuseT = 1024;
-constexpr int kFuseRounds = (3 * kFuseM + kFuseT - 1) / kFuseT;   // 24
-constexpr uint16_t kNoChild = 0xffffu;
+constexpr int kFuseM = kFuseRounds * kFuseT;
+constexpr int kFuseC = 1024;
+constexpr uint32_t kNoChild = 0xffffu;
 
+// Ascending sort of one value per lane over the wavefront (bitonic).
+__device__ __forceinline__ uint32_t wave_sort(uint32_t v, int lane) {
+    for (int size = 2; size <= 64; size <<= 1)
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            const uint32_t o = __shfl_xor(v, stride);
+            const bool low = ((lane & stride) == 0) == ((lane & size) == 0);
+            v = low ? min(v, o) : max(v, o);
+        }
+    return v;
+}
 
 // roots[b] = (subtree root cell, cells in the subtree, root depth, deepest depth)
 __global__ void __launch_bounds__(kFuseT)
@@ -441,177 +464,160 @@ k_orb_fused(const int4* __restrict__ roots, const int4* __restrict__ cell,
             const int4* __restrict__ aux, const uint32_t* __restrict__ plist, int64_t n,
             const double* __restrict__ wpos, int32_t* __restrict__ loc, double* __restrict__ clo,
             double* __restrict__ chi, int32_t* __restrict__ perm) {
-    __shared__ __align__(16) uint16_t lst[2 * 3 * kFuseM];
-    __shared__ uint8_t flag[kFuseM];
-    __shared__ uint16_t pcl[kFuseM];
-    // per local cell: first | count << 16 | child0 << 32 | depth << 48 | axis << 56
-    __shared__ uint64_t cinfo[kFuseC];
-    __shared__ uint16_t cch1[kFuseC];
-    __shared__ uint32_t sfirst[3 * kFuseC];
-    __shared__ uint32_t wsum[kFuseT / 64];
-    __shared__ uint64_t wmask[(kFuseT / 64) * kFuseRounds];
-    __shared__ uint32_t wpre[(kFuseT / 64) * kFuseRounds];
-    const int4 r = roots[blockIdx.x];
-    const int root = r.x, nsub = r.y, depth_span = r.w - r.z;
+    __shared__ __align__(16) uint16_t lst[3 * kFuseM];
+    __shared__ uint8_t flag[kFuseM];       // left marks by local id
+    __shared__ uint8_t axs[kFuseM];        // split axis, at the cell's first position
+    __shared__ uint32_t cch[kFuseC];       // children: first | second << 16
+    __shared__ uint32_t cfc[kFuseC];       // first position | count << 16
+    __shared__ uint32_t wsum[4][kFuseT / 64];
+    const int4 rt = roots[blockIdx.x];
+    const int root = rt.x, nsub = rt.y, depth_span = rt.w - rt.z;
     const int4 rc = cell[root];
     const int base = rc.x, m = rc.y;
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
     const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
     const uint32_t* __restrict__ l0 = plist + base;
-    auto L = [&](int buf, int a, int k) -> uint16_t& { return lst[(buf * 3 + a) * kFuseM + k]; };
-    auto c_first = [](uint64_t ci) { return (int)(ci & 0xffffu); };
-    auto c_count = [](uint64_t ci) { return (int)((ci >> 16) & 0xffffu); };
-    auto c_child0 = [](uint64_t ci) { return (int)((ci >> 32) & 0xffffu); };
-    auto c_dep = [](uint64_t ci) { return (int)((ci >> 48) & 0xffu); };
-    auto c_axis = [](uint64_t ci) { return (int)(ci >> 56); };
+    const int R = (m + kFuseT - 1) / kFuseT;
+    const int k0 = wave * R * 64 + lane;   // this thread's positions: k0 + 64 r, r < R
 
     for (int k = t; k < m; k += kFuseT) {
-        L(0, 0, k) = (uint16_t)k;
+        lst[k] = (uint16_t)k;
         loc[l0[k]] = k;
-        pcl[k] = 0;
     }
     for (int c = t; c < nsub; c += kFuseT) {
         const int4 ci = cell[root + c], ai = aux[root + c];
-        const uint64_t ch0 = ai.x >= 0 ? (uint64_t)(ai.x - root) : (uint64_t)kNoChild;
-        cinfo[c] = (uint64_t)(ci.x - base) | ((uint64_t)ci.y << 16) | (ch0 << 32) |
-                   ((uint64_t)(ai.w - r.z) << 48);
-        cch1[c] = ai.y >= 0 ? (uint16_t)(ai.y - root) : kNoChild;
+        cch[c] = ai.x >= 0 ? (uint32_t)(ai.x - root) | (uint32_t)(ai.y - root) << 16 : kNoChild;
+        cfc[c] = (uint32_t)(ci.x - base) | (uint32_t)ci.y << 16;
     }
     // loc[] is written and read through global memory by this workgroup
     // only, so the barrier's workgroup-scope ordering suffices (an
     // agent-scope fence here writes back the whole L2, per workgroup)
     __syncthreads();
     for (int k = t; k < m; k += kFuseT) {
-        L(0, 1, k) = (uint16_t)loc[plist[n + base + k]];
-        L(0, 2, k) = (uint16_t)loc[plist[2 * n + base + k]];
+        lst[kFuseM + k] = (uint16_t)loc[plist[n + base + k]];
+        lst[2 * kFuseM + k] = (uint16_t)loc[plist[2 * n + base + k]];
     }
+    // the cell of each of the thread's positions; fresh: bit r, the cell is
+    // of the current depth
+    uint32_t fc[kFuseRounds], id[kFuseRounds];
+    uint32_t fresh = 0u;
+#pragma unroll
+    for (int r = 0; r < kFuseRounds; ++r) {
+        fc[r] = (uint32_t)m << 16;
+        id[r] = 0u;
+        if (r < R && k0 + 64 * r < m) fresh |= 1u << r;
+    }
+    const uint32_t mine = fresh;           // the thread's positions below m
     __syncthreads();
 
-    const int R = (3 * m + kFuseT - 1) / kFuseT;   // rounds of 64 positions per wave
-    int cur = 0;
     for (int dep = 0;; ++dep) {
         // bounds of the cells of this depth, split axis of those that split
-        for (int c = t; c < nsub; c += kFuseT) {
-            const uint64_t ci = cinfo[c];
-            if (c_dep(ci) != dep) continue;
-            const int f = c_first(ci), e = f + c_count(ci) - 1;
+#pragma unroll
+        for (int r = 0; r < kFuseRounds; ++r) {
+            const int k = k0 + 64 * r, f = (int)(fc[r] & 0xffffu);
+            if (!((fresh >> r) & 1u) || k != f) continue;
+            const int e = f + (int)(fc[r] >> 16) - 1, c = root + (int)id[r];
             double lo[3], hi[3];
             for (int a = 0; a < 3; ++a) {
-                lo[a] = wpos[3 * (size_t)l0[L(cur, a, f)] + a];
-                hi[a] = wpos[3 * (size_t)l0[L(cur, a, e)] + a];
-                clo[3 * (size_t)(root + c) + a] = lo[a];
-                chi[3 * (size_t)(root + c) + a] = hi[a];
+                lo[a] = wpos[3 * (size_t)l0[lst[a * kFuseM + f]] + a];
+                hi[a] = wpos[3 * (size_t)l0[lst[a * kFuseM + e]] + a];
             }
-            if (c_child0(ci) != kNoChild) {
+            for (int a = 0; a < 3; ++a) {
+                clo[3 * (size_t)c + a] = lo[a];
+                chi[3 * (size_t)c + a] = hi[a];
+            }
+            {
 #pragma clang fp contract(off)
                 const double e0 = hi[0] - lo[0], e1 = hi[1] - lo[1], e2 = hi[2] - lo[2];
                 int axis = 0;
                 double best = e0;
                 if (e1 > best) { axis = 1; best = e1; }
                 if (e2 > best) axis = 2;
-                cinfo[c] = (ci & 0x00ffffffffffffffull) | ((uint64_t)axis << 56);
+                axs[f] = (uint8_t)axis;
             }
         }
         if (dep == depth_span) break;
         __syncthreads();
-        auto splits = [&](uint64_t ci) { return c_dep(ci) == dep && c_child0(ci) != kNoChild; };
-        for (int k = t; k < m; k += kFuseT) {
-            const uint64_t ci = cinfo[pcl[k]];
-            if (!splits(ci)) continue;
-            flag[L(cur, c_axis(ci), k)] = (k - c_first(ci) < c_count(ci) / 2) ? 1 : 0;
+        // left marks from the split axis's list; split: bit r, the cell splits;
+        // own: bit r, position k is in the first half
+        uint32_t split = 0u, own = 0u;
+        uint32_t ch[kFuseRounds];
+        int ax[kFuseRounds];
+#pragma unroll
+        for (int r = 0; r < kFuseRounds; ++r) {
+            ch[r] = kNoChild;
+            ax[r] = 0;
+            if (!((mine >> r) & 1u)) continue;
+            ch[r] = cch[id[r]];
+            if (ch[r] == kNoChild) continue;
+            split |= 1u << r;
+            const int k = k0 + 64 * r, f = (int)(fc[r] & 0xffffu), nl = (int)(fc[r] >> 17);
+            ax[r] = axs[f];
+            const bool o = k - f < nl;
+            own |= (o ? 1u : 0u) << r;
+            flag[lst[ax[r] * kFuseM + k]] = o ? 1 : 0;
         }
         __syncthreads();
-        // Stable partition of the three lists by one exclusive scan over the
-        // left marks of all 3m positions (each cell's range is contiguous in
-        // every list, so differences inside a range count that range only).
-        // Wave w owns the positions [w R 64, (w + 1) R 64), 64 consecutive
-        // ones per round; a round's marks are one ballot, and a position's
-        // prefix is wave base + round prefix + popcount of the lanes below.
-        uint64_t* __restrict__ mymask = &wmask[wave * kFuseRounds];
-        uint32_t* __restrict__ mypre = &wpre[wave * kFuseRounds];
-#pragma unroll 4
-        for (int rr = 0; rr < R; ++rr) {
-            const int q = (wave * R + rr) * 64 + lane;
-            bool f = false;
-            if (q < 3 * m) {
-                const int a = q >= m ? (q >= 2 * m ? 2 : 1) : 0;
-                const int k = q - a * m;
-                f = splits(cinfo[pcl[k]]) && flag[L(cur, a, k)];
-            }
-            const uint64_t mk = __ballot(f);
-            if (lane == 0) mymask[rr] = mk;
-        }
-        {
-            // lane rr scans the round counts of its wave
-            const uint32_t cnt = lane < R ? (uint32_t)__popcll(mymask[lane]) : 0u;
-            uint32_t x = cnt;
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t y = __shfl_up(x, off);
-                if (lane >= off) x += y;
-            }
-            if (lane < R) mypre[lane] = x - cnt;
-            if (lane == 63) wsum[wave] = x;
-        }
-        __syncthreads();
-        if (t < kFuseT / 64) {
-            uint32_t acc = 0;
-            for (int w = 0; w < t; ++w) acc += wsum[w];
-            for (int rr = 0; rr < R; ++rr) wpre[t * kFuseRounds + rr] += acc;
-        }
-        __syncthreads();
-        auto prefix = [&](int q) {
-            const int w = q / (R * 64), rr = (q >> 6) - w * R, l = q & 63;
-            const uint64_t mk = wmask[w * kFuseRounds + rr];
-            const uint64_t bl = l ? (~0ull >> (64 - l)) : 0ull;
-            return wpre[w * kFuseRounds + rr] + (uint32_t)__popcll(mk & bl);
-        };
-        for (int x = t; x < 3 * nsub; x += kFuseT) {
-            const int c = x / 3, a = x - 3 * c;
-            const uint64_t ci = cinfo[c];
-            if (splits(ci)) sfirst[a * kFuseC + c] = prefix(a * m + c_first(ci));
-        }
-        __syncthreads();
-#pragma unroll 4
-        for (int rr = 0; rr < R; ++rr) {
-            const int q = (wave * R + rr) * 64 + lane;
-            if (q < 3 * m) {
-                const int a = q >= m ? (q >= 2 * m ? 2 : 1) : 0;
-                const int k = q - a * m;
-                const int c = pcl[k];
-                const uint64_t ci = cinfo[c];
-                int pos = k;
-                if (splits(ci)) {
-                    const uint64_t mk = mymask[rr];
-                    const int f = c_first(ci), nl = c_count(ci) / 2;
-                    const int lr = (int)(mypre[rr] + (uint32_t)__popcll(mk & below) -
-                                         sfirst[a * kFuseC + c]);
-                    pos = ((mk >> lane) & 1ull) ? f + lr : f + nl + (k - f - lr);
-                }
-                L(cur ^ 1, a, pos) = L(cur, a, k);
+        // marks and their prefix sums inside the wave, per list (0 to 2) and of
+        // the own pattern (3)
+        uint32_t p[3][kFuseRounds], pre[4][kFuseRounds], mk[3] = {0u, 0u, 0u};
+        uint32_t cnt[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int r = 0; r < kFuseRounds; ++r) {
+            if (r >= R) continue;
+            const int k = k0 + 64 * r;
+            const bool sp = (split >> r) & 1u, o = (own >> r) & 1u;
+            const uint64_t mo = __ballot(o);
+            pre[3][r] = cnt[3] + (uint32_t)__popcll(mo & below);
+            cnt[3] += (uint32_t)__popcll(mo);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                p[a][r] = sp ? lst[a * kFuseM + k] : 0u;
+                const bool b = sp && (a == ax[r] ? o : flag[p[a][r]] != 0);
+                const uint64_t mb = __ballot(b);
+                pre[a][r] = cnt[a] + (uint32_t)__popcll(mb & below);
+                cnt[a] += (uint32_t)__popcll(mb);
+                mk[a] |= (b ? 1u : 0u) << r;
             }
         }
+        if (lane < 4) wsum[lane][wave] = lane == 0 ? cnt[0] : lane == 1 ? cnt[1] : lane == 2 ? cnt[2] : cnt[3];
         __syncthreads();
-        for (int k = t; k < m; k += kFuseT) {
-            const int c = pcl[k];
-            const uint64_t ci = cinfo[c];
-            if (splits(ci)) pcl[k] = (k - c_first(ci) < c_count(ci) / 2) ? c_child0(ci) : cch1[c];
+        // marks of the waves before (the four sums in lanes of 16)
+        uint32_t before = (lane & 15) < wave ? wsum[lane >> 4][lane & 15] : 0u;
+        for (int off = 8; off > 0; off >>= 1) before += __shfl_xor(before, off);
+        const uint32_t bo = __shfl(before, 48);
+        const uint32_t ba[3] = {(uint32_t)__shfl(before, 0) - bo, (uint32_t)__shfl(before, 16) - bo,
+                                (uint32_t)__shfl(before, 32) - bo};
+        fresh = split;
+#pragma unroll
+        for (int r = 0; r < kFuseRounds; ++r) {
+            if (!((split >> r) & 1u)) continue;
+            const int k = k0 + 64 * r, f = (int)(fc[r] & 0xffffu), c = (int)(fc[r] >> 16), nl = c / 2;
+            // marks before k in its cell, list a: those before k in the list
+            // minus those before the cell, which are the own pattern's before
+            // k less the cell's own min(k - f, nl)
+            const int cellpre = (int)pre[3][r] - min(k - f, nl);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const int lr = (int)(ba[a] + pre[a][r]) - cellpre;
+                const int pos = (mk[a] >> r) & 1u ? f + lr : f + nl + (k - f - lr);
+                lst[a * kFuseM + pos] = (uint16_t)p[a][r];
+            }
+            const bool o = (own >> r) & 1u;
+            id[r] = o ? ch[r] & 0xffffu : ch[r] >> 16;
+            fc[r] = o ? (uint32_t)f | (uint32_t)nl << 16 : (uint32_t)(f + nl) | (uint32_t)(c - nl) << 16;
         }
-        cur ^= 1;
         __syncthreads();
     }
-    // leaves: particles in ascending caller index
-    uint32_t* gid = reinterpret_cast<uint32_t*>(&lst[(cur ^ 1) * 3 * kFuseM]);
+    // leaves, one wave each: particles in ascending caller index
     __syncthreads();
-    for (int k = t; k < m; k += kFuseT) gid[k] = l0[L(cur, 0, k)];
-    __syncthreads();
-    for (int k = t; k < m; k += kFuseT) {
-        const uint64_t ci = cinfo[pcl[k]];
-        const int f = c_first(ci), e = f + c_count(ci);
-        const uint32_t id = gid[k];
-        int rank = 0;
-        for (int q = f; q < e; ++q) rank += gid[q] < id ? 1 : 0;
-        perm[base + f + rank] = (int32_t)id;
+    for (int c = wave; c < nsub; c += kFuseT / 64) {
+        if (cch[c] != kNoChild) continue;
+        const int f = (int)(cfc[c] & 0xffffu), cnt = (int)(cfc[c] >> 16);
+        uint32_t v = lane < cnt ? l0[lst[f + lane]] : 0xffffffffu;
+        v = wave_sort(v, lane);
+        if (lane < cnt) perm[base + f + lane] = (int32_t)v;
     }
 }
 
