@@ -5,14 +5,19 @@
 //
 // Radix sort: 8-bit digits, tiles of 4096 elements (256 threads x 16
 // rounds; 1024 for segments under kSmallSortN elements, whose few tiles
-// would otherwise leave most CUs idle); a tile never straddles two segments.  Per pass: (1) per-tile
-// digit histogram in LDS, (2) one exclusive scan over the
-// [segment][digit][tile] table (segment-major, so segment s lands in
-// [s n, (s + 1) n)), (3) scatter: inside a tile the 256 elements of a round
-// are ranked per digit with wavefront ballots (eight ballots give each lane
-// the mask of lanes holding its digit) and a running per-digit count in
-// LDS, so the order of equal digits is kept (stable), which makes the sort
-// stable across passes; the tile is ordered in LDS and written out in runs.
+// would otherwise leave most CUs idle); a tile never straddles two segments.
+// Per pass: (1) per-tile digit histogram in LDS, stored [segment][digit][tile];
+// (2) an exclusive scan of each row of tiles, one workgroup per row, and the
+// row's total; (3) scatter: the 256 row totals of the segment, scanned by
+// each workgroup, give the digits' starts; inside a tile the 256 elements of
+// a round are ranked per digit with wavefront ballots (eight ballots give
+// each lane the mask of lanes holding its digit) and a running per-digit
+// count in LDS, so the order of equal digits is kept (stable), which makes
+// the sort stable across passes; the tile is ordered in LDS and written out in
+// runs.  Up to kDirectTiles tiles per segment the scatter adds up its row of
+// the histogram itself and (2) is left out (12 us less per build at 4,096
+// particles; at 262,144, 256 tiles, its serial sums would cost more than the
+// launch).
 #include <algorithm>
 
 #include "gpu_plan.h"
@@ -66,6 +71,38 @@ rs_hist(const K* __restrict__ keys, int64_t n, int shift, uint32_t* __restrict__
     hist[tr.col + (size_t)threadIdx.x * tiles] = h[threadIdx.x];
 }
 
+constexpr int kDirectTiles = 32;
+
+// Exclusive scan of one row of `tiles` counts (in place) and its total, one
+// workgroup per [segment][digit] row.
+__global__ void __launch_bounds__(kThreads)
+rs_rowscan(uint32_t* __restrict__ hist, int tiles, uint32_t* __restrict__ total) {
+    __shared__ uint32_t wsum[kThreads / 64];
+    uint32_t* __restrict__ row = hist + (size_t)blockIdx.x * tiles;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    uint32_t carry = 0;
+    for (int b = 0; b < tiles; b += kThreads) {
+        const int k = b + t;
+        const uint32_t v = k < tiles ? row[k] : 0u;
+        uint32_t x = v;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off);
+            if (lane >= off) x += y;
+        }
+        if (lane == 63) wsum[wave] = x;
+        __syncthreads();
+        uint32_t before = carry, all = 0;
+        for (int w = 0; w < kThreads / 64; ++w) {
+            if (w < wave) before += wsum[w];
+            all += wsum[w];
+        }
+        if (k < tiles) row[k] = before + x - v;
+        carry += all;
+        __syncthreads();
+    }
+    if (t == 0) total[blockIdx.x] = carry;
+}
+
 // Exclusive scan of m 32-bit values by one workgroup of 1024 threads.
 __global__ void __launch_bounds__(1024) scan_single(uint32_t* __restrict__ a, int64_t m) {
     __shared__ uint32_t part[1024];
@@ -95,11 +132,15 @@ __global__ void __launch_bounds__(1024) scan_single(uint32_t* __restrict__ a, in
 // the tile's elements of that digit), then written out position by
 // position: consecutive positions of one digit go to consecutive addresses,
 // so the global writes come in runs instead of one element per line.
-template <class K, bool VALS, int R>
+//
+// DIRECT: hist holds the tiles' counts; otherwise their exclusive scan by row
+// (rs_rowscan), the tile's own counts being the difference to the next
+// entry, and `total` the rows' totals.
+template <class K, bool VALS, int R, bool DIRECT>
 __global__ void __launch_bounds__(kThreads)
 rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
            K* __restrict__ kout, uint32_t* __restrict__ vout, int64_t n, int shift,
-           const uint32_t* __restrict__ hist, const uint32_t* __restrict__ offs, int tiles) {
+           const uint32_t* __restrict__ hist, const uint32_t* __restrict__ total, int tiles) {
     __shared__ K ks[kThreads * R];
     __shared__ uint32_t vs[VALS ? kThreads * R : 1];
     __shared__ uint32_t start[256];     // digit start inside the tile
@@ -109,19 +150,39 @@ rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
     const TileRange tr = tile_range<R>(n, tiles);
-    // exclusive scan of the tile's digit counts (one wave scans 4 per lane)
+    // exclusive scans over the digits of the tile's counts (start) and of the
+    // segment's (one wave scans 4 digits per lane); goff: the digit's total in
+    // the segment first, its start in the output for this tile in the end
+    uint32_t mine;   // elements of digit t in the segment's tiles before this one
     {
-        const uint32_t c = hist[tr.col + (size_t)t * tiles];
-        goff[t] = offs[tr.col + (size_t)t * tiles];
-        run[t] = 0;
+        const int seg = blockIdx.x / tiles, tile = blockIdx.x - seg * tiles;
+        const uint32_t* __restrict__ row = hist + ((size_t)seg * 256 + t) * tiles;
+        uint32_t c, all;
+        if constexpr (DIRECT) {
+            mine = 0;
+            all = 0;
+            for (int k = 0; k < tiles; ++k) {
+                const uint32_t v = row[k];
+                if (k < tile) mine += v;
+                all += v;
+            }
+            c = row[tile];
+        } else {
+            mine = row[tile];
+            all = total[seg * 256 + t];
+            c = (tile + 1 < tiles ? row[tile + 1] : all) - mine;
+        }
         start[t] = c;
+        goff[t] = all;
+        run[t] = 0;
         for (int w = 0; w < kThreads / 64; ++w) wc[w][t] = 0;
     }
     __syncthreads();
-    if (wave == 0) {
+    if (wave < 2) {
+        uint32_t* __restrict__ a = wave == 0 ? start : goff;
         uint32_t v[4], tot = 0;
         for (int j = 0; j < 4; ++j) {
-            v[j] = start[4 * lane + j];
+            v[j] = a[4 * lane + j];
             tot += v[j];
         }
         uint32_t x = tot;
@@ -131,11 +192,13 @@ rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
         }
         uint32_t e = x - tot;
         for (int j = 0; j < 4; ++j) {
-            start[4 * lane + j] = e;
+            a[4 * lane + j] = e;
             e += v[j];
         }
     }
     __syncthreads();
+    goff[t] += mine + (uint32_t)((int64_t)(blockIdx.x / tiles) * n);
+    // (read again only after the barriers of the rounds below)
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     for (int r = 0; r < R; ++r) {
         const int64_t i = tr.begin + r * kThreads + t;
@@ -199,21 +262,33 @@ scan_tile_sums(const int32_t* __restrict__ in, int64_t n, uint32_t* __restrict__
     if (threadIdx.x == 0) sums[blockIdx.x] = (uint32_t)red[0];
 }
 
-// SCANNED: sums holds each tile's offset (scan_single ran); otherwise the
-// tile sums themselves, and each workgroup adds up those before its tile
-// (one launch fewer; for up to kApplySumMax tiles).
+// sums holds each tile's offset (kScanned: scan_single ran) or the tile sums
+// themselves, and each workgroup adds up those before its tile (kTileSums, one
+// launch fewer; for up to kApplySumMax tiles).
 constexpr int kApplySumMax = 4096;
 
-template <bool SCANNED>
+//
+// KIND: kScanned; kTileSums; or kOwnSums, where each workgroup adds up the
+// input before its tile itself (no scan_tile_sums launch; for up to
+// kOwnSumMax elements).
+enum { kScanned, kTileSums, kOwnSums };
+constexpr int64_t kOwnSumMax = 32768;
+
+template <int KIND>
 __global__ void __launch_bounds__(kThreads)
 scan_tile_apply(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
                 const uint32_t* __restrict__ sums) {
     __shared__ int32_t part[kThreads];
     __shared__ uint32_t toff;
     const int t = threadIdx.x;
-    if (!SCANNED) {
+    if (KIND != kScanned) {
         uint32_t c = 0;
-        for (int k = t; k < (int)blockIdx.x; k += kThreads) c += sums[k];
+        if (KIND == kTileSums) {
+            for (int k = t; k < (int)blockIdx.x; k += kThreads) c += sums[k];
+        } else {
+#pragma unroll 4
+            for (int k = t; k < (int)blockIdx.x * kTile; k += kThreads) c += (uint32_t)in[k];
+        }
         for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off);
         if ((t & 63) == 0) part[t >> 6] = (int32_t)c;
         __syncthreads();
@@ -239,7 +314,7 @@ scan_tile_apply(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64
         part[t] += x;
         __syncthreads();
     }
-    int32_t run = (int32_t)(SCANNED ? sums[blockIdx.x] : toff) + (t == 0 ? 0 : part[t - 1]);
+    int32_t run = (int32_t)(KIND == kScanned ? sums[blockIdx.x] : toff) + (t == 0 ? 0 : part[t - 1]);
     for (int r = 0; r < kRounds; ++r) {
         if (base + r < n) out[base + r] = run;
         run += v[r];
@@ -255,7 +330,7 @@ int64_t sort_tiles(int64_t n) { return (n + kTile - 1) / kTile; }
 
 int64_t sort_hist_words(int64_t n, int nseg) {
     const int64_t m = (int64_t)nseg * 256 * radix_tiles(n);
-    return 2 * m + sort_tiles(m) + 16;
+    return m + (int64_t)nseg * 256 + 16;
 }
 
 template <class K, int R>
@@ -268,22 +343,19 @@ hipError_t radix_sort_r(K* keys, uint32_t* vals, K* tmp_keys, uint32_t* tmp_vals
     K* kb = tmp_keys;
     uint32_t* va = vals;
     uint32_t* vb = tmp_vals;
-    // scratch layout: counts [m], their exclusive scan [m], tile sums
+    // scratch layout: counts [m], then the row totals
     const int64_t m = (int64_t)nseg * 256 * tiles;
-    uint32_t* offs = hist + m;
-    uint32_t* scan_scratch = hist + 2 * m;
+    uint32_t* total = hist + m;
+    const bool direct = tiles <= kDirectTiles;
+    const auto scatter = vals ? (direct ? rs_scatter<K, true, R, true> : rs_scatter<K, true, R, false>)
+                              : (direct ? rs_scatter<K, false, R, true> : rs_scatter<K, false, R, false>);
     for (int shift = bit_begin; shift < bit_end; shift += 8) {
         hipLaunchKernelGGL((rs_hist<K, R>), dim3(blocks), dim3(kThreads), 0, s, ka, n, shift, hist,
                            tiles);
-        const hipError_t e = exclusive_scan_i32(reinterpret_cast<const int32_t*>(hist),
-                                                reinterpret_cast<int32_t*>(offs), m, scan_scratch, s);
-        if (e != hipSuccess) return e;
-        if (vals)
-            hipLaunchKernelGGL((rs_scatter<K, true, R>), dim3(blocks), dim3(kThreads), 0, s, ka, va,
-                               kb, vb, n, shift, hist, offs, tiles);
-        else
-            hipLaunchKernelGGL((rs_scatter<K, false, R>), dim3(blocks), dim3(kThreads), 0, s, ka, va,
-                               kb, vb, n, shift, hist, offs, tiles);
+        if (!direct)
+            hipLaunchKernelGGL(rs_rowscan, dim3(nseg * 256), dim3(kThreads), 0, s, hist, tiles, total);
+        hipLaunchKernelGGL(scatter, dim3(blocks), dim3(kThreads), 0, s, ka, va, kb, vb, n, shift, hist,
+                           total, tiles);
         std::swap(ka, kb);
         std::swap(va, vb);
         *result_in_tmp = !*result_in_tmp;
@@ -322,13 +394,21 @@ hipError_t exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, uint32
                               hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int tiles = (int)sort_tiles(n);
+    if (n <= kOwnSumMax) {
+        // one launch in place of two: 4 us less for the short rows of small
+        // plans.  in and out must not be the same array (nor are they for the
+        // larger n, by the callers).
+        hipLaunchKernelGGL(scan_tile_apply<kOwnSums>, dim3(tiles), dim3(kThreads), 0, s, in, out, n,
+                           tile_sums);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(scan_tile_sums, dim3(tiles), dim3(kThreads), 0, s, in, n, tile_sums);
     if (tiles <= kApplySumMax) {
-        hipLaunchKernelGGL(scan_tile_apply<false>, dim3(tiles), dim3(kThreads), 0, s, in, out, n,
+        hipLaunchKernelGGL(scan_tile_apply<kTileSums>, dim3(tiles), dim3(kThreads), 0, s, in, out, n,
                            tile_sums);
     } else {
         hipLaunchKernelGGL(scan_single, dim3(1), dim3(1024), 0, s, tile_sums, (int64_t)tiles);
-        hipLaunchKernelGGL(scan_tile_apply<true>, dim3(tiles), dim3(kThreads), 0, s, in, out, n,
+        hipLaunchKernelGGL(scan_tile_apply<kScanned>, dim3(tiles), dim3(kThreads), 0, s, in, out, n,
                            tile_sums);
     }
     return hipGetLastError();
