@@ -1017,7 +1017,6 @@ int gpu_build(pmfmm_ctx* ctx, const std::vector<pmfmm::BoxParams>& boxes, const 
         dp = ctx->d.stage_pos.as<double>();
         dm = ctx->d.stage_mass.as<double>();
     }
-    HIP_TRY(pmfmm::gpu_enqueue_checks(ctx->d, dp, dm, n, s));
     const bool same = ctx->topo_on_device && ctx->topo_counts == cnt && same_boxes(ctx->topo_boxes, boxes);
     if (!same) {
         try {
@@ -1309,8 +1308,6 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
             return rc;
         }
     }
-    HIP_TRY(pmfmm::launch_zero_i32(counter, pmfmm::kQueueSegs * pmfmm::kCounterStride, s));
-    if (timing) HIP_TRY(hipEventRecord(ctx->ev[1], s));
     pmfmm::P2PArgs a{};
     a.x64 = ctx->d.x64.as<double4>();
     a.x32 = ctx->d.x32.as<float4>();
@@ -1337,6 +1334,9 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
                        : std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : default_wg_waves(mode),
                                   pmfmm::p2p_max_threads(mode) / 64);
     const int grid = launch_grid(ctx, ctx->n_cu * pmfmm::p2p_blocks_per_cu(mode, wg, lds));
+    if (pmfmm::queue_counts((int32_t)ctx->n_items, grid, wg))
+        HIP_TRY(pmfmm::launch_zero_i32(counter, pmfmm::kQueueSegs * pmfmm::kCounterStride, s));
+    if (timing) HIP_TRY(hipEventRecord(ctx->ev[1], s));
     HIP_TRY(pmfmm::launch_p2p(mode, a, wg, grid, lds, s));
     if (timing) HIP_TRY(hipEventRecord(ctx->ev[2], s));
     pmfmm::ReduceArgs r{ctx->d.leaf.as<int4>(), ctx->d.leaf_slot.as<int32_t>(), partial,
@@ -1618,13 +1618,7 @@ int pmfmm_adjoint(pmfmm_ctx* ctx, const double* w, double* grad_pos, double* gra
     HIP_TRY(ctx->d.w32.ensure((size_t)n * 16 + pmfmm::kReadAhead));
     HIP_TRY(pmfmm::launch_gather_w(w, ctx->d.perm.as<int32_t>(), ctx->d.w64.as<double4>(), ctx->d.w32.as<float4>(),
                                    (int32_t)n, s));
-    HIP_TRY(pmfmm::launch_zero_i32(ctx->d.counter.as<int32_t>(), pmfmm::kQueueSegs * pmfmm::kCounterStride, s));
     const bool timing = ctx->p.timing != 0;
-    if (timing) {
-        int rc = ensure_events(ctx);
-        if (rc) return rc;
-        HIP_TRY(hipEventRecord(ctx->ev[4], s));
-    }
     pmfmm::AdjArgs a{};
     a.x64 = ctx->d.x64.as<double4>();
     a.x32 = ctx->d.x32.as<float4>();
@@ -1662,6 +1656,13 @@ int pmfmm_adjoint(pmfmm_ctx* ctx, const double* w, double* grad_pos, double* gra
                                      pmfmm::is_fp32(mode) ? 16 : 4);
     const int grid =
         launch_grid(ctx, ctx->n_cu * pmfmm::adjoint_blocks_per_cu(mode, wg, a.table != nullptr));
+    if (pmfmm::queue_counts(a.n_items, grid, wg))
+        HIP_TRY(pmfmm::launch_zero_i32(a.counter, pmfmm::kQueueSegs * pmfmm::kCounterStride, s));
+    if (timing) {
+        int rc = ensure_events(ctx);
+        if (rc) return rc;
+        HIP_TRY(hipEventRecord(ctx->ev[4], s));
+    }
     HIP_TRY(pmfmm::launch_adjoint(mode, a, wg, grid, s));
     if (timing) {
         HIP_TRY(hipEventRecord(ctx->ev[5], s));

@@ -335,7 +335,7 @@ constexpr size_t kReadAhead = 128;
 
 // First queue position of segment x of a queue of n items (segments and
 // counters: kQueueSegs in plan.h).
-__device__ inline int32_t queue_seg_begin(int x, int32_t n) {
+__host__ __device__ inline int32_t queue_seg_begin(int x, int32_t n) {
     return (int32_t)(((int64_t)x * n + kQueueSegs - 1) / kQueueSegs);
 }
 
@@ -356,10 +356,16 @@ __device__ __forceinline__ ItemCursor item_cursor() {
     return ItemCursor{(int)(blockIdx.x % kQueueSegs), 0};
 }
 
+// Whether a launch of `grid` workgroups of `waves` waves reads the counters
+// (which must then be zero at its start).
+__host__ __device__ inline bool queue_counts(int32_t n_items, int grid, int waves) {
+    return (n_items + kQueueSegs - 1) / kQueueSegs > grid / kQueueSegs * waves;
+}
+
 __device__ __forceinline__ int take_item(ItemCursor& c, int lane, int32_t n_items,
                                          int32_t* __restrict__ counter) {
-    const int wgs = (int)(gridDim.x / kQueueSegs);   // at least this many per segment
-    if ((n_items + kQueueSegs - 1) / kQueueSegs <= wgs * (int)(blockDim.x >> 6)) {
+    if (!queue_counts(n_items, (int)gridDim.x, (int)(blockDim.x >> 6))) {
+        const int wgs = (int)(gridDim.x / kQueueSegs);   // at least this many per segment
         if (c.done++ != 0 || (int)(blockIdx.x / kQueueSegs) >= wgs) return -1;
         const int q = queue_seg_begin(c.seg, n_items) +
                       __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * wgs +

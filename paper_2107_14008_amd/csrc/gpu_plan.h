@@ -66,8 +66,8 @@ struct DevPlan {
     DevBuf p2p_row, wpos, keys, keys_tmp, plist, plist_tmp, hist, flag, lv_first, tile_sums;
     bool force64 = false;   // sort by the full 64-bit keys (a long run of equal short keys)
     DevBuf pc, pc_tmp, clo, chi, wcell, box_first, walkbox, front, front_next, p2p_keys,
-        p2p_keys_tmp, m2l_keys, m2l_keys_tmp, wcount, cost, cost_keys, cost_keys_tmp, queue_tmp,
-        item_count, cell_axis, farflag, walk_ctl, froots, loop_cells, m2l_vals, rowcnt,
+        p2p_keys_tmp, m2l_keys, m2l_keys_tmp, wcount, cost, item_cost, rowcand,
+        item_count, cell_axis, farflag, froots, loop_cells, m2l_vals, rowcnt,
         longrows;
     // scratch of the M2L rows, which may be built on another stream beside
     // the P2P rows
@@ -105,8 +105,8 @@ struct DevPlan {
                           &w64, &w32, &fargrad, &p2p_row, &wpos, &keys, &keys_tmp, &plist, &plist_tmp, &hist,
                           &flag, &lv_first, &tile_sums, &pc, &pc_tmp, &clo, &chi, &wcell,
                           &box_first, &walkbox, &front, &front_next, &p2p_keys, &p2p_keys_tmp,
-                          &m2l_keys, &m2l_keys_tmp, &wcount, &cost, &cost_keys, &cost_keys_tmp,
-                          &queue_tmp, &item_count, &cell_axis, &farflag, &walk_ctl, &froots,
+                          &m2l_keys, &m2l_keys_tmp, &wcount, &cost, &item_cost, &rowcand,
+                          &item_count, &cell_axis, &farflag, &froots,
                           &loop_cells, &m2l_vals, &rowcnt, &longrows})
             b->release();
     }
@@ -138,11 +138,6 @@ hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* tmp_keys, ui
 hipError_t exclusive_scan_i32(const int32_t* in, int32_t* out, int64_t n, uint32_t* tile_sums,
                               hipStream_t s);
 
-// Enqueues the checks of device particles (finite positions, finite
-// non-negative masses); gpu_build_plan reads their result.
-hipError_t gpu_enqueue_checks(DevPlan& d, const double* pos, const double* mass, int64_t n,
-                              hipStream_t s);
-
 // Uploads the tree shape of `topo` (cells, leaves, depth levels) and the
 // per-box constants.
 hipError_t upload_topology(DevPlan& d, const Plan& topo, const BoxDev* boxdev, hipStream_t s);
@@ -159,9 +154,9 @@ using M2LReady = std::function<std::string(int64_t n_m2l, int32_t dmin_src, int3
 // `mass` (n) in device memory, for the shape uploaded by upload_topology.
 // Fills perm, cell bounds and centres, x64 / x32, the P2P and M2L CSR, the
 // work items and queue.  Synchronises `s` (the list sizes come back to the
-// host).  Returns an error message ("" on success); when the checks of
-// gpu_enqueue_checks (which must precede it on `s`) fail, stops early and
-// sets *input_error to a message naming the first offending particle.
+// host).  Returns an error message ("" on success); for a non-finite position
+// or a negative or non-finite mass, stops early and sets *input_error to a
+// message naming the first offending particle.
 std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, const double* mass,
                            int chunk, hipStream_t s, PlanCounts& out, std::string* input_error,
                            const M2LReady& on_m2l = M2LReady(), hipStream_t side = nullptr);

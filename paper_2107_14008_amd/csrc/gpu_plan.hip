@@ -77,20 +77,52 @@ __device__ __forceinline__ uint32_t coord_key(double x, double scale, double kma
     return t >= kmax ? (uint32_t)kmax : (uint32_t)t;
 }
 
-__global__ void k_wrap_keys(const double* __restrict__ pos, int64_t n, const int32_t* __restrict__ bf,
-                            int nbox, const BoxDev* __restrict__ boxes, double* __restrict__ wpos,
-                            uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int key_bits) {
+// The start of a build: the words of the planner's counters (wcount, with
+// the walk's control words behind them) and the row counts to their initial
+// values, in one launch.
+constexpr int kCtlWords = 1024;         // walk control words, at wcount + kCtlAt
+constexpr int kCtlAt = 32;
+// wcount words: 0, 1 first bad position / mass (INT_MAX: none), 2 long-run flag
+// of the coordinate sort, 4 .. 7 the host-driven walk's M2L depths, 8, 9
+// candidate pairs, 10 items, 16, 17 smallest M2L depths (INT_MAX: none), 20 ..
+// 23 the host-driven walk's counters
+
+__global__ void k_init(int32_t* __restrict__ wcount, int32_t* __restrict__ rowcnt, int nrow,
+                       int32_t* __restrict__ rowcnt_m2l, int nrow_m2l, int32_t* __restrict__ m2l_row,
+                       int nm2l_row) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kCtlAt + kCtlWords)
+        wcount[i] = (i < 2 || i == 16 || i == 17) ? 0x7fffffff : 0;
+    if (i < nrow) rowcnt[i] = 0;
+    if (i < nrow_m2l) rowcnt_m2l[i] = 0;
+    if (i < nm2l_row) m2l_row[i] = 0;
+}
+
+// Per particle: the input checks, the wrapped position, the three sort keys
+// and the cell it starts in (its box's root).
+__global__ void k_prepare(const double* __restrict__ pos, const double* __restrict__ mass, int64_t n,
+                          const int32_t* __restrict__ bf, const int32_t* __restrict__ bfc, int nbox,
+                          const BoxDev* __restrict__ boxes, double* __restrict__ wpos,
+                          uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int key_bits,
+                          int32_t* __restrict__ pc, int* __restrict__ bad) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const double L = boxes[box_of(bf, nbox, (int)i)].L;
+    const int b = box_of(bf, nbox, (int)i);
+    const double L = boxes[b].L;
     const double range = key_bits == 24 ? 16777216.0 : 4294967296.0;
     const double scale = range / L;
+    double x[3];
+    for (int a = 0; a < 3; ++a) x[a] = pos[3 * i + a];
+    const double m = mass[i];
+    if (!(isfinite(x[0]) && isfinite(x[1]) && isfinite(x[2]))) atomicMin(&bad[0], (int)i);
+    if (!(isfinite(m) && m >= 0.0)) atomicMin(&bad[1], (int)i);
     for (int a = 0; a < 3; ++a) {
-        const double x = wrap_coord(pos[3 * i + a], L);
-        wpos[3 * i + a] = x;
-        keys[a * n + i] = coord_key(x, scale, range - 1.0);
+        const double y = wrap_coord(x[a], L);
+        wpos[3 * i + a] = y;
+        keys[a * n + i] = coord_key(y, scale, range - 1.0);
         vals[a * n + i] = (uint32_t)i;
     }
+    pc[i] = bfc[b];
 }
 
 // Full 64-bit keys of the wrapped coordinates (the fallback sort).
@@ -160,13 +192,6 @@ __global__ void k_box_keys(const uint32_t* __restrict__ vals, int64_t n, const i
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     keys[i] = (uint32_t)box_of(bf, nbox, (int)vals[i]);
-}
-
-__global__ void k_init_pc(int64_t n, const int32_t* __restrict__ bf, const int32_t* __restrict__ bfc,
-                          int nbox, int32_t* __restrict__ pc) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    pc[i] = bfc[box_of(bf, nbox, (int)i)];
 }
 
 // Bounds of every cell of one depth from the ends of its sorted ranges,
@@ -1191,9 +1216,12 @@ __global__ void k_m2l_split(const int32_t* __restrict__ row, int nrows, const in
     atomicMin(&mindep[1], aux[c].w);
 }
 
+// Items of every row (their scan gives each row's first slot); clears the
+// words that k_queue adds to.
 __global__ void k_item_count(int nl, const int32_t* __restrict__ row, int chunk,
-                             int32_t* __restrict__ cnt) {
+                             int32_t* __restrict__ cnt, uint32_t* __restrict__ wcount) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 3) wcount[8 + i] = 0u;
     if (i > nl) return;
     if (i == nl) { cnt[i] = 0; return; }
     const int len = row[i + 1] - row[i];
@@ -1201,94 +1229,103 @@ __global__ void k_item_count(int nl, const int32_t* __restrict__ row, int chunk,
 }
 
 // Work items of each TaskGroup row, one wavefront per row and one lane per
-// item; the queue key is (segment of the slot) * 256 + 255 - (pair count >>
-// cshift), so the sorted queue holds the kQueueSegs segments in order, each
-// longest first up to 1/256 of the largest item.  Slots from the item count
-// to `cap` get segment kQueueSegs (after every item in the stable sort).
-// rowcand[i]: candidate pairs of row i; ctl[2]: the item count.
+// item; cost[slot] = 255 - (pair count >> cshift), so that ascending costs are
+// the longest first up to 1/256 of the largest item.  rowcand[i]: candidate
+// pairs of row i.
 __global__ void k_items(int nl, const int32_t* __restrict__ row, const int32_t* __restrict__ js,
                         const int4* __restrict__ leaf, int chunk, int cshift,
-                        const int32_t* __restrict__ slot0, int cap, int4* __restrict__ items,
-                        uint64_t* __restrict__ cost_keys, uint32_t* __restrict__ slots,
-                        unsigned long long* __restrict__ rowcand, uint32_t* __restrict__ ctl) {
+                        const int32_t* __restrict__ slot0, int4* __restrict__ items,
+                        uint8_t* __restrict__ cost, unsigned long long* __restrict__ rowcand) {
     const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int i = (int)(gt >> 6), lane = (int)(gt & 63);
+    if (i >= nl) return;
     unsigned long long total = 0;
-    if (i < nl) {
-        const int r0 = row[i], len = row[i + 1] - r0;
-        if (len > 0) {
-            const int parts = (len + chunk - 1) / chunk;
-            const int base = len / parts, extra = len % parts;
-            const int ni = leaf[i].y;
-            for (int k = lane; k < parts; k += 64) {
-                const int t = r0 + k * base + min(k, extra);
-                const int sz = base + (k < extra ? 1 : 0);
-                // the tasks' source counts, eight loads in flight at a time
-                unsigned long long c = 0;
-                int q = t;
-                for (; q + 8 <= t + sz; q += 8) {
-                    int jv[8];
+    const int r0 = row[i], len = row[i + 1] - r0;
+    if (len > 0) {
+        const int parts = (len + chunk - 1) / chunk;
+        const int base = len / parts, extra = len % parts;
+        const int ni = leaf[i].y;
+        for (int k = lane; k < parts; k += 64) {
+            const int t = r0 + k * base + min(k, extra);
+            const int sz = base + (k < extra ? 1 : 0);
+            // the tasks' source counts, eight loads in flight at a time
+            unsigned long long c = 0;
+            int q = t;
+            for (; q + 8 <= t + sz; q += 8) {
+                int jv[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) jv[u] = js[q + u] >> 5;
+                for (int u = 0; u < 8; ++u) jv[u] = js[q + u] >> 5;
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) c += (unsigned long long)leaf[jv[u]].y;
-                }
-                for (; q < t + sz; ++q) c += (unsigned long long)leaf[js[q] >> 5].y;
-                c *= (unsigned long long)ni;
-                total += c;
-                const int s = slot0[i] + k;
-                items[s] = make_int4(i, t, t + sz, s);
-                const unsigned long long b = c >> cshift;
-                const uint64_t seg = (uint64_t)((int64_t)s * kQueueSegs / slot0[nl]);
-                cost_keys[s] = (seg << 8) | (uint64_t)(255u - (b > 255ull ? 255u : (uint32_t)b));
-                slots[s] = (uint32_t)s;
+                for (int u = 0; u < 8; ++u) c += (unsigned long long)leaf[jv[u]].y;
             }
+            for (; q < t + sz; ++q) c += (unsigned long long)leaf[js[q] >> 5].y;
+            c *= (unsigned long long)ni;
+            total += c;
+            const int s = slot0[i] + k;
+            items[s] = make_int4(i, t, t + sz, s);
+            const unsigned long long b = c >> cshift;
+            cost[s] = (uint8_t)(255u - (b > 255ull ? 255u : (uint32_t)b));
         }
     }
-    {
-        // padding slots, spread over all threads of the grid
-        const int n_items = slot0[nl];
-        if (gt == 0) ctl[2] = (uint32_t)n_items;
-        const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-        for (int64_t s = n_items + gt; s < cap; s += stride) {
-            cost_keys[s] = ((uint64_t)kQueueSegs << 8) | 255u;
-            slots[s] = (uint32_t)s;
-        }
-    }
-    // the row's candidate pairs (summed by k_sum_rows: one atomic per row
-    // on a single counter would serialise)
+    // the row's candidate pairs (summed by k_queue: one atomic per row on a
+    // single counter would serialise)
     for (int off = 32; off > 0; off >>= 1) total += __shfl_down(total, off);
-    if (lane == 0 && i < nl) rowcand[i] = total;
+    if (lane == 0) rowcand[i] = total;
 }
 
-// out = sum of v[0, n), by one workgroup of 1024 threads.
+// The queue, one workgroup per segment: a counting sort of its slots by cost
+// (the order inside a cost class, which only the schedule sees, is the order
+// in which the lanes arrive).  Eight launches of a radix sort over (segment,
+// cost) keys took its place before (64^3 build: 630 -> 578 us with the other
+// launches saved beside it).  Each workgroup also adds up
+// its share of the rows' candidate pairs.
 __global__ void __launch_bounds__(1024)
-k_sum_rows(const unsigned long long* __restrict__ v, int n, unsigned long long* __restrict__ out) {
+k_queue(int nl, const int32_t* __restrict__ slot0, const uint8_t* __restrict__ cost,
+        const unsigned long long* __restrict__ rowcand, uint32_t* __restrict__ queue,
+        uint32_t* __restrict__ wcount) {
+    __shared__ uint32_t h[256];
     __shared__ unsigned long long part[1024 / 64];
-    unsigned long long x = 0;
-    for (int i = threadIdx.x; i < n; i += 1024) x += v[i];
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = x;
+    const int t = threadIdx.x, lane = t & 63;
+    const int n = slot0[nl];
+    const int beg = queue_seg_begin((int)blockIdx.x, n), end = queue_seg_begin((int)blockIdx.x + 1, n);
+    if (t < 256) h[t] = 0u;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long t = 0;
-        for (int w = 0; w < 1024 / 64; ++w) t += part[w];
-        *out = t;
+#pragma unroll 4
+    for (int s = beg + t; s < end; s += 1024) atomicAdd(&h[cost[s]], 1u);
+    __syncthreads();
+    if (t < 64) {
+        uint32_t v[4], tot = 0;
+        for (int j = 0; j < 4; ++j) {
+            v[j] = h[4 * lane + j];
+            tot += v[j];
+        }
+        uint32_t x = tot;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off);
+            if (lane >= off) x += y;
+        }
+        uint32_t e = x - tot;
+        for (int j = 0; j < 4; ++j) {
+            h[4 * lane + j] = e;
+            e += v[j];
+        }
     }
-}
-
-__global__ void k_check(const double* __restrict__ pos, const double* __restrict__ mass, int64_t n,
-                        int* __restrict__ bad) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const double x = pos[3 * i], y = pos[3 * i + 1], z = pos[3 * i + 2], m = mass[i];
-    if (!(isfinite(x) && isfinite(y) && isfinite(z))) atomicMin(&bad[0], (int)i);
-    if (!(isfinite(m) && m >= 0.0)) atomicMin(&bad[1], (int)i);
-}
-
-__global__ void k_fill_i32(int* p, int n, int v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    __syncthreads();
+#pragma unroll 4
+    for (int s = beg + t; s < end; s += 1024) queue[beg + atomicAdd(&h[cost[s]], 1u)] = (uint32_t)s;
+    unsigned long long c = 0;
+    const int i0 = queue_seg_begin((int)blockIdx.x, nl), i1 = queue_seg_begin((int)blockIdx.x + 1, nl);
+#pragma unroll 4
+    for (int i = i0 + t; i < i1; i += 1024) c += rowcand[i];
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_down(c, off);
+    if (lane == 0) part[t >> 6] = c;
+    __syncthreads();
+    if (t == 0) {
+        unsigned long long all = 0;
+        for (int w = 0; w < 1024 / 64; ++w) all += part[w];
+        atomicAdd(reinterpret_cast<unsigned long long*>(wcount + 8), all);
+        if (blockIdx.x == 0) wcount[10] = (uint32_t)n;
+    }
 }
 
 inline unsigned grid_of(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
@@ -1310,26 +1347,6 @@ hipError_t up(DevBuf& b, const std::vector<T>& v, hipStream_t s) {
     hipError_t e = b.ensure(std::max<size_t>(16, v.size() * sizeof(T)));
     if (e != hipSuccess || v.empty()) return e;
     return hipMemcpyAsync(b.p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s);
-}
-
-// Sorts keys (and values) in place; swaps in the scratch buffers when the
-// number of passes leaves the result there.
-std::string sort_in_place(DevBuf& keys, DevBuf* vals, DevBuf& ktmp, DevBuf* vtmp, DevBuf& hist,
-                          int64_t n, int bit_end, hipStream_t s) {
-    if (n <= 1) return std::string();
-    bit_end = std::min(64, (bit_end + 7) / 8 * 8);
-    TRY(ktmp.ensure(n * 8));
-    if (vals) TRY(vtmp->ensure(n * 4));
-    TRY(hist.ensure((size_t)sort_hist_words(n) * 4));
-    bool in_tmp = false;
-    TRY(radix_sort_u64(keys.as<uint64_t>(), vals ? vals->as<uint32_t>() : nullptr, ktmp.as<uint64_t>(),
-                       vtmp ? vtmp->as<uint32_t>() : nullptr, hist.as<uint32_t>(), n, 0, bit_end, s,
-                       &in_tmp));
-    if (in_tmp) {
-        std::swap(keys, ktmp);
-        if (vals) std::swap(*vals, *vtmp);
-    }
-    return std::string();
 }
 
 // LDS capacity of the long-row sort; PMFMM_ROW_LDS lowers it (tests use it
@@ -1359,21 +1376,6 @@ struct PhaseTimer {
 };
 
 }  // namespace
-
-hipError_t gpu_enqueue_checks(DevPlan& d, const double* pos, const double* mass, int64_t n,
-                              hipStream_t s) {
-    hipError_t e = d.wcount.ensure(128);
-    if (e != hipSuccess) return e;
-    // wcount[0..1]: first bad position / mass (INT_MAX: none); wcount[2]:
-    // the long-run flag of the coordinate sort
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, reinterpret_cast<int*>(d.wcount.p), 2,
-                       0x7fffffff);
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, s, reinterpret_cast<int*>(d.wcount.p) + 2,
-                       1, 0);
-    hipLaunchKernelGGL(k_check, dim3(grid_of(n)), dim3(256), 0, s, pos, mass, n,
-                       reinterpret_cast<int*>(d.wcount.p));
-    return hipGetLastError();
-}
 
 hipError_t upload_topology(DevPlan& d, const Plan& topo, const BoxDev* boxdev, hipStream_t s) {
     const int64_t nc = (int64_t)topo.cells.size(), nl = (int64_t)topo.leaf_cell.size();
@@ -1486,10 +1488,20 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
     TRY(d.plist.ensure(n * 12));
     TRY(d.plist_tmp.ensure(n * 12));
     TRY(d.keys_tmp.ensure(n * 24));
+    TRY(d.pc.ensure(n * 4));
+    TRY(d.pc_tmp.ensure(n * 4));
+    TRY(d.wcount.ensure((kCtlAt + kCtlWords) * 4));
+    TRY(d.rowcnt.ensure((nl + 2) * 4));
+    TRY(d.rowcnt_m2l.ensure((nc + 2) * 4));
+    TRY(d.m2l_row.ensure((nc + 1) * 4));
+    hipLaunchKernelGGL(k_init, dim3(grid_of(std::max<int64_t>(nc + 2, kCtlAt + kCtlWords))), dim3(256), 0, s,
+                       d.wcount.as<int32_t>(), d.rowcnt.as<int32_t>(), (int)nl + 2,
+                       d.rowcnt_m2l.as<int32_t>(), (int)nc + 2, d.m2l_row.as<int32_t>(), (int)nc + 1);
     const int key_bits = n <= kKey24Max ? 24 : 32;
-    hipLaunchKernelGGL(k_wrap_keys, dim3(grid_of(n)), dim3(256), 0, s, pos, n,
-                       d.box_first.as<int32_t>(), nbox, d.boxes.as<BoxDev>(), d.wpos.as<double>(),
-                       d.keys.as<uint32_t>(), d.plist.as<uint32_t>(), key_bits);
+    hipLaunchKernelGGL(k_prepare, dim3(grid_of(n)), dim3(256), 0, s, pos, mass, n,
+                       d.box_first.as<int32_t>(), d.item_count.as<int32_t>(), nbox, d.boxes.as<BoxDev>(),
+                       d.wpos.as<double>(), d.keys.as<uint32_t>(), d.plist.as<uint32_t>(), key_bits,
+                       d.pc.as<int32_t>(), d.wcount.as<int>());
     TRY(hipGetLastError());
     // the three axis lists are three segments of one sort: by the key,
     // then each run of equal keys by coordinate
@@ -1541,8 +1553,6 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
 
     clk.lap("sort");
     // ---- ORB levels
-    TRY(d.pc.ensure(n * 4));
-    TRY(d.pc_tmp.ensure(n * 4));
     // mark bytes at 0, mark bits at bits_off; k_orb_fused reuses the buffer
     // for n int32
     const int64_t bits_off = (n + 255) / 256 * 256;
@@ -1555,9 +1565,6 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
     TRY(d.clo.ensure(nc * 24));
     TRY(d.chi.ensure(nc * 24));
     TRY(d.cell_axis.ensure(nc * 4));
-    hipLaunchKernelGGL(k_init_pc, dim3(grid_of(n)), dim3(256), 0, s, n, d.box_first.as<int32_t>(),
-                       d.item_count.as<int32_t>(), nbox, d.pc.as<int32_t>());
-    TRY(hipGetLastError());
     // the level loop partitions the cells above the fused subtrees
     const int nloop = (int)d.loop_depth_begin.size() - 1;
     for (int dep = 0; dep < nloop; ++dep) {
@@ -1640,7 +1647,6 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
 
     clk.lap("records");
     // ---- dual walk
-    TRY(d.wcount.ensure(128));
     // the canonical half of (root, root, s): the zero shift and the 13
     // shifts with code > 13
     const int64_t nf0 = 14 * (int64_t)nbox;
@@ -1654,13 +1660,15 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
     int64_t n_p2p = 0, n_m2l = 0;
     int32_t dmin_src = 0x7fffffff, dmin_tgt = 0x7fffffff;
     bool done = false;
+    bool any_m2l = false;
+    for (const BoxParams& b : topo.boxes) any_m2l = any_m2l || (b.order >= 0 && b.theta > 0.0);
     int flags[3] = {0, 0, 0};
     bool have_flags = false;
     const int2 ks = make_int2(5 + bits_for((uint64_t)std::max<int64_t>(1, nl - 1)),
                               5 + bits_for((uint64_t)std::max<int64_t>(1, nc - 1)));
     // Level-by-level walk without host round trips, sized from the previous
     // build of the same tree shape; falls back to the host-driven loop.
-    if (d.walk_cap_front > 0 && d.walk_levels > 0) {
+    if (d.walk_cap_front > 0 && d.walk_levels > 0 && d.walk_levels + 16 <= kCtlWords) {
         const uint32_t capf = d.walk_cap_front, capp = d.walk_cap_p2p, capm = d.walk_cap_m2l;
         const int L = d.walk_levels;
         TRY(d.front.ensure((size_t)std::max<int64_t>(capf, nf0) * 8));
@@ -1674,10 +1682,7 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
         int top = 0;
         while (top < L && top < (int)d.walk_sizes.size() && d.walk_sizes[top] <= kWalkTopMax) ++top;
         const int Le = top + 2 * ((L - top + 1) / 2);
-        TRY(d.walk_ctl.ensure((size_t)(Le + 8) * 4));
-        hipLaunchKernelGGL(k_zero_u32, dim3((Le + 8 + 255) / 256), dim3(256), 0, s,
-                           d.walk_ctl.as<uint32_t>(), Le + 8);
-        uint32_t* ctl = d.walk_ctl.as<uint32_t>();
+        uint32_t* ctl = d.wcount.as<uint32_t>() + kCtlAt;   // cleared by k_init
         uint32_t* sizes = ctl + 4;
         hipLaunchKernelGGL(k_walk_top, dim3(1), dim3(kWalkT), 0, s, nbox, d.item_count.as<int32_t>(),
                            d.front.as<int2>(), d.front_next.as<int2>(), top, sizes, ctl, capf,
@@ -1695,18 +1700,17 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
                                d.p2p_keys.as<uint64_t>(), d.m2l_keys.as<uint64_t>());
             cur ^= 1;
         }
-        hipLaunchKernelGGL(k_m2l_depths, dim3(8), dim3(256), 0, s, d.m2l_keys.as<uint64_t>(),
-                           ctl + 1, capm, ks.y, d.cell_aux.as<int4>(), ctl + 5 + Le);
+        if (any_m2l)
+            hipLaunchKernelGGL(k_m2l_depths, dim3(8), dim3(256), 0, s, d.m2l_keys.as<uint64_t>(),
+                               ctl + 1, capm, ks.y, d.cell_aux.as<int4>(), ctl + 5 + Le);
         TRY(hipGetLastError());
         // the walk's counts and the input checks in one round trip, into
         // pinned memory
         TRY(d.ensure_host_rb());
-        if (Le + 7 + 3 > DevPlan::kHostRbWords) return "walk has too many levels for the read-back buffer";
-        TRY(hipMemcpyAsync(d.host_rb, ctl, (Le + 7) * 4, hipMemcpyDeviceToHost, s));
-        TRY(hipMemcpyAsync(d.host_rb + Le + 7, d.wcount.p, 12, hipMemcpyDeviceToHost, s));
+        TRY(hipMemcpyAsync(d.host_rb, d.wcount.p, (kCtlAt + Le + 7) * 4, hipMemcpyDeviceToHost, s));
         TRY(hipStreamSynchronize(s));
-        std::vector<uint32_t> hc(d.host_rb, d.host_rb + Le + 7);
-        std::memcpy(flags, d.host_rb + Le + 7, 12);
+        std::vector<uint32_t> hc(d.host_rb + kCtlAt, d.host_rb + kCtlAt + Le + 7);
+        std::memcpy(flags, d.host_rb, 12);
         have_flags = true;
         if (clk.on) {
             std::fprintf(stderr, "[pmfmm gpu plan] walk frontier per level:");
@@ -1729,6 +1733,7 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
         // this loop's counters: wcount[20..23] (words 0..2 hold the checks)
         uint32_t* wc = d.wcount.as<uint32_t>() + 20;
         hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, wc, 4);
+        // (an overflowed walk above has left its keys' counts elsewhere)
         if (d.p2p_keys.bytes < 16) TRY(d.p2p_keys.ensure(1 << 20));
         if (d.m2l_keys.bytes < 16) TRY(d.m2l_keys.ensure(1 << 16));
         uint32_t hc[4] = {0, 0, 0, 0};
@@ -1805,17 +1810,14 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
     // ---- canonical order and CSR
     TRY(d.p2p_row.ensure((nl + 1) * 4));
     TRY(d.js.ensure(std::max<int64_t>(1, n_p2p) * 4));
-    TRY(d.m2l_row.ensure((nc + 1) * 4));
     TRY(d.m2l_src.ensure(std::max<int64_t>(1, n_m2l) * 4));
     TRY(d.m2l_shift.ensure(std::max<int64_t>(1, n_m2l) * 4));
     TRY(d.m2l_vals.ensure(std::max<int64_t>(1, n_m2l) * 4));
     // slots, then long-row scratch: two int32 per key
     TRY(d.p2p_keys_tmp.ensure(std::max<int64_t>(1, n_p2p) * 8));
     TRY(d.m2l_keys_tmp.ensure(std::max<int64_t>(1, n_m2l) * 8));
-    TRY(d.rowcnt.ensure((nl + 2) * 4));
     TRY(d.longrows.ensure((nl + 1) * 4));
     TRY(d.tile_sums.ensure(sort_tiles(nl + 1) * 4 + 16));
-    TRY(d.rowcnt_m2l.ensure((nc + 2) * 4));
     TRY(d.longrows_m2l.ensure((nc + 1) * 4));
     TRY(d.tile_sums_m2l.ensure(sort_tiles(nc + 1) * 4 + 16));
     struct RowList {
@@ -1826,7 +1828,7 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
         DevBuf& row;
         DevBuf& vals;
         DevBuf& tmp;       // per-key slots, then long-row scratch
-        DevBuf& cnt;       // nrows + 2 counts
+        DevBuf& cnt;       // nrows + 2 counts, cleared by k_init
         DevBuf& longs;     // nrows + 1
         DevBuf& tsums;     // scan scratch
     };
@@ -1836,8 +1838,6 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
                            d.m2l_keys_tmp, d.rowcnt_m2l, d.longrows_m2l, d.tile_sums_m2l};
     // the rows in two parts: the atomic row counts, then the rest
     auto count_rows = [&](const RowList& rl, hipStream_t st) -> hipError_t {
-        hipLaunchKernelGGL(k_zero_u32, dim3(grid_of(rl.nrows + 2)), dim3(256), 0, st,
-                           rl.cnt.as<uint32_t>(), rl.nrows + 2);
         if (rl.nk > 0)
             hipLaunchKernelGGL(k_row_count, dim3(grid_of(rl.nk, kRcKeys)), dim3(kRcThreads), 0, st,
                                rl.keys.as<uint64_t>(), rl.nk, rl.ks, rl.cnt.as<int32_t>(),
@@ -1882,17 +1882,17 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
         // on s while the host enqueues the side stream's launches
         TRY(count_rows(p2p_rows, s));
     }
-    TRY(count_rows(m2l_rows, ms));
-    TRY(finish_rows(m2l_rows, ms));
-    // M2L sources and shifts; the smallest depths go to wcount words 16, 17
-    // (the walk's k_m2l_depths gave the same values to the host already)
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, ms, reinterpret_cast<int*>(d.wcount.p) + 16,
-                       2, 0x7fffffff);
-    if (n_m2l > 0)
+    // M2L rows (all empty, as k_init left them, without tasks), sources and
+    // shifts; the smallest depths go to wcount words 16, 17 (the walk's
+    // k_m2l_depths gave the same values to the host already)
+    if (n_m2l > 0) {
+        TRY(count_rows(m2l_rows, ms));
+        TRY(finish_rows(m2l_rows, ms));
         hipLaunchKernelGGL(k_m2l_split, dim3(grid_of(nc)), dim3(256), 0, ms, d.m2l_row.as<int32_t>(),
                            (int)nc, d.m2l_vals.as<int32_t>(), d.cell_aux.as<int4>(),
                            d.m2l_src.as<int32_t>(), d.m2l_shift.as<int32_t>(),
                            reinterpret_cast<int32_t*>(d.wcount.p) + 16);
+    }
     TRY(hipGetLastError());
     if (fork) TRY(hipEventRecord(d.m2l_done, side));
     if (!fork) TRY(count_rows(p2p_rows, s));
@@ -1918,8 +1918,9 @@ std::string gpu_make_items(DevPlan& d, const Plan& topo, int64_t n_p2p, int chun
     TRY(d.cost.ensure((nl + 1) * 4));
     TRY(d.leaf_slot.ensure((nl + 1) * 4));
     TRY(d.tile_sums.ensure(sort_tiles(nl + 1) * 4 + 16));
+    TRY(d.wcount.ensure((kCtlAt + kCtlWords) * 4));
     hipLaunchKernelGGL(k_item_count, dim3(grid_of(nl + 1)), dim3(256), 0, s, (int)nl,
-                       d.p2p_row.as<int32_t>(), chunk, d.cost.as<int32_t>());
+                       d.p2p_row.as<int32_t>(), chunk, d.cost.as<int32_t>(), d.wcount.as<uint32_t>());
     TRY(hipGetLastError());
     TRY(exclusive_scan_i32(d.cost.as<int32_t>(), d.leaf_slot.as<int32_t>(), nl + 1,
                            d.tile_sums.as<uint32_t>(), s));
@@ -1928,25 +1929,19 @@ std::string gpu_make_items(DevPlan& d, const Plan& topo, int64_t n_p2p, int chun
     // only at the end
     const int64_t cap = std::max<int64_t>(1, (n_p2p + chunk - 1) / chunk + nl);
     TRY(d.items.ensure(cap * 16));
-    TRY(d.cost_keys.ensure(cap * 8));
-    // per-row candidate pairs in the sort's scratch (free until the sort)
-    TRY(d.cost_keys_tmp.ensure(std::max<int64_t>(cap, nl) * 8));
+    TRY(d.item_cost.ensure(cap));
+    TRY(d.rowcand.ensure(nl * 8));
     TRY(d.queue.ensure(cap * 4));
-    TRY(d.wcount.ensure(128));
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, d.wcount.as<uint32_t>(), 16);
     // largest item: chunk tasks of at most 64 x 64 pairs
     const int cshift = std::max(0, bits_for((uint64_t)chunk * 64 * 64) - 8);
-    hipLaunchKernelGGL(k_items, dim3(grid_of((nl + 1) * 64)), dim3(256), 0, s, (int)nl,
+    hipLaunchKernelGGL(k_items, dim3(grid_of(nl * 64)), dim3(256), 0, s, (int)nl,
                        d.p2p_row.as<int32_t>(), d.js.as<int32_t>(), d.leaf.as<int4>(), chunk, cshift,
-                       d.leaf_slot.as<int32_t>(), (int)cap, d.items.as<int4>(),
-                       d.cost_keys.as<uint64_t>(), d.queue.as<uint32_t>(),
-                       d.cost_keys_tmp.as<unsigned long long>(), d.wcount.as<uint32_t>() + 8);
-    hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(1024), 0, s, d.cost_keys_tmp.as<unsigned long long>(),
-                       (int)nl, reinterpret_cast<unsigned long long*>(d.wcount.as<uint32_t>() + 8));
+                       d.leaf_slot.as<int32_t>(), d.items.as<int4>(), d.item_cost.as<uint8_t>(),
+                       d.rowcand.as<unsigned long long>());
+    hipLaunchKernelGGL(k_queue, dim3(kQueueSegs), dim3(1024), 0, s, (int)nl, d.leaf_slot.as<int32_t>(),
+                       d.item_cost.as<uint8_t>(), d.rowcand.as<unsigned long long>(),
+                       d.queue.as<uint32_t>(), d.wcount.as<uint32_t>());
     TRY(hipGetLastError());
-    std::string err = sort_in_place(d.cost_keys, &d.queue, d.cost_keys_tmp, &d.queue_tmp, d.hist,
-                                    cap, 12, s);
-    if (!err.empty()) return err;
     // words 8, 9: candidate pairs; 10: items; 16, 17: M2L depths (set by the build)
     uint32_t w[10];
     TRY(d.ensure_host_rb());
