@@ -63,11 +63,11 @@ struct DevPlan {
     DevBuf cell, cell_aux, cellc, M, Lc, Lt, m2l_row, m2l_src, m2l_shift, level_cells;
     DevBuf w64, w32, fargrad;
     // on-GPU planner scratch
-    DevBuf p2p_row, wpos, keys, keys_tmp, plist, plist_tmp, hist, flag, lv_first, tile_sums;
+    DevBuf p2p_row, wpos, keys, keys_tmp, plist, plist_tmp, hist, flag, tile_sums;
     bool force64 = false;   // sort by the full 64-bit keys (a long run of equal short keys)
-    DevBuf pc, pc_tmp, clo, chi, wcell, box_first, walkbox, front, front_next, p2p_keys,
+    DevBuf clo, chi, wcell, box_first, walkbox, front, front_next, p2p_keys,
         p2p_keys_tmp, m2l_keys, m2l_keys_tmp, wcount, cost, item_cost, rowcand,
-        item_count, cell_axis, farflag, froots, loop_cells, m2l_vals, rowcnt,
+        item_count, cell_axis, farflag, froots, loop_cells, loop_tiles, m2l_vals, rowcnt,
         longrows;
     // scratch of the M2L rows, which may be built on another stream beside
     // the P2P rows
@@ -103,11 +103,11 @@ struct DevPlan {
                           &boxes, &table, &adj_table, &ftable, &x64, &x32, &stage_pos, &stage_mass, &far, &cell,
                           &cell_aux, &cellc, &M, &Lc, &Lt, &m2l_row, &m2l_src, &m2l_shift, &level_cells,
                           &w64, &w32, &fargrad, &p2p_row, &wpos, &keys, &keys_tmp, &plist, &plist_tmp, &hist,
-                          &flag, &lv_first, &tile_sums, &pc, &pc_tmp, &clo, &chi, &wcell,
+                          &flag, &tile_sums, &clo, &chi, &wcell,
                           &box_first, &walkbox, &front, &front_next, &p2p_keys, &p2p_keys_tmp,
                           &m2l_keys, &m2l_keys_tmp, &wcount, &cost, &item_cost, &rowcand,
                           &item_count, &cell_axis, &farflag, &froots,
-                          &loop_cells, &m2l_vals, &rowcnt, &longrows})
+                          &loop_cells, &loop_tiles, &m2l_vals, &rowcnt, &longrows})
             b->release();
     }
 };

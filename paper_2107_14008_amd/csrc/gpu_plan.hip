@@ -98,13 +98,12 @@ __global__ void k_init(int32_t* __restrict__ wcount, int32_t* __restrict__ rowcn
     if (i < nm2l_row) m2l_row[i] = 0;
 }
 
-// Per particle: the input checks, the wrapped position, the three sort keys
-// and the cell it starts in (its box's root).
+// Per particle: the input checks, the wrapped position and the three sort keys.
 __global__ void k_prepare(const double* __restrict__ pos, const double* __restrict__ mass, int64_t n,
-                          const int32_t* __restrict__ bf, const int32_t* __restrict__ bfc, int nbox,
+                          const int32_t* __restrict__ bf, int nbox,
                           const BoxDev* __restrict__ boxes, double* __restrict__ wpos,
                           uint32_t* __restrict__ keys, uint32_t* __restrict__ vals, int key_bits,
-                          int32_t* __restrict__ pc, int* __restrict__ bad) {
+                          int* __restrict__ bad) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int b = box_of(bf, nbox, (int)i);
@@ -122,7 +121,6 @@ __global__ void k_prepare(const double* __restrict__ pos, const double* __restri
         keys[a * n + i] = coord_key(y, scale, range - 1.0);
         vals[a * n + i] = (uint32_t)i;
     }
-    pc[i] = bfc[b];
 }
 
 // Full 64-bit keys of the wrapped coordinates (the fallback sort).
@@ -194,103 +192,87 @@ __global__ void k_box_keys(const uint32_t* __restrict__ vals, int64_t n, const i
     keys[i] = (uint32_t)box_of(bf, nbox, (int)vals[i]);
 }
 
-// Bounds of every cell of one depth from the ends of its sorted ranges,
-// the split axis of those that split, and pfirst[c]: the left marks before
-// cell c's first position, the same in each of the three lists.  A
-// splitting cell marks the first floor(count / 2) positions of its range in
-// every list and nothing else is marked, so with the level's cells in
-// position order (the pre-order within one depth) pfirst[c] = the marks of
-// the level's cells before c: a scan over the level's cells, no marks read.
-// One workgroup.
-constexpr int kCellsT = 1024;
+// One level of the level loop: the cells that split at this depth, in position
+// order, and where each tile of kLvTile positions finds its first one.  Both
+// depend on the shape of the tree alone and come from the host: a position's
+// cell is then at most a step or two from its tile's first (the loop's cells
+// hold more than kFuseM particles, or more than kFuseC cells), and no array of
+// cells by position is read, partitioned and written at every level.
+struct LevelCells {
+    const int4* cells;      // (first position, count, cell id, left marks before it)
+    const int32_t* tile;    // per tile: index of the first cell that ends beyond its start
+    int count;
+    int32_t* axis;          // per cell: split axis, written by k_level_flag
+};
 
-__global__ void __launch_bounds__(kCellsT)
-k_cells_level(const int32_t* __restrict__ level, int nd, const int4* __restrict__ cell,
-              const int4* __restrict__ aux, const uint32_t* __restrict__ plist, int64_t n,
-              const double* __restrict__ wpos, double* __restrict__ clo, double* __restrict__ chi,
-              int32_t* __restrict__ axis_out, int32_t* __restrict__ pfirst) {
-    __shared__ uint32_t wsum[kCellsT / 64];
-    __shared__ uint32_t carry;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    if (t == 0) carry = 0u;
-    __syncthreads();
-    for (int k0 = 0; k0 < nd; k0 += kCellsT) {
-        const int k = k0 + t;
-        uint32_t half = 0u;
-        int c = -1;
-        if (k < nd) {
-            c = level[k];
-            const int4 ci = cell[c];
-            double lo[3], hi[3];
-            for (int a = 0; a < 3; ++a) {
-                lo[a] = wpos[3 * (size_t)plist[a * n + ci.x] + a];
-                hi[a] = wpos[3 * (size_t)plist[a * n + ci.x + ci.y - 1] + a];
-                clo[3 * (size_t)c + a] = lo[a];
-                chi[3 * (size_t)c + a] = hi[a];
-            }
-            if (aux[c].x >= 0) {
-#pragma clang fp contract(off)
-                const double e0 = hi[0] - lo[0], e1 = hi[1] - lo[1], e2 = hi[2] - lo[2];
-                int axis = 0;
-                double best = e0;
-                if (e1 > best) { axis = 1; best = e1; }
-                if (e2 > best) axis = 2;
-                axis_out[c] = axis;
-                half = (uint32_t)(ci.y / 2);
-            }
-        }
-        uint32_t x = half;
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = __shfl_up(x, off);
-            if (lane >= off) x += y;
-        }
-        if (lane == 63) wsum[wave] = x;
-        __syncthreads();
-        uint32_t before = 0u, tot = 0u;
-        for (int w = 0; w < kCellsT / 64; ++w) {
-            const uint32_t v = wsum[w];
-            if (w < wave) before += v;
-            tot += v;
-        }
-        if (k < nd) pfirst[c] = (int32_t)(carry + before + x - half);
-        __syncthreads();
-        if (t == 0) carry += tot;
-        __syncthreads();
+// The cell of position i, from index c on (c only grows); false if i is in no
+// cell of the level.
+__device__ __forceinline__ bool level_cell(const LevelCells& lv, int64_t i, int& c, int4& ci) {
+    while (c < lv.count) {
+        ci = lv.cells[c];
+        if (i < (int64_t)ci.x + ci.y) return i >= ci.x;
+        ++c;
     }
-}
-
-// Left marks of the particles of the cells splitting at this level (sax[c]
-// >= 0), from their positions in the split axis's list, as bytes indexed by
-// particle (a byte store needs no atomic); k_pack_marks then packs them
-// into bits for the level's random reads.
-__global__ void k_flag(int64_t n, const int32_t* __restrict__ pc, const int4* __restrict__ cell,
-                       const int32_t* __restrict__ sax, const uint32_t* __restrict__ plist,
-                       uint8_t* __restrict__ flag) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int c = pc[i];
-    const int ax = sax[c];
-    if (ax < 0) return;
-    const int4 ci = cell[c];
-    flag[plist[ax * n + i]] = (i - ci.x < ci.y / 2) ? 1 : 0;
+    return false;
 }
 
 // The stable partition of one level, with the left marks of the three lists
 // (list a at [a n, (a + 1) n) of plist) computed where they are used instead
 // of stored: a position's mark is its particle's left mark if its cell
 // splits at this level, else 0.  A tile is the list positions [b T, (b + 1)
-// T), T = 1024, of all three lists, whose cells are the same (one pc / sax /
-// cell read serves the three).  k_level_sums counts each tile's marks per
-// list; k_cells_level has given the count of marks before each splitting
-// cell's first position (the same in the three lists), and k_level_move
-// counts them before every position (the tiles before its own, summed
-// where they are needed, + the in-tile scan) and from the difference places
-// the position.
+// T), T = 1024, of all three lists, whose cells are the same.  A splitting
+// cell marks the first floor(count / 2) positions of its range in every list
+// and nothing else is marked, so the marks before a cell's first position are
+// the same in the three lists and known from the shape.  k_level_flag gives
+// every particle its mark, k_level_sums counts each tile's marks per list, and
+// k_level_move counts them before every position (the tiles before its own,
+// summed where they are needed, + the in-tile scan) and from the difference
+// places the position.
 constexpr int kLvThreads = 256;
 constexpr int kLvRounds = 4;
 constexpr int kLvTile = kLvThreads * kLvRounds;   // 1024 positions of each list
 
-// The particles' left marks as bits: k_flag writes one byte per particle of
+// Per tile: the bounds of the cells it meets from the ends of their sorted
+// ranges (six lanes of every wave, two dependent loads; one workgroup for the
+// level's cells took a launch of its own), their split axes, and the left
+// marks of its positions in the split axis's list, as bytes indexed by
+// particle (a byte store needs no atomic); k_pack_marks then packs them into
+// bits for the level's random reads.  The tile that holds a cell's first
+// position writes its bounds and axis.
+__global__ void __launch_bounds__(kLvThreads)
+k_level_flag(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
+             const double* __restrict__ wpos, double* __restrict__ clo, double* __restrict__ chi,
+             uint8_t* __restrict__ flag) {
+    const int64_t base = (int64_t)blockIdx.x * kLvTile, last = min(n, base + kLvTile);
+    const int t = threadIdx.x, lane = t & 63;
+    for (int c = lv.tile[blockIdx.x]; c < lv.count; ++c) {
+        const int4 ci = lv.cells[c];
+        if (ci.x >= last) break;
+        const int a = min(lane >> 1, 2);
+        const int64_t e = (lane & 1) ? (int64_t)ci.x + ci.y - 1 : ci.x;
+        const double v = wpos[3 * (size_t)plist[(int64_t)a * n + e] + a];
+        const double lo[3] = {__shfl(v, 0), __shfl(v, 2), __shfl(v, 4)};
+        const double hi[3] = {__shfl(v, 1), __shfl(v, 3), __shfl(v, 5)};
+        int axis = 0;
+        {
+#pragma clang fp contract(off)
+            const double e0 = hi[0] - lo[0], e1 = hi[1] - lo[1], e2 = hi[2] - lo[2];
+            double best = e0;
+            if (e1 > best) { axis = 1; best = e1; }
+            if (e2 > best) axis = 2;
+        }
+        if (ci.x >= base && t < 3) {
+            clo[3 * (size_t)ci.z + t] = t == 0 ? lo[0] : t == 1 ? lo[1] : lo[2];
+            chi[3 * (size_t)ci.z + t] = t == 0 ? hi[0] : t == 1 ? hi[1] : hi[2];
+            if (t == 0) lv.axis[c] = axis;
+        }
+        const int64_t i1 = min(last, (int64_t)ci.x + ci.y), half = (int64_t)ci.x + ci.y / 2;
+        for (int64_t i = max(base, (int64_t)ci.x) + t; i < i1; i += kLvThreads)
+            flag[plist[axis * n + i]] = i < half ? 1 : 0;
+    }
+}
+
+// The particles' left marks as bits: k_level_flag writes one byte per particle of
 // a splitting cell (scattered by particle), and this packs the bytes of
 // particles [64 w, 64 w + 64) into word w (one wavefront per word).  The
 // level's random reads by particle then fall on n / 8 bytes, which stay in
@@ -307,25 +289,23 @@ __device__ __forceinline__ uint32_t mark_bit(const uint64_t* __restrict__ bits, 
     return (uint32_t)(bits[p >> 6] >> (p & 63u)) & 1u;
 }
 
-// sax[c]: the split axis of a cell that splits at this level, else -1.  On
-// the split axis's own list the mark follows from the position alone, so
+// On the split axis's own list the mark follows from the position alone, so
 // only the two other lists read the particle's bit.
 // tile_sums[a ntiles + b]: the marks of list a in tile b.
 __global__ void __launch_bounds__(kLvThreads)
-k_level_sums(int64_t n, const int32_t* __restrict__ pc, const int32_t* __restrict__ sax,
-             const int4* __restrict__ cell, const uint32_t* __restrict__ plist,
+k_level_sums(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
              const uint64_t* __restrict__ bits, uint32_t* __restrict__ tile_sums, int ntiles) {
     __shared__ uint64_t wsum[kLvThreads / 64];
     const int64_t base = (int64_t)blockIdx.x * kLvTile;
     // the three counts packed 21 bits apart (each at most kLvTile)
     uint64_t cnt = 0;
+    int c = lv.tile[blockIdx.x];
+#pragma unroll
     for (int r = 0; r < kLvRounds; ++r) {
         const int64_t i = base + r * kLvThreads + threadIdx.x;
-        if (i >= n) continue;
-        const int c = pc[i];
-        const int ax = sax[c];
-        if (ax < 0) continue;
-        const int4 ci = cell[c];
+        int4 ci;
+        if (i >= n || !level_cell(lv, i, c, ci)) continue;
+        const int ax = lv.axis[c];
         const uint32_t own = (i - ci.x < ci.y / 2) ? 1u : 0u;
         for (int a = 0; a < 3; ++a) {
             const uint32_t m = a == ax ? own : mark_bit(bits, plist[(int64_t)a * n + i]);
@@ -351,12 +331,10 @@ constexpr int kLvSumMax = 2048;
 
 template <bool SCANNED>
 __global__ void __launch_bounds__(kLvThreads)
-k_level_move(int64_t n, const int32_t* __restrict__ pc, int32_t* __restrict__ pc_out,
-             const int4* __restrict__ cell, const int4* __restrict__ aux,
-             const int32_t* __restrict__ sax, const uint32_t* __restrict__ plist,
+k_level_move(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
              uint32_t* __restrict__ pout, const uint64_t* __restrict__ bits,
              const uint32_t* __restrict__ tile_sums, const uint32_t* __restrict__ offs,
-             int ntiles, const int32_t* __restrict__ pfirst) {
+             int ntiles) {
     __shared__ uint8_t mk[3][kLvTile];
     __shared__ uint16_t pre[3][kLvTile];
     __shared__ uint64_t wsum[kLvThreads / 64];
@@ -374,19 +352,20 @@ k_level_move(int64_t n, const int32_t* __restrict__ pc, int32_t* __restrict__ pc
     }
     const int64_t base = (int64_t)blockIdx.x * kLvTile;
     uint32_t pv[kLvRounds][3];
-    int32_t cv[kLvRounds];
+    int4 cv[kLvRounds];     // the position's cell; count 0: none splits here
+    int c = lv.tile[blockIdx.x];
+#pragma unroll
     for (int r = 0; r < kLvRounds; ++r) {
         const int64_t i = base + r * kLvThreads + t;
         uint32_t m[3] = {0u, 0u, 0u};
-        cv[r] = -1;
+        cv[r] = make_int4(0, 0, 0, 0);
         pv[r][0] = pv[r][1] = pv[r][2] = 0u;
         if (i < n) {
-            const int c = pc[i];
-            cv[r] = c;
             for (int a = 0; a < 3; ++a) pv[r][a] = plist[(int64_t)a * n + i];
-            const int ax = sax[c];
-            if (ax >= 0) {
-                const int4 ci = cell[c];
+            int4 ci;
+            if (level_cell(lv, i, c, ci)) {
+                cv[r] = ci;
+                const int ax = lv.axis[c];
                 const uint32_t own = (i - ci.x < ci.y / 2) ? 1u : 0u;
                 for (int a = 0; a < 3; ++a) m[a] = a == ax ? own : mark_bit(bits, pv[r][a]);
             }
@@ -424,25 +403,23 @@ k_level_move(int64_t n, const int32_t* __restrict__ pc, int32_t* __restrict__ pc
             for (int w = 0; w < kLvThreads / 64; ++w) toff[a] += woff[a][w];
         }
     }
+#pragma unroll
     for (int r = 0; r < kLvRounds; ++r) {
         const int64_t i = base + r * kLvThreads + t;
         if (i >= n) continue;
-        const int c = cv[r];
-        if (sax[c] < 0) {
+        const int4 ci = cv[r];
+        if (ci.y == 0) {
             for (int a = 0; a < 3; ++a) pout[(int64_t)a * n + i] = pv[r][a];
-            pc_out[i] = c;
             continue;
         }
-        const int4 ci = cell[c];
         const int64_t first = ci.x, nl = ci.y / 2;
-        const int64_t pf = pfirst[c];
+        const int64_t pf = (uint32_t)ci.w;
         for (int a = 0; a < 3; ++a) {
             const int j = r * kLvThreads + t;
             const int64_t lr = (int64_t)(toff[a] + pre[a][j]) - pf;
             const int64_t pos = mk[a][j] ? first + lr : first + nl + (i - first - lr);
             pout[(int64_t)a * n + pos] = pv[r][a];
         }
-        pc_out[i] = (i - first < nl) ? aux[c].x : aux[c].y;
     }
 }
 
@@ -1432,7 +1409,7 @@ hipError_t upload_topology(DevPlan& d, const Plan& topo, const BoxDev* boxdev, h
     auto fusable = [&](int64_t k) {
         return topo.cells[k].count <= kFuseM && sub[k] <= kFuseC;
     };
-    std::vector<int32_t> roots, split(nc, 0), loop_cells;
+    std::vector<int32_t> roots, split(nc, 0), loop_cells, loop_tiles;
     std::vector<int32_t> loop_begin(1, 0);
     for (int64_t k = 0; k < nc; ++k) {
         const Cell& c = topo.cells[k];
@@ -1446,15 +1423,29 @@ hipError_t upload_topology(DevPlan& d, const Plan& topo, const BoxDev* boxdev, h
             roots.push_back(deep[k]);
         }
     }
+    // per level of the loop: its cells (first, count, id, left marks before
+    // them; the pre-order within a depth is the position order) and each
+    // tile's first cell
+    const int64_t n_tiles = (topo.n + kLvTile - 1) / kLvTile;
     for (int dep = 0; dep + 1 < (int)topo.depth_begin.size(); ++dep) {
         const size_t before = loop_cells.size();
-        for (int q = topo.depth_begin[dep]; q < topo.depth_begin[dep + 1]; ++q)
-            if (split[topo.cells_by_depth[q]]) loop_cells.push_back(topo.cells_by_depth[q]);
+        uint32_t marks = 0;
+        for (int q = topo.depth_begin[dep]; q < topo.depth_begin[dep + 1]; ++q) {
+            const int32_t k = topo.cells_by_depth[q];
+            if (!split[k]) continue;
+            const Cell& c = topo.cells[k];
+            for (int32_t v : {c.first, c.count, k, (int32_t)marks}) loop_cells.push_back(v);
+            marks += (uint32_t)(c.count / 2);
+        }
         if (loop_cells.size() == before) break;
-        loop_begin.push_back((int32_t)loop_cells.size());
+        size_t at = before;
+        for (int64_t b = 0; b < n_tiles; ++b) {
+            while (at < loop_cells.size() && (int64_t)loop_cells[at] + loop_cells[at + 1] <= b * kLvTile) at += 4;
+            loop_tiles.push_back((int32_t)((at - before) / 4));
+        }
+        loop_begin.push_back((int32_t)(loop_cells.size() / 4));
     }
     d.n_froots = (int)(roots.size() / 4);
-    const std::vector<int32_t> sax0(nc, -1);
     d.loop_depth_begin = loop_begin;
     hipError_t e;
     if ((e = up(d.cell, cell, s)) != hipSuccess) return e;
@@ -1462,9 +1453,8 @@ hipError_t upload_topology(DevPlan& d, const Plan& topo, const BoxDev* boxdev, h
     if ((e = up(d.leaf, leaf, s)) != hipSuccess) return e;
     if ((e = up(d.level_cells, topo.cells_by_depth, s)) != hipSuccess) return e;
     if ((e = up(d.loop_cells, loop_cells, s)) != hipSuccess) return e;
-    // split axis per cell: -1 except for the level loop's cells, whose axis
-    // k_cells_level writes at their level of every build
-    if ((e = up(d.cell_axis, sax0, s)) != hipSuccess) return e;
+    if ((e = up(d.loop_tiles, loop_tiles, s)) != hipSuccess) return e;
+    if ((e = d.cell_axis.ensure(loop_cells.size() + 16)) != hipSuccess) return e;
     if ((e = up(d.froots, roots, s)) != hipSuccess) return e;
     if ((e = up(d.box_first, topo.box_first_particle, s)) != hipSuccess) return e;
     if ((e = up(d.walkbox, wb, s)) != hipSuccess) return e;
@@ -1488,8 +1478,6 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
     TRY(d.plist.ensure(n * 12));
     TRY(d.plist_tmp.ensure(n * 12));
     TRY(d.keys_tmp.ensure(n * 24));
-    TRY(d.pc.ensure(n * 4));
-    TRY(d.pc_tmp.ensure(n * 4));
     TRY(d.wcount.ensure((kCtlAt + kCtlWords) * 4));
     TRY(d.rowcnt.ensure((nl + 2) * 4));
     TRY(d.rowcnt_m2l.ensure((nc + 2) * 4));
@@ -1499,9 +1487,8 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
                        d.rowcnt_m2l.as<int32_t>(), (int)nc + 2, d.m2l_row.as<int32_t>(), (int)nc + 1);
     const int key_bits = n <= kKey24Max ? 24 : 32;
     hipLaunchKernelGGL(k_prepare, dim3(grid_of(n)), dim3(256), 0, s, pos, mass, n,
-                       d.box_first.as<int32_t>(), d.item_count.as<int32_t>(), nbox, d.boxes.as<BoxDev>(),
-                       d.wpos.as<double>(), d.keys.as<uint32_t>(), d.plist.as<uint32_t>(), key_bits,
-                       d.pc.as<int32_t>(), d.wcount.as<int>());
+                       d.box_first.as<int32_t>(), nbox, d.boxes.as<BoxDev>(), d.wpos.as<double>(),
+                       d.keys.as<uint32_t>(), d.plist.as<uint32_t>(), key_bits, d.wcount.as<int>());
     TRY(hipGetLastError());
     // the three axis lists are three segments of one sort: by the key,
     // then each run of equal keys by coordinate
@@ -1559,52 +1546,34 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
     TRY(d.flag.ensure(std::max<int64_t>(n * 4, bits_off + (n + 63) / 64 * 8)));
     uint64_t* bits = reinterpret_cast<uint64_t*>(d.flag.as<uint8_t>() + bits_off);
     const int64_t lv_tiles = (n + kLvTile - 1) / kLvTile;
-    TRY(d.lv_first.ensure(nc * 4));
     // per-list tile sums, their scan (large n) and the scan's scratch
     TRY(d.tile_sums.ensure((6 * lv_tiles + sort_tiles(3 * lv_tiles)) * 4 + 16));
     TRY(d.clo.ensure(nc * 24));
     TRY(d.chi.ensure(nc * 24));
-    TRY(d.cell_axis.ensure(nc * 4));
     // the level loop partitions the cells above the fused subtrees
     const int nloop = (int)d.loop_depth_begin.size() - 1;
     for (int dep = 0; dep < nloop; ++dep) {
         const int c0 = d.loop_depth_begin[dep], ncd = d.loop_depth_begin[dep + 1] - c0;
-        hipLaunchKernelGGL(k_cells_level, dim3(1), dim3(kCellsT), 0, s,
-                           d.loop_cells.as<int32_t>() + c0, ncd, d.cell.as<int4>(),
-                           d.cell_aux.as<int4>(), d.plist.as<uint32_t>(), n, d.wpos.as<double>(),
-                           d.clo.as<double>(), d.chi.as<double>(), d.cell_axis.as<int32_t>(),
-                           d.lv_first.as<int32_t>());
-        TRY(hipGetLastError());
-        hipLaunchKernelGGL(k_flag, dim3(grid_of(n)), dim3(256), 0, s, n, d.pc.as<int32_t>(),
-                           d.cell.as<int4>(), d.cell_axis.as<int32_t>(), d.plist.as<uint32_t>(),
-                           d.flag.as<uint8_t>());
+        const LevelCells lv{d.loop_cells.as<int4>() + c0, d.loop_tiles.as<int32_t>() + dep * lv_tiles, ncd,
+                            d.cell_axis.as<int32_t>() + c0};
+        hipLaunchKernelGGL(k_level_flag, dim3(lv_tiles), dim3(kLvThreads), 0, s, n, lv,
+                           d.plist.as<uint32_t>(), d.wpos.as<double>(), d.clo.as<double>(),
+                           d.chi.as<double>(), d.flag.as<uint8_t>());
         hipLaunchKernelGGL(k_pack_marks, dim3(grid_of(n)), dim3(256), 0, s, n,
                            d.flag.as<uint8_t>(), bits);
-        hipLaunchKernelGGL(k_level_sums, dim3(lv_tiles), dim3(kLvThreads), 0, s, n,
-                           d.pc.as<int32_t>(), d.cell_axis.as<int32_t>(), d.cell.as<int4>(),
+        hipLaunchKernelGGL(k_level_sums, dim3(lv_tiles), dim3(kLvThreads), 0, s, n, lv,
                            d.plist.as<uint32_t>(), bits, d.tile_sums.as<uint32_t>(), (int)lv_tiles);
         TRY(hipGetLastError());
-        if (lv_tiles <= kLvSumMax) {
-            hipLaunchKernelGGL(k_level_move<false>, dim3(lv_tiles), dim3(kLvThreads), 0, s, n,
-                               d.pc.as<int32_t>(), d.pc_tmp.as<int32_t>(), d.cell.as<int4>(),
-                               d.cell_aux.as<int4>(), d.cell_axis.as<int32_t>(),
-                               d.plist.as<uint32_t>(), d.plist_tmp.as<uint32_t>(), bits,
-                               d.tile_sums.as<uint32_t>(), nullptr, (int)lv_tiles,
-                               d.lv_first.as<int32_t>());
-        } else {
-            uint32_t* offs = d.tile_sums.as<uint32_t>() + 3 * lv_tiles;
+        uint32_t* offs = d.tile_sums.as<uint32_t>() + 3 * lv_tiles;
+        if (lv_tiles > kLvSumMax)
             TRY(exclusive_scan_i32(d.tile_sums.as<int32_t>(), reinterpret_cast<int32_t*>(offs),
                                    3 * lv_tiles, offs + 3 * lv_tiles, s));
-            hipLaunchKernelGGL(k_level_move<true>, dim3(lv_tiles), dim3(kLvThreads), 0, s, n,
-                               d.pc.as<int32_t>(), d.pc_tmp.as<int32_t>(), d.cell.as<int4>(),
-                               d.cell_aux.as<int4>(), d.cell_axis.as<int32_t>(),
-                               d.plist.as<uint32_t>(), d.plist_tmp.as<uint32_t>(), bits,
-                               d.tile_sums.as<uint32_t>(), offs, (int)lv_tiles,
-                               d.lv_first.as<int32_t>());
-        }
+        hipLaunchKernelGGL(lv_tiles > kLvSumMax ? k_level_move<true> : k_level_move<false>,
+                           dim3(lv_tiles), dim3(kLvThreads), 0, s, n, lv, d.plist.as<uint32_t>(),
+                           d.plist_tmp.as<uint32_t>(), bits, d.tile_sums.as<uint32_t>(), offs,
+                           (int)lv_tiles);
         TRY(hipGetLastError());
         std::swap(d.plist, d.plist_tmp);
-        std::swap(d.pc, d.pc_tmp);
     }
     // the subtrees below, each in one workgroup; leaves into perm
     TRY(d.perm.ensure(n * 4));
