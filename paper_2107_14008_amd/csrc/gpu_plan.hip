@@ -841,19 +841,26 @@ __device__ __forceinline__ uint32_t walk_emit(const WalkOut& o, int2* __restrict
     }
     if (lane == 63) wtot[wave] = x;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t run = 0;
-        for (int w = 0; w < kWalkT / 64; ++w) {
-            const uint64_t tw = wtot[w];
-            wtot[w] = run;
-            run += tw;
+    if (wave == 0) {
+        // the waves' totals scanned across 16 lanes, then lanes 0 to 2 reserve
+        // the group's slots at once: three reservations one after another by
+        // one thread waited for three device-scope atomics
+        const uint64_t tw = lane < kWalkT / 64 ? wtot[lane] : 0ull;
+        uint64_t y = tw;
+        for (int off = 1; off < kWalkT / 64; off <<= 1) {
+            const uint64_t z = __shfl_up(y, off);
+            if (lane >= off) y += z;
         }
-        const uint32_t tc = (uint32_t)(run & 0xffffu), tp = (uint32_t)((run >> 16) & 0xffffu),
-                       tm = (uint32_t)(run >> 32);
-        bbase[0] = (tc != 0 && lch == nullptr) ? atomicAdd(next_count, tc) : 0u;
-        bbase[1] = tp ? atomicAdd(&ctl[0], tp) : 0u;
-        bbase[2] = tm ? atomicAdd(&ctl[1], tm) : 0u;
-        bbase[3] = tc;
+        const uint64_t all = __shfl(y, kWalkT / 64 - 1);
+        if (lane < kWalkT / 64) wtot[lane] = y - tw;
+        const uint32_t tc = (uint32_t)(all & 0xffffu), tp = (uint32_t)((all >> 16) & 0xffffu),
+                       tm = (uint32_t)(all >> 32);
+        if (lane < 3) {
+            const uint32_t add = lane == 0 ? (lch == nullptr ? tc : 0u) : lane == 1 ? tp : tm;
+            uint32_t* at = lane == 0 ? next_count : ctl + (lane - 1);
+            bbase[lane] = add != 0 ? atomicAdd(at, add) : 0u;
+        }
+        if (lane == 3) bbase[3] = tc;
     }
     __syncthreads();
     const uint64_t off = wtot[wave] + x - v;
