@@ -1399,11 +1399,18 @@ hipError_t upload_topology(DevPlan& d, const Plan& topo, const BoxDev* boxdev, h
     std::vector<int32_t> bfc(topo.box_first_cell.begin(), topo.box_first_cell.end());
     d.walk_levels = 0;      // a new shape: size the walk level by level once
 
-    // Subtrees finished by k_orb_fused: the highest cells with at most kFuseM
+    // Subtrees finished by k_orb_fused: the highest cells with at most fuse
     // particles and kFuseC cells (cells are in pre-order, so a subtree is the
     // contiguous id range [c, c + sub[c])).  A leaf (<= 64 particles) always
     // qualifies, so the subtrees cover every leaf; the level loop partitions
-    // the cells above them, all of which split.
+    // the cells above them, all of which split.  fuse is kFuseM where that
+    // gives every CU a subtree, and down to a quarter of it below: with
+    // kFuseM throughout, 32^3 particles were four workgroups of nine levels
+    // at 16 us each; a quarter trades two of the loop's levels (23 us each)
+    // for seven levels at 5 us (whole build, before -> after: 40^3 455 -> 397
+    // us, 64^3 572 -> 536, 100^3 1071 -> 1051; 12^3 to 32^3 within the spread).
+    int fuse = kFuseM;
+    while (fuse > kFuseM / 4 && topo.n / 256 <= fuse / 2) fuse /= 2;
     std::vector<int32_t> sub(nc, 1), deep(nc, 0);
     for (int64_t k = nc - 1; k >= 0; --k) {
         const Cell& c = topo.cells[k];
@@ -1414,7 +1421,7 @@ hipError_t upload_topology(DevPlan& d, const Plan& topo, const BoxDev* boxdev, h
         }
     }
     auto fusable = [&](int64_t k) {
-        return topo.cells[k].count <= kFuseM && sub[k] <= kFuseC;
+        return topo.cells[k].count <= fuse && sub[k] <= kFuseC;
     };
     std::vector<int32_t> roots, split(nc, 0), loop_cells, loop_tiles;
     std::vector<int32_t> loop_begin(1, 0);
