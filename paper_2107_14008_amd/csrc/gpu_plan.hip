@@ -1135,25 +1135,81 @@ __device__ __forceinline__ int pow2_at_least(int n) {
 
 // One wavefront per row of at most kRowShort values; longer rows are listed
 // for k_row_sort_long.
-constexpr int kRowShort = 256;
+constexpr int kRowShort = 1024;
 constexpr int kRowLds = 8192;
 
-__global__ void __launch_bounds__(64)
-k_row_sort_short(const int32_t* __restrict__ row, int32_t* __restrict__ vals,
+// v of lane ^ M.  The masks that stay within 16 lanes are DPP moves (4 in
+// two), so only 16 and 32 cross the LDS unit.
+template <int M>
+__device__ __forceinline__ int32_t lane_xor(int32_t v) {
+    if constexpr (M == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);    // quad 1 0 3 2
+    if constexpr (M == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);    // quad 2 3 0 1
+    if constexpr (M == 4)                                     // half-row mirror (7), quad 3 2 1 0 (3)
+        return __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true), 0x1B,
+                                        0xF, 0xF, true);
+    if constexpr (M == 8) return __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);   // row rotate 8
+    return __shfl_xor(v, M);
+}
+
+// Strides J, J / 2, ..., 1 of bitonic phase K over the 64 R values of a wave,
+// value i = R lane + r in register r.
+template <int R, int K, int J>
+__device__ __forceinline__ void bitonic_strides(int32_t (&v)[R], int lane) {
+    if constexpr (J >= R) {
+        const bool low = ((lane & (J / R)) == 0) == (((R * lane) & K) == 0);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int32_t o = lane_xor<J / R>(v[r]);
+            v[r] = low ? min(v[r], o) : max(v[r], o);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r & J) continue;
+            const bool up = ((R * lane + r) & K) == 0;
+            const int32_t x = v[r], y = v[r | J];
+            v[r] = up ? min(x, y) : max(x, y);
+            v[r | J] = up ? max(x, y) : min(x, y);
+        }
+    }
+    if constexpr (J > 1) bitonic_strides<R, K, J / 2>(v, lane);
+}
+
+template <int R, int K>
+__device__ __forceinline__ void bitonic_phases(int32_t (&v)[R], int lane) {
+    if constexpr (K > 2) bitonic_phases<R, K / 2>(v, lane);
+    bitonic_strides<R, K, K / 2>(v, lane);
+}
+
+template <int R>
+__device__ __forceinline__ void sort_row(int32_t* __restrict__ p, int len, int lane) {
+    int32_t v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = 64 * r + lane < len ? p[64 * r + lane] : INT32_MAX;
+    bitonic_phases<R, 64 * R>(v, lane);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (R * lane + r < len) p[R * lane + r] = v[r];
+}
+
+// The values stay in registers, blocked R to a lane, so of the 36 strides of
+// a 256-value row 15 are within a lane and 18 of the rest are DPP moves; with
+// the row in LDS, each stride was four LDS operations and a barrier.
+__global__ void __launch_bounds__(256)
+k_row_sort_short(const int32_t* __restrict__ row, int nrows, int32_t* __restrict__ vals,
                  int32_t* __restrict__ longs, int32_t* __restrict__ nlong) {
-    __shared__ int32_t b[kRowShort];
-    const int r = blockIdx.x, t = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int r = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (r >= nrows) return;
     const int r0 = row[r], len = row[r + 1] - r0;
     if (len <= 1) return;
-    if (len > kRowShort) {
-        if (t == 0) longs[atomicAdd(nlong, 1)] = r;
-        return;
-    }
-    const int P = pow2_at_least(len);
-    for (int k = t; k < P; k += 64) b[k] = k < len ? vals[r0 + k] : INT32_MAX;
-    __syncthreads();
-    bitonic_sort(b, P, t, 64);
-    for (int k = t; k < len; k += 64) vals[r0 + k] = b[k];
+    int32_t* p = vals + r0;
+    if (len <= 64) return sort_row<1>(p, len, lane);
+    if (len <= 128) return sort_row<2>(p, len, lane);
+    if (len <= 256) return sort_row<4>(p, len, lane);
+    if (len <= 512) return sort_row<8>(p, len, lane);
+    if (len <= kRowShort) return sort_row<16>(p, len, lane);
+    if (lane == 0) longs[atomicAdd(nlong, 1)] = r;
 }
 
 // The listed long rows, one workgroup at a time each: in LDS up to lds_cap
@@ -1839,8 +1895,8 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
                                rl.vals.as<int32_t>());
             // the count of long rows goes in cnt[nrows + 1] (zeroed above)
             int32_t* nlong = cnt + rl.nrows + 1;
-            hipLaunchKernelGGL(k_row_sort_short, dim3(rl.nrows), dim3(64), 0, st,
-                               rl.row.as<int32_t>(), rl.vals.as<int32_t>(),
+            hipLaunchKernelGGL(k_row_sort_short, dim3((rl.nrows + 3) / 4), dim3(256), 0, st,
+                               rl.row.as<int32_t>(), rl.nrows, rl.vals.as<int32_t>(),
                                rl.longs.as<int32_t>(), nlong);
             hipLaunchKernelGGL(k_row_sort_long, dim3(64), dim3(256), 0, st, rl.row.as<int32_t>(),
                                rl.vals.as<int32_t>(), rl.longs.as<int32_t>(), nlong, slot,
