@@ -409,10 +409,7 @@ adj_reduce_kernel(const int4* __restrict__ leaf, const int32_t* __restrict__ lea
     const int4 li = leaf[l];
     if (lane >= li.y) return;
     double g[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int s = leaf_slot[l]; s < leaf_slot[l + 1]; ++s) {
-        const double* p = partial + (size_t)s * 256;
-        for (int c = 0; c < 4; ++c) g[c] += p[64 * c + lane];
-    }
+    sum_slots(partial, leaf_slot[l], leaf_slot[l + 1], lane, g);
     if (far != nullptr) {
         const double4 f = far[li.x + lane];
         g[0] += f.x;

@@ -389,6 +389,35 @@ __device__ __forceinline__ int take_item(ItemCursor& c, int lane, int32_t n_item
     }
 }
 
+// acc[c] += lane's value of component c in item slots [s0, s1), in slot order.
+// B slots' loads are in flight at a time: one after the other, the 40 slots of
+// a 16^3 leaf were 40 memory latencies.
+template <int C, int B>
+__device__ __forceinline__ int sum_slot_blocks(const double* __restrict__ partial, int s, int s1,
+                                               int lane, double (&acc)[C]) {
+    for (; s + B <= s1; s += B) {
+        double v[B][C];
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int c = 0; c < C; ++c) v[b][c] = partial[(size_t)(s + b) * (64 * C) + 64 * c + lane];
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] += v[b][c];
+    }
+    return s;
+}
+
+template <int C>
+__device__ __forceinline__ void sum_slots(const double* __restrict__ partial, int s0, int s1, int lane,
+                                          double (&acc)[C]) {
+    s0 = sum_slot_blocks<C, 8>(partial, s0, s1, lane, acc);
+    s0 = sum_slot_blocks<C, 4>(partial, s0, s1, lane, acc);
+    s0 = sum_slot_blocks<C, 2>(partial, s0, s1, lane, acc);
+    sum_slot_blocks<C, 1>(partial, s0, s1, lane, acc);
+}
+
 // Per-box constants.  The float32 forms work on offsets scaled by sigma
 // (x32 and the per-task centre offsets): sigma = 1, except for the r^2
 // table, where sigma^2 = 2^kR2Emax / r_cut^2 puts the cutoff at

@@ -483,14 +483,16 @@ hipError_t launch_zero_f64(double* p, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-// needM / needL hold 2 n_cells ints each: marks first, then the spread flags.
+// needM / needL hold 2 n_cells ints each, needL right after needM: the spread
+// flags first, then the marks.
 hipError_t launch_far_flags(const FarArgs& a, hipStream_t s) {
     const int64_t nc = a.n_cells;
     int32_t* markM = a.needM + nc;
     int32_t* markL = a.needL + nc;
     const unsigned g = (unsigned)((nc + 255) / 256);
-    hipLaunchKernelGGL(zero_i32_n, dim3(g), dim3(256), 0, s, markM, nc);
-    hipLaunchKernelGGL(zero_i32_n, dim3(g), dim3(256), 0, s, markL, nc);
+    // both marks in one launch, with the flags of needL that lie between them
+    hipLaunchKernelGGL(zero_i32_n, dim3((unsigned)((3 * nc + 255) / 256)), dim3(256), 0, s, markM,
+                       3 * nc);
     hipLaunchKernelGGL(far_mark_kernel, dim3(g), dim3(256), 0, s, a.m2l_row, a.m2l_src, (int)nc, markM,
                        markL);
     hipLaunchKernelGGL(far_spread_kernel, dim3(g), dim3(256), 0, s, a.cell, (int)nc, markM, markL,

@@ -809,25 +809,19 @@ reduce_kernel(const int4* __restrict__ leaf, const int32_t* __restrict__ leaf_sl
     if (l >= n_leaves) return;
     const int4 li = leaf[l];
     if (lane >= li.y) return;
-    const int s0 = leaf_slot[l], s1 = leaf_slot[l + 1];
-    double ax = 0.0, ay = 0.0, az = 0.0;
-    for (int s = s0; s < s1; ++s) {
-        const double* p = partial + (size_t)s * 192;
-        ax += p[lane];
-        ay += p[64 + lane];
-        az += p[128 + lane];
-    }
+    double f[3] = {0.0, 0.0, 0.0};
+    sum_slots(partial, leaf_slot[l], leaf_slot[l + 1], lane, f);
     const int k = li.x + lane;
     if (far != nullptr && needL[li.w]) {   // L2P wrote only these leaves
-        ax += far[3 * (size_t)k];
-        ay += far[3 * (size_t)k + 1];
-        az += far[3 * (size_t)k + 2];
+        f[0] += far[3 * (size_t)k];
+        f[1] += far[3 * (size_t)k + 1];
+        f[2] += far[3 * (size_t)k + 2];
     }
     const double G = boxes[li.z].G;
     const int o = perm[k];
-    out[3 * (size_t)o] = G * ax;
-    out[3 * (size_t)o + 1] = G * ay;
-    out[3 * (size_t)o + 2] = G * az;
+    out[3 * (size_t)o] = G * f[0];
+    out[3 * (size_t)o + 1] = G * f[1];
+    out[3 * (size_t)o + 2] = G * f[2];
 }
 
 // One wavefront per leaf: particles into leaf order, wrapped, as float64
