@@ -224,25 +224,33 @@ __device__ __forceinline__ bool level_cell(const LevelCells& lv, int64_t i, int&
 // cell marks the first floor(count / 2) positions of its range in every list
 // and nothing else is marked, so the marks before a cell's first position are
 // the same in the three lists and known from the shape.  k_level_flag gives
-// every particle its mark, k_level_sums counts each tile's marks per list, and
+// every particle its mark, k_level_sums looks the positions' marks up, keeps
+// them as bits in list order and counts each tile's per list, and
 // k_level_move counts them before every position (the tiles before its own,
-// summed where they are needed, + the in-tile scan) and from the difference
-// places the position.
+// summed where they are needed, + the tile's words) and from the difference
+// places the position.  The look-ups are random reads at a line per lane, so
+// they are made once: with k_level_move looking them up again it took 189 us
+// a level at 256^3 and 24 at 128^3, now 79 and 14.5 (read and write of the
+// lists: 5.1 TB/s).
 constexpr int kLvThreads = 256;
 constexpr int kLvRounds = 4;
 constexpr int kLvTile = kLvThreads * kLvRounds;   // 1024 positions of each list
+constexpr int kLvWords = kLvTile / 64;            // mark words of each list's tile
+static_assert(3 * kLvWords <= 64, "one wavefront scans the words");
 
 // Per tile: the bounds of the cells it meets from the ends of their sorted
 // ranges (six lanes of every wave, two dependent loads; one workgroup for the
 // level's cells took a launch of its own), their split axes, and the left
 // marks of its positions in the split axis's list, as bytes indexed by
-// particle (a byte store needs no atomic); k_pack_marks then packs them into
-// bits for the level's random reads.  The tile that holds a cell's first
-// position writes its bounds and axis.
+// particle (a byte store needs no atomic).  A left mark is the value `gen`,
+// another one at each level, so only the left half is written (scattered: 171
+// us a level at 256^3 with both halves, now 112), but for the first level
+// (`all`), which gives every particle of the loop's cells a value.  The tile
+// that holds a cell's first position writes its bounds and axis.
 __global__ void __launch_bounds__(kLvThreads)
 k_level_flag(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
              const double* __restrict__ wpos, double* __restrict__ clo, double* __restrict__ chi,
-             uint8_t* __restrict__ flag) {
+             uint8_t* __restrict__ flag, int gen, bool all) {
     const int64_t base = (int64_t)blockIdx.x * kLvTile, last = min(n, base + kLvTile);
     const int t = threadIdx.x, lane = t & 63;
     for (int c = lv.tile[blockIdx.x]; c < lv.count; ++c) {
@@ -266,60 +274,98 @@ k_level_flag(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
             chi[3 * (size_t)ci.z + t] = t == 0 ? hi[0] : t == 1 ? hi[1] : hi[2];
             if (t == 0) lv.axis[c] = axis;
         }
-        const int64_t i1 = min(last, (int64_t)ci.x + ci.y), half = (int64_t)ci.x + ci.y / 2;
+        const int64_t half = (int64_t)ci.x + ci.y / 2;
+        const int64_t i1 = min(last, all ? (int64_t)ci.x + ci.y : half);
         for (int64_t i = max(base, (int64_t)ci.x) + t; i < i1; i += kLvThreads)
-            flag[plist[axis * n + i]] = i < half ? 1 : 0;
+            flag[plist[axis * n + i]] = (uint8_t)(i < half ? gen : 0);
     }
 }
 
-// The particles' left marks as bits: k_level_flag writes one byte per particle of
-// a splitting cell (scattered by particle), and this packs the bytes of
-// particles [64 w, 64 w + 64) into word w (one wavefront per word).  The
-// level's random reads by particle then fall on n / 8 bytes, which stay in
-// an XCD's 4 MB L2 up to tens of millions of particles; the bytes outgrow
-// it from about four million.
-__global__ void k_pack_marks(int64_t n, const uint8_t* __restrict__ flag,
+// The particles' left marks as bits, particles [64 w, 64 w + 64) in word w, for
+// k_level_sums' random reads: n / 8 bytes stay in an XCD's 4 MB L2 up to tens
+// of millions of particles.  The marks as bytes stay there, beside the lists
+// that stream through, up to about kLvByteMax of them, and below that the
+// launch costs what it gives or more (whole build with / without it: 128^3
+// 1424 / 1406 us, 144^3 2170 / 2178, 160^3 2485 / 2520).
+constexpr int64_t kLvByteMax = int64_t(3) << 20;
+
+__global__ void k_pack_marks(int64_t n, const uint8_t* __restrict__ flag, int gen,
                              uint64_t* __restrict__ bits) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t b = __ballot(i < n && flag[i] != 0);
+    const uint64_t b = __ballot(i < n && flag[i] == gen);
     if ((threadIdx.x & 63) == 0 && i < n) bits[i >> 6] = b;
 }
 
-__device__ __forceinline__ uint32_t mark_bit(const uint64_t* __restrict__ bits, uint32_t p) {
-    return (uint32_t)(bits[p >> 6] >> (p & 63u)) & 1u;
-}
-
 // On the split axis's own list the mark follows from the position alone, so
-// only the two other lists read the particle's bit.
-// tile_sums[a ntiles + b]: the marks of list a in tile b.
+// only the two other lists read the particle's mark (PACKED: a bit of `bits`,
+// else a byte of `flag`).  marks[a nwords + w]: the marks of positions [64 w,
+// 64 w + 64) of list a; tile_sums[a ntiles + b]: the marks of list a in tile b.
+// 108 us a level at 256^3 (140 with a chain of four loads per position), of
+// which the two look-ups per position, a line per lane, are at least 55.
+template <bool PACKED>
 __global__ void __launch_bounds__(kLvThreads)
 k_level_sums(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
-             const uint64_t* __restrict__ bits, uint32_t* __restrict__ tile_sums, int ntiles) {
-    __shared__ uint64_t wsum[kLvThreads / 64];
+             const uint8_t* __restrict__ flag, int gen, const uint64_t* __restrict__ bits,
+             uint64_t* __restrict__ marks, int64_t nwords, uint32_t* __restrict__ tile_sums,
+             int ntiles) {
+    __shared__ uint32_t wsum[3][kLvThreads / 64];
     const int64_t base = (int64_t)blockIdx.x * kLvTile;
-    // the three counts packed 21 bits apart (each at most kLvTile)
-    uint64_t cnt = 0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t cnt[3] = {0u, 0u, 0u};
+    auto mark_of = [&](uint32_t p) -> bool {
+        return PACKED ? (bits[p >> 6] >> (p & 63u)) & 1u : flag[p] == gen;
+    };
     int c = lv.tile[blockIdx.x];
+    const int4 c0 = c < lv.count ? lv.cells[c] : make_int4(0, 0, 0, 0);
+    bool m[kLvRounds][3];
+    if (c0.x <= base && (int64_t)c0.x + c0.y >= base + kLvTile) {
+        // the tile lies in one cell, as most do (the loop's cells are several
+        // tiles long): all its look-ups are in flight at a time
+        const int ax = lv.axis[c], u = ax == 0 ? 1 : 0, v = ax == 2 ? 1 : 2;
+        uint32_t p[kLvRounds][2];
+#pragma unroll
+        for (int r = 0; r < kLvRounds; ++r) {
+            const int64_t i = base + r * kLvThreads + threadIdx.x;
+            p[r][0] = plist[(int64_t)u * n + i];
+            p[r][1] = plist[(int64_t)v * n + i];
+        }
+#pragma unroll
+        for (int r = 0; r < kLvRounds; ++r) {
+            const bool own = base + r * kLvThreads + threadIdx.x - c0.x < c0.y / 2;
+            const bool mu = mark_of(p[r][0]), mv = mark_of(p[r][1]);
+            m[r][0] = ax == 0 ? own : mu;
+            m[r][1] = ax == 0 ? mu : ax == 1 ? own : mv;
+            m[r][2] = ax == 2 ? own : mv;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < kLvRounds; ++r) {
+            const int64_t i = base + r * kLvThreads + threadIdx.x;
+            m[r][0] = m[r][1] = m[r][2] = false;
+            int4 ci;
+            if (i >= n || !level_cell(lv, i, c, ci)) continue;
+            const int ax = lv.axis[c];
+            for (int a = 0; a < 3; ++a)
+                m[r][a] = a == ax ? i - ci.x < ci.y / 2 : mark_of(plist[(int64_t)a * n + i]);
+        }
+    }
 #pragma unroll
     for (int r = 0; r < kLvRounds; ++r) {
         const int64_t i = base + r * kLvThreads + threadIdx.x;
-        int4 ci;
-        if (i >= n || !level_cell(lv, i, c, ci)) continue;
-        const int ax = lv.axis[c];
-        const uint32_t own = (i - ci.x < ci.y / 2) ? 1u : 0u;
+        uint64_t word[3];
         for (int a = 0; a < 3; ++a) {
-            const uint32_t m = a == ax ? own : mark_bit(bits, plist[(int64_t)a * n + i]);
-            cnt += (uint64_t)m << (21 * a);
+            word[a] = __ballot(m[r][a]);
+            cnt[a] += (uint32_t)__popcll(word[a]);
         }
+        if (lane < 3 && i - lane < n)
+            marks[lane * nwords + ((i - lane) >> 6)] = lane == 0 ? word[0] : lane == 1 ? word[1] : word[2];
     }
-    for (int off = 32; off > 0; off >>= 1) cnt += __shfl_down(cnt, off);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = cnt;
+    if (lane < 3) wsum[lane][wave] = lane == 0 ? cnt[0] : lane == 1 ? cnt[1] : cnt[2];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t t = 0;
-        for (int w = 0; w < kLvThreads / 64; ++w) t += wsum[w];
-        for (int a = 0; a < 3; ++a)
-            tile_sums[(size_t)a * ntiles + blockIdx.x] = (uint32_t)(t >> (21 * a)) & 0x1fffffu;
+    if (threadIdx.x < 3) {
+        uint32_t t = 0;
+        for (int w = 0; w < kLvThreads / 64; ++w) t += wsum[threadIdx.x][w];
+        tile_sums[(size_t)threadIdx.x * ntiles + blockIdx.x] = t;
     }
 }
 
@@ -332,15 +378,28 @@ constexpr int kLvSumMax = 2048;
 template <bool SCANNED>
 __global__ void __launch_bounds__(kLvThreads)
 k_level_move(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
-             uint32_t* __restrict__ pout, const uint64_t* __restrict__ bits,
+             uint32_t* __restrict__ pout, const uint64_t* __restrict__ marks, int64_t nwords,
              const uint32_t* __restrict__ tile_sums, const uint32_t* __restrict__ offs,
              int ntiles) {
-    __shared__ uint8_t mk[3][kLvTile];
-    __shared__ uint16_t pre[3][kLvTile];
-    __shared__ uint64_t wsum[kLvThreads / 64];
+    __shared__ uint64_t word[3][kLvWords];
+    __shared__ uint32_t pre[3][kLvWords];       // marks of the tile before the word
     __shared__ uint32_t woff[3][kLvThreads / 64];
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kLvTile;
+    if (t < 3 * kLvWords) {
+        const int a = t / kLvWords, q = t % kLvWords;
+        const int64_t w = base / 64 + q;
+        const uint64_t v = w < nwords ? marks[a * nwords + w] : 0u;
+        const uint32_t own = (uint32_t)__popcll(v);
+        uint32_t x = own;
+        for (int off = 1; off < kLvWords; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off, kLvWords);
+            if (q >= off) x += y;
+        }
+        word[a][q] = v;
+        pre[a][q] = x - own;
+    }
     if (!SCANNED) {
         // this tile's offsets: the counts of the tiles before it, per list
         for (int a = 0; a < 3; ++a) {
@@ -350,48 +409,11 @@ k_level_move(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
             if (lane == 0) woff[a][wave] = c;
         }
     }
-    const int64_t base = (int64_t)blockIdx.x * kLvTile;
     uint32_t pv[kLvRounds][3];
-    int4 cv[kLvRounds];     // the position's cell; count 0: none splits here
-    int c = lv.tile[blockIdx.x];
 #pragma unroll
     for (int r = 0; r < kLvRounds; ++r) {
         const int64_t i = base + r * kLvThreads + t;
-        uint32_t m[3] = {0u, 0u, 0u};
-        cv[r] = make_int4(0, 0, 0, 0);
-        pv[r][0] = pv[r][1] = pv[r][2] = 0u;
-        if (i < n) {
-            for (int a = 0; a < 3; ++a) pv[r][a] = plist[(int64_t)a * n + i];
-            int4 ci;
-            if (level_cell(lv, i, c, ci)) {
-                cv[r] = ci;
-                const int ax = lv.axis[c];
-                const uint32_t own = (i - ci.x < ci.y / 2) ? 1u : 0u;
-                for (int a = 0; a < 3; ++a) m[a] = a == ax ? own : mark_bit(bits, pv[r][a]);
-            }
-        }
-        for (int a = 0; a < 3; ++a) mk[a][r * kLvThreads + t] = (uint8_t)m[a];
-    }
-    __syncthreads();
-    // in-tile exclusive prefix per list: thread t owns positions
-    // [kLvRounds t, kLvRounds (t + 1)); the three counts packed 21 bits apart
-    uint64_t own = 0;
-    for (int j = 0; j < kLvRounds; ++j)
-        for (int a = 0; a < 3; ++a) own += (uint64_t)mk[a][kLvRounds * t + j] << (21 * a);
-    uint64_t x = own;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint64_t y = __shfl_up(x, off);
-        if (lane >= off) x += y;
-    }
-    if (lane == 63) wsum[wave] = x;
-    __syncthreads();
-    uint64_t run = x - own;
-    for (int w = 0; w < wave; ++w) run += wsum[w];
-    for (int j = 0; j < kLvRounds; ++j) {
-        for (int a = 0; a < 3; ++a) {
-            pre[a][kLvRounds * t + j] = (uint16_t)((run >> (21 * a)) & 0x1fffffu);
-            run += (uint64_t)mk[a][kLvRounds * t + j] << (21 * a);
-        }
+        for (int a = 0; a < 3; ++a) pv[r][a] = i < n ? plist[(int64_t)a * n + i] : 0u;
     }
     __syncthreads();
     uint32_t toff[3];
@@ -403,21 +425,24 @@ k_level_move(int64_t n, LevelCells lv, const uint32_t* __restrict__ plist,
             for (int w = 0; w < kLvThreads / 64; ++w) toff[a] += woff[a][w];
         }
     }
+    int c = lv.tile[blockIdx.x];
 #pragma unroll
     for (int r = 0; r < kLvRounds; ++r) {
         const int64_t i = base + r * kLvThreads + t;
         if (i >= n) continue;
-        const int4 ci = cv[r];
-        if (ci.y == 0) {
+        int4 ci;
+        if (!level_cell(lv, i, c, ci)) {        // no cell splits here
             for (int a = 0; a < 3; ++a) pout[(int64_t)a * n + i] = pv[r][a];
             continue;
         }
         const int64_t first = ci.x, nl = ci.y / 2;
         const int64_t pf = (uint32_t)ci.w;
+        const int q = r * (kLvThreads / 64) + wave;
         for (int a = 0; a < 3; ++a) {
-            const int j = r * kLvThreads + t;
-            const int64_t lr = (int64_t)(toff[a] + pre[a][j]) - pf;
-            const int64_t pos = mk[a][j] ? first + lr : first + nl + (i - first - lr);
+            const uint64_t v = word[a][q];
+            const uint32_t below = (uint32_t)__popcll(v & ((1ull << lane) - 1));
+            const int64_t lr = (int64_t)(toff[a] + pre[a][q] + below) - pf;
+            const int64_t pos = (v >> lane) & 1 ? first + lr : first + nl + (i - first - lr);
             pout[(int64_t)a * n + pos] = pv[r][a];
         }
     }
@@ -1610,11 +1635,13 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
 
     clk.lap("sort");
     // ---- ORB levels
-    // mark bytes at 0, mark bits at bits_off; k_orb_fused reuses the buffer
-    // for n int32
-    const int64_t bits_off = (n + 255) / 256 * 256;
-    TRY(d.flag.ensure(std::max<int64_t>(n * 4, bits_off + (n + 63) / 64 * 8)));
+    // mark bytes at 0, then the particles' mark bits, then the lists' mark
+    // words; k_orb_fused reuses the buffer for n int32
+    const int64_t bits_off = (n + 255) / 256 * 256, nwords = (n + 63) / 64;
+    TRY(d.flag.ensure(std::max<int64_t>(n * 4, bits_off + 4 * nwords * 8)));
     uint64_t* bits = reinterpret_cast<uint64_t*>(d.flag.as<uint8_t>() + bits_off);
+    uint64_t* marks = bits + nwords;
+    const bool packed = n > kLvByteMax;
     const int64_t lv_tiles = (n + kLvTile - 1) / kLvTile;
     // per-list tile sums, their scan (large n) and the scan's scratch
     TRY(d.tile_sums.ensure((6 * lv_tiles + sort_tiles(3 * lv_tiles)) * 4 + 16));
@@ -1628,11 +1655,14 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
                             d.cell_axis.as<int32_t>() + c0};
         hipLaunchKernelGGL(k_level_flag, dim3(lv_tiles), dim3(kLvThreads), 0, s, n, lv,
                            d.plist.as<uint32_t>(), d.wpos.as<double>(), d.clo.as<double>(),
-                           d.chi.as<double>(), d.flag.as<uint8_t>());
-        hipLaunchKernelGGL(k_pack_marks, dim3(grid_of(n)), dim3(256), 0, s, n,
-                           d.flag.as<uint8_t>(), bits);
-        hipLaunchKernelGGL(k_level_sums, dim3(lv_tiles), dim3(kLvThreads), 0, s, n, lv,
-                           d.plist.as<uint32_t>(), bits, d.tile_sums.as<uint32_t>(), (int)lv_tiles);
+                           d.chi.as<double>(), d.flag.as<uint8_t>(), dep + 1, dep == 0);
+        if (packed)
+            hipLaunchKernelGGL(k_pack_marks, dim3(grid_of(n)), dim3(256), 0, s, n,
+                               d.flag.as<uint8_t>(), dep + 1, bits);
+        hipLaunchKernelGGL(packed ? k_level_sums<true> : k_level_sums<false>, dim3(lv_tiles),
+                           dim3(kLvThreads), 0, s, n, lv, d.plist.as<uint32_t>(),
+                           d.flag.as<uint8_t>(), dep + 1, bits, marks, nwords,
+                           d.tile_sums.as<uint32_t>(), (int)lv_tiles);
         TRY(hipGetLastError());
         uint32_t* offs = d.tile_sums.as<uint32_t>() + 3 * lv_tiles;
         if (lv_tiles > kLvSumMax)
@@ -1640,8 +1670,8 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
                                    3 * lv_tiles, offs + 3 * lv_tiles, s));
         hipLaunchKernelGGL(lv_tiles > kLvSumMax ? k_level_move<true> : k_level_move<false>,
                            dim3(lv_tiles), dim3(kLvThreads), 0, s, n, lv, d.plist.as<uint32_t>(),
-                           d.plist_tmp.as<uint32_t>(), bits, d.tile_sums.as<uint32_t>(), offs,
-                           (int)lv_tiles);
+                           d.plist_tmp.as<uint32_t>(), marks, nwords, d.tile_sums.as<uint32_t>(),
+                           offs, (int)lv_tiles);
         TRY(hipGetLastError());
         std::swap(d.plist, d.plist_tmp);
     }
