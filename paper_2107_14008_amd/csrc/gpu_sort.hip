@@ -9,12 +9,15 @@
 // Per pass: (1) per-tile digit histogram in LDS, stored [segment][digit][tile];
 // (2) an exclusive scan of each row of tiles, one workgroup per row, and the
 // row's total; (3) scatter: the 256 row totals of the segment, scanned by
-// each workgroup, give the digits' starts; inside a tile the 256 elements of
-// a round are ranked per digit with wavefront ballots (eight ballots give
-// each lane the mask of lanes holding its digit) and a running per-digit
-// count in LDS, so the order of equal digits is kept (stable), which makes
-// the sort stable across passes; the tile is ordered in LDS and written out in
-// runs.  Up to kDirectTiles tiles per segment the scatter adds up its row of
+// each workgroup, give the digits' starts; inside a tile each wavefront takes
+// 64 R consecutive elements, loaded at once, and ranks them 64 at a time per
+// digit with ballots (eight ballots give each lane the mask of lanes holding
+// its digit) and a running per-digit count of its own in LDS, so the order of
+// equal digits is kept (stable), which makes the sort stable across passes;
+// the tile is ordered in LDS and written out in runs.  With the four
+// wavefronts sharing each round's 256 elements, a round was three barriers and
+// a load behind them: a scatter of 3 x 128^3 pairs 46 us, now 36; 3 x 256^3
+// 368, now 261 (the reads and writes alone 175).  Up to kDirectTiles tiles per segment the scatter adds up its row of
 // the histogram itself and (2) is left out (12 us less per build at 4,096
 // particles; at 262,144, 256 tiles, its serial sums would cost more than the
 // launch).
@@ -63,9 +66,16 @@ rs_hist(const K* __restrict__ keys, int64_t n, int shift, uint32_t* __restrict__
     h[threadIdx.x] = 0;
     __syncthreads();
     const TileRange tr = tile_range<R>(n, tiles);
+    K k[R];
+#pragma unroll
     for (int r = 0; r < R; ++r) {
         const int64_t i = tr.begin + r * kThreads + threadIdx.x;
-        if (i < tr.end) atomicAdd(&h[(keys[i] >> shift) & 255u], 1u);
+        k[r] = i < tr.end ? keys[i] : K(0);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = tr.begin + r * kThreads + threadIdx.x;
+        if (i < tr.end) atomicAdd(&h[(k[r] >> shift) & 255u], 1u);
     }
     __syncthreads();
     hist[tr.col + (size_t)threadIdx.x * tiles] = h[threadIdx.x];
@@ -145,11 +155,19 @@ rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
     __shared__ uint32_t vs[VALS ? kThreads * R : 1];
     __shared__ uint32_t start[256];     // digit start inside the tile
     __shared__ uint32_t goff[256];      // digit start in the output
-    __shared__ uint32_t run[256];       // elements of each digit placed so far
-    __shared__ uint32_t wc[kThreads / 64][256];
+    __shared__ uint32_t wc[kThreads / 64][256];   // per wave: elements of each digit
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
     const TileRange tr = tile_range<R>(n, tiles);
+    const int64_t w0 = tr.begin + (int64_t)wave * (64 * R) + lane;
+    K key[R];
+    uint32_t val[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = w0 + 64 * r;
+        key[r] = i < tr.end ? kin[i] : K(0);
+        if (VALS) val[r] = i < tr.end ? vin[i] : 0u;
+    }
     // exclusive scans over the digits of the tile's counts (start) and of the
     // segment's (one wave scans 4 digits per lane); goff: the digit's total in
     // the segment first, its start in the output for this tile in the end
@@ -174,7 +192,6 @@ rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
         }
         start[t] = c;
         goff[t] = all;
-        run[t] = 0;
         for (int w = 0; w < kThreads / 64; ++w) wc[w][t] = 0;
     }
     __syncthreads();
@@ -198,49 +215,50 @@ rs_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
     }
     __syncthreads();
     goff[t] += mine + (uint32_t)((int64_t)(blockIdx.x / tiles) * n);
-    // (read again only after the barriers of the rounds below)
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    // the ranks among the wave's elements of the same digit
+    const uint64_t below = (1ull << lane) - 1;
+    uint32_t rank[R];
+#pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int64_t i = tr.begin + r * kThreads + t;
-        const bool valid = i < tr.end;
-        K key = 0;
-        uint32_t val = 0;
-        uint32_t d = 0;
-        if (valid) {
-            key = kin[i];
-            if (VALS) val = vin[i];
-            d = (uint32_t)(key >> shift) & 255u;
-        }
+        const bool valid = w0 + 64 * r < tr.end;
+        const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
         uint64_t m = __ballot(valid);
         for (int b = 0; b < 8; ++b) {
             const bool bit = (d >> b) & 1u;
             const uint64_t bb = __ballot(bit);
             m &= bit ? bb : ~bb;
         }
-        const uint32_t rank = (uint32_t)__popcll(m & below);
-        if (valid && rank == 0) wc[wave][d] = (uint32_t)__popcll(m);
-        __syncthreads();
-        if (valid) {
-            uint32_t pos = start[d] + run[d] + rank;
-            for (int w = 0; w < wave; ++w) pos += wc[w][d];
-            ks[pos] = key;
-            if (VALS) vs[pos] = val;
-        }
-        __syncthreads();
-        uint32_t add = 0;
-        for (int w = 0; w < kThreads / 64; ++w) {
-            add += wc[w][t];
-            wc[w][t] = 0;
-        }
-        run[t] += add;
-        __syncthreads();
+        const uint32_t first = (uint32_t)__popcll(m & below), had = wc[wave][d];
+        rank[r] = had + first;
+        // every lane has read the count before the first of them adds to it
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (valid && first == 0) wc[wave][d] = had + (uint32_t)__popcll(m);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
+    __syncthreads();
+    {   // each wave's start of digit t in the tile
+        uint32_t at = start[t];
+        for (int w = 0; w < kThreads / 64; ++w) {
+            const uint32_t c = wc[w][t];
+            wc[w][t] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (w0 + 64 * r >= tr.end) continue;
+        const uint32_t pos = wc[wave][(uint32_t)(key[r] >> shift) & 255u] + rank[r];
+        ks[pos] = key[r];
+        if (VALS) vs[pos] = val[r];
+    }
+    __syncthreads();
     const int len = (int)(tr.end - tr.begin);
     for (int p = t; p < len; p += kThreads) {
-        const K key = ks[p];
-        const uint32_t d = (uint32_t)(key >> shift) & 255u;
+        const K k = ks[p];
+        const uint32_t d = (uint32_t)(k >> shift) & 255u;
         const uint32_t o = goff[d] + (uint32_t)p - start[d];
-        kout[o] = key;
+        kout[o] = k;
         if (VALS) vout[o] = vs[p];
     }
 }
