@@ -834,20 +834,32 @@ k_walk(const int2* __restrict__ front, int nf, int2* __restrict__ next,
 // One level of the walk with the frontier size read on the device (no host
 // round trip between levels).  Capacities are checked; an overflow is
 // reported and the host then redoes the walk level by level.  The appends
-// are aggregated per workgroup (one atomic per counter per 1024 pairs):
+// are aggregated per workgroup (one atomic per counter per group of pairs):
 // all workgroups add to the same three counters, and at one atomic per
 // wavefront those additions, serialised at one address, took most of a
 // level's time.
 // ctl: [0] p2p total, [1] m2l total, [2] overflow flag, [3] largest frontier;
 // sizes[it] = frontier size of level it.
 constexpr int kWalkT = 1024;
-// frontiers up to this size go to the one-workgroup top of the walk
-constexpr uint32_t kWalkTopMax = 4 * kWalkT;
+// Frontiers of up to kWalkNarrowMax pairs are walked by smaller workgroups: a
+// thread reads two 80-byte cells of its own, a line at a time, so 1024 pairs on
+// one CU are 4 us of address work, and a few thousand pairs were on a few of
+// the CUs.  Walk of 64^3 142 -> 105 us, 128^3 279 -> 255; 64 and 128 threads
+// were slower at 64^3 (126, 122), and beyond, the groups' additions to the
+// same three counters cost more than that (128^3 with 256 throughout: 368).
+constexpr int kWalkNarrow = 256;
+constexpr int64_t kWalkNarrowMax = 65536;
+constexpr int kWalkThreads = 512 * 1024;   // of a launch, at most
+// frontiers up to this size go to the one-workgroup top of the walk: as many as
+// stay in its LDS (walk of 16^3 / 64^3 / 128^3 with 256 43 / 112 / 264 us, 1024
+// 38 / 105 / 255, 4096 47 / 113 / 256)
+constexpr uint32_t kWalkTopMax = kWalkT;
 
 // Appends one group's outputs (a WalkOut per thread of the workgroup): the
 // keys to the key arrays and the child pairs to `next` at slots reserved
 // from *next_count, or, with `lch`, to that workgroup-local array from 0.
 // One atomic per counter per group.  Returns the group's child count.
+template <int T>
 __device__ __forceinline__ uint32_t walk_emit(const WalkOut& o, int2* __restrict__ next,
                                               uint32_t* __restrict__ next_count,
                                               uint32_t cap_front, int2* lch,
@@ -870,14 +882,14 @@ __device__ __forceinline__ uint32_t walk_emit(const WalkOut& o, int2* __restrict
         // the waves' totals scanned across 16 lanes, then lanes 0 to 2 reserve
         // the group's slots at once: three reservations one after another by
         // one thread waited for three device-scope atomics
-        const uint64_t tw = lane < kWalkT / 64 ? wtot[lane] : 0ull;
+        const uint64_t tw = lane < T / 64 ? wtot[lane] : 0ull;
         uint64_t y = tw;
-        for (int off = 1; off < kWalkT / 64; off <<= 1) {
+        for (int off = 1; off < T / 64; off <<= 1) {
             const uint64_t z = __shfl_up(y, off);
             if (lane >= off) y += z;
         }
-        const uint64_t all = __shfl(y, kWalkT / 64 - 1);
-        if (lane < kWalkT / 64) wtot[lane] = y - tw;
+        const uint64_t all = __shfl(y, T / 64 - 1);
+        if (lane < T / 64) wtot[lane] = y - tw;
         const uint32_t tc = (uint32_t)(all & 0xffffu), tp = (uint32_t)((all >> 16) & 0xffffu),
                        tm = (uint32_t)(all >> 32);
         if (lane < 3) {
@@ -920,6 +932,7 @@ __device__ __forceinline__ uint32_t walk_emit(const WalkOut& o, int2* __restrict
 
 // One level's share of workgroup `blk` of `nblk` (nf pairs in front).
 // Returns false when the frontier is beyond its capacity.
+template <int T>
 __device__ __forceinline__ bool walk_level(const int2* __restrict__ front, int2* __restrict__ next,
                                            int it, uint32_t nf, uint32_t blk, uint32_t nblk,
                                            uint32_t* __restrict__ sizes, uint32_t* __restrict__ ctl,
@@ -935,7 +948,7 @@ __device__ __forceinline__ bool walk_level(const int2* __restrict__ front, int2*
         const uint32_t k = base + threadIdx.x;
         WalkOut o{0u, 0u, 0u, {}, {0ull, 0ull}};
         if (k < nf) walk_classify(front[k], wbox, wcell, ks, o);
-        (void)walk_emit(o, next, &sizes[it + 1], cap_front, nullptr, ctl, cap_p2p, cap_m2l,
+        (void)walk_emit<T>(o, next, &sizes[it + 1], cap_front, nullptr, ctl, cap_p2p, cap_m2l,
                         p2p_keys, m2l_keys, wtot, bbase);
     }
     if (blk == 0 && threadIdx.x == 0) atomicMax(&ctl[3], nf);
@@ -952,6 +965,7 @@ __device__ __forceinline__ bool walk_level(const int2* __restrict__ front, int2*
 // Two levels per launch took the 128^3 walk from 0.55 to 0.33 ms; three
 // took 0.37 ms (the deeper a workgroup's subtree, the more the workgroups'
 // shares differ).
+template <int T>
 __device__ __forceinline__ void walk_two(const int2* __restrict__ front, int2* __restrict__ next,
                                          int it, uint32_t nf, uint32_t blk, uint32_t nblk,
                                          uint32_t* __restrict__ sizes, uint32_t* __restrict__ ctl,
@@ -966,14 +980,14 @@ __device__ __forceinline__ void walk_two(const int2* __restrict__ front, int2* _
         const uint32_t k = base + threadIdx.x;
         WalkOut o{0u, 0u, 0u, {}, {0ull, 0ull}};
         if (k < nf) walk_classify(front[k], wbox, wcell, ks, o);
-        const uint32_t n1 = walk_emit(o, nullptr, nullptr, 0u, lch, ctl, cap_p2p, cap_m2l,
+        const uint32_t n1 = walk_emit<T>(o, nullptr, nullptr, 0u, lch, ctl, cap_p2p, cap_m2l,
                                       p2p_keys, m2l_keys, wtot, bbase);
         if (threadIdx.x == 0 && n1 != 0) atomicAdd(&sizes[it + 1], n1);
         for (uint32_t r = 0; r < n1; r += blockDim.x) {
             const uint32_t j = r + threadIdx.x;
             WalkOut o2{0u, 0u, 0u, {}, {0ull, 0ull}};
             if (j < n1) walk_classify(lch[j], wbox, wcell, ks, o2);
-            (void)walk_emit(o2, next, &sizes[it + 2], cap_front, nullptr, ctl, cap_p2p, cap_m2l,
+            (void)walk_emit<T>(o2, next, &sizes[it + 2], cap_front, nullptr, ctl, cap_p2p, cap_m2l,
                             p2p_keys, m2l_keys, wtot, bbase);
         }
     }
@@ -981,18 +995,19 @@ __device__ __forceinline__ void walk_two(const int2* __restrict__ front, int2* _
 }
 
 // Levels it and it + 1, the frontier size read on the device.
-__global__ void __launch_bounds__(kWalkT)
+template <int T>
+__global__ void __launch_bounds__(T)
 k_walk_multi(const int2* __restrict__ front, int2* __restrict__ next, int it,
              uint32_t* __restrict__ sizes, uint32_t* __restrict__ ctl, uint32_t cap_front,
              uint32_t cap_p2p, uint32_t cap_m2l, const WalkBox* __restrict__ wbox,
              const WalkCell* __restrict__ wcell, int2 ks, uint64_t* __restrict__ p2p_keys,
              uint64_t* __restrict__ m2l_keys) {
-    __shared__ uint64_t wtot[kWalkT / 64];
+    __shared__ uint64_t wtot[T / 64];
     __shared__ uint32_t bbase[4];
-    __shared__ int2 lch[4 * kWalkT];
+    __shared__ int2 lch[4 * T];
     const uint32_t nf = sizes[it];
     if (nf > cap_front) return;
-    walk_two(front, next, it, nf, blockIdx.x, gridDim.x, sizes, ctl, cap_front, cap_p2p, cap_m2l,
+    walk_two<T>(front, next, it, nf, blockIdx.x, gridDim.x, sizes, ctl, cap_front, cap_p2p, cap_m2l,
              wbox, wcell, ks, p2p_keys, m2l_keys, wtot, bbase, lch);
 }
 
@@ -1003,10 +1018,14 @@ constexpr int walk_top_steps(int levels) { return levels / 2 + (levels & 1); }
 
 // The first frontier (each box's root against itself with the zero shift and
 // the 13 shifts of code > 13, the canonical half) and the walk's first
-// `levels` levels in one workgroup, two at a time: the top of the walk has
-// frontiers of a few hundred pairs, where a launch per level costs more than
-// the level.  The frontier sizes, which thread 0 adds to with atomics, are
-// read back with atomic loads.
+// `levels` levels in one workgroup: the top of the walk has frontiers of a few
+// hundred pairs, where a launch per level costs more than the level.  A level
+// is a chain of latencies, so while a frontier has a pair per thread or less
+// it stays in LDS (a child's four at most fit), with the counts of the keys:
+// through global memory and device-scope atomics a level of 16^3 was 0.5 us
+// more.  From the first larger frontier on (or at the end) it is
+// in global memory, two levels a step, and its sizes, which thread 0 adds to
+// with atomics, are read back with atomic loads.
 __global__ void __launch_bounds__(kWalkT)
 k_walk_top(int nbox, const int32_t* __restrict__ box_root, int2* __restrict__ buf0,
            int2* __restrict__ buf1, int levels, uint32_t* __restrict__ sizes,
@@ -1016,28 +1035,56 @@ k_walk_top(int nbox, const int32_t* __restrict__ box_root, int2* __restrict__ bu
     __shared__ uint64_t wtot[kWalkT / 64];
     __shared__ uint32_t bbase[4];
     __shared__ int2 lch[4 * kWalkT];
-    const uint32_t nf0 = (uint32_t)(14 * nbox);
-    for (uint32_t q = threadIdx.x; q < nf0; q += blockDim.x) {
+    __shared__ uint32_t lctl[4];
+    const uint32_t t = threadIdx.x;
+    uint32_t nf = (uint32_t)(14 * nbox);
+    auto root_pair = [&](uint32_t q) {
         const int b = (int)(q / 14), j = (int)(q - 14 * (uint32_t)b);
         const int root = box_root[b];
-        buf0[q] = make_int2(root, (root << 5) | (13 + j));
+        return make_int2(root, (root << 5) | (13 + j));
+    };
+    int it = 0;
+    if (nf <= (uint32_t)kWalkT) {
+        if (t < 4) lctl[t] = 0u;
+        if (t < nf) lch[t] = root_pair(t);
+        __syncthreads();
+        uint32_t most = 0;
+        while (it < levels && nf != 0 && nf <= (uint32_t)kWalkT) {
+            most = max(most, nf);
+            if (t == 0) sizes[it] = nf;
+            WalkOut o{0u, 0u, 0u, {}, {0ull, 0ull}};
+            if (t < nf) walk_classify(lch[t], wbox, wcell, ks, o);
+            nf = walk_emit<kWalkT>(o, nullptr, nullptr, 0u, lch, lctl, cap_p2p, cap_m2l, p2p_keys,
+                           m2l_keys, wtot, bbase);
+            ++it;
+        }
+        if (t < 2 && lctl[t] != 0u) atomicAdd(&ctl[t], lctl[t]);
+        if (t == 2 && lctl[2] != 0u) ctl[2] = 1u;
+        if (t == 3) atomicMax(&ctl[3], most);
+        if (nf == 0) return;
     }
-    if (threadIdx.x == 0) sizes[0] = nf0;
+    if (nf > cap_front) {
+        if (t == 0) ctl[2] = 1u;
+        return;
+    }
+    // the frontier of level `levels` ends in buffer walk_top_steps(levels) & 1
+    int step = (walk_top_steps(levels) ^ walk_top_steps(levels - it)) & 1;
+    for (uint32_t q = t; q < nf; q += blockDim.x)
+        ((step & 1) ? buf1 : buf0)[q] = it == 0 ? root_pair(q) : lch[q];
+    if (t == 0) sizes[it] = nf;
     __syncthreads();
-    int step = 0;
-    for (int it = 0; it < levels; ++step) {
-        const uint32_t nf = it == 0 ? nf0
-                                    : __hip_atomic_load(&sizes[it], __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_AGENT);
+    for (const int it0 = it; it < levels; ++step) {
+        if (it != it0)
+            nf = __hip_atomic_load(&sizes[it], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (nf > cap_front) return;
         const int2* front = (step & 1) ? buf1 : buf0;
         int2* next = (step & 1) ? buf0 : buf1;
         if (it + 2 <= levels) {
-            walk_two(front, next, it, nf, 0u, 1u, sizes, ctl, cap_front, cap_p2p, cap_m2l, wbox,
+            walk_two<kWalkT>(front, next, it, nf, 0u, 1u, sizes, ctl, cap_front, cap_p2p, cap_m2l, wbox,
                      wcell, ks, p2p_keys, m2l_keys, wtot, bbase, lch);
             it += 2;
         } else {
-            (void)walk_level(front, next, it, nf, 0u, 1u, sizes, ctl, cap_front, cap_p2p,
+            (void)walk_level<kWalkT>(front, next, it, nf, 0u, 1u, sizes, ctl, cap_front, cap_p2p,
                              cap_m2l, wbox, wcell, ks, p2p_keys, m2l_keys, wtot, bbase);
             it += 1;
         }
@@ -1762,8 +1809,11 @@ std::string gpu_build_plan(DevPlan& d, const Plan& topo, const double* pos, cons
             // workgroups for the frontier the last build had at this level
             // (the kernel strides over any size; this only trims launches)
             const int64_t prev = it < (int)d.walk_sizes.size() ? d.walk_sizes[it] : capf;
-            const unsigned g = (unsigned)std::min<int64_t>(512, (prev + prev / 4 + 2 * kWalkT) / kWalkT);
-            hipLaunchKernelGGL(k_walk_multi, dim3(g), dim3(kWalkT), 0, s, bufs[cur]->as<int2>(),
+            const bool narrow = prev <= kWalkNarrowMax;
+            const int T = narrow ? kWalkNarrow : kWalkT;
+            const unsigned g = (unsigned)std::min<int64_t>(kWalkThreads / T, (prev + prev / 4 + 2 * T) / T);
+            hipLaunchKernelGGL(narrow ? k_walk_multi<kWalkNarrow> : k_walk_multi<kWalkT>, dim3(g), dim3(T),
+                               0, s, bufs[cur]->as<int2>(),
                                bufs[cur ^ 1]->as<int2>(), it, sizes, ctl, capf, capp, capm,
                                d.walkbox.as<WalkBox>(), d.wcell.as<WalkCell>(), ks,
                                d.p2p_keys.as<uint64_t>(), d.m2l_keys.as<uint64_t>());
