@@ -11,7 +11,7 @@ reduction.  ``value`` counts candidate pairs of the P2P tasks (n_i * n_j per
 task, the paper's interaction count) per second of whole step, for the
 float32 form (cell-relative float32 pairs, T(r) / r^3 from a table of
 quadratic segments over r^2, 64 per octave, float64 accumulation).  The float32 form with the paper's
-table (512 nodes on x, T_[2]) and the plain float64 form (exact erfc/exp)
+table (512 nodes on x, T_[2]) and the plain float64 form (T to rounding)
 are timed the same way and reported beside it.
 
 Prints one JSON line.  ``--gpus N`` with N > 1 exits: this build runs on one
@@ -49,17 +49,18 @@ from paper_2107_14008_amd import inputs  # noqa: E402
 FLOPS_EVAL_F32_R2, FLOPS_INSIDE_F32_R2 = 9, 14
 FLOPS_INSIDE_F32_R2_LINEAR = 12
 # float32 Taylor table of Eq. (int) (T_[2], the paper's single-precision
-# form): every evaluated pair takes displacement 3, r^2 5, 1/r 1, table
-# coordinate 2, index and offset 2, Horner 4, m T / r^3 4, accumulation 6.
-FLOPS_EVAL_F32_T2, FLOPS_INSIDE_F32_T2 = 27, 0
-# float64 exact erfc / exp: displacement 3, r^2 5, 1/r 1, x 2,
-# T = erfc + c x e^-x^2 6, g 4, accumulation 6 per evaluated pair.
-FLOPS_EVAL_F64_EXACT, FLOPS_INSIDE_F64_EXACT = 27, 0
+# form): displacement 3, r^2 5, cutoff test 1 per evaluated pair; inside r_cut
+# 1/r 1, table coordinate 2, index and offset 2, Horner 4, m T / r^3 4,
+# accumulation 6.
+FLOPS_EVAL_F32_T2, FLOPS_INSIDE_F32_T2 = 9, 19
+# float64 exact (F(y) = T / x^3 by degree-6 segments over y = x^2, to rounding;
+# r_cut <= 6 r_s): displacement 3, r^2 5, y 1 and the two range tests 2 per
+# evaluated pair; inside r_cut segment index 2, t 1, Horner 12, g 1 and
+# accumulation 6.
+FLOPS_EVAL_F64_EXACT, FLOPS_INSIDE_F64_EXACT = 11, 22
 # float64 Taylor table T_[4]: as the float32 table with a degree-4 Horner.
 FLOPS_EVAL_F64_T4, FLOPS_INSIDE_F64_T4 = 31, 0
-# float64 r^2 table (degree 6): displacement 3, r^2 5, s = r^2 sigma^2 1 and
-# the two range tests 2 per evaluated pair; inside r_cut segment index 2,
-# t = s - s_k 1, degree-6 Horner 12, g = m F 1 and accumulation 6.
+# float64 r^2 table: for r_cut <= 6 r_s the same table.
 FLOPS_EVAL_F64_R2, FLOPS_INSIDE_F64_R2 = 11, 22
 # (images other than s = 0 add 3 float64 additions per pair; not counted)
 FORM_FLOPS = {
@@ -619,10 +620,11 @@ def main():
             "fp32_paper_table_form": f"float32 cell-relative pairs, "
                                      f"{args.table_size}-node T_[{args.table_level}] "
                                      f"table of Eq. (int)",
-            "fp64_form": "float64 pairs, exact erfc/exp",
+            "fp64_form": "float64 pairs, T/x^3 to rounding from degree-6 segments over x^2 "
+                         "(128 per octave)",
             "fp64_table_form": "float64 pairs, 2048-node T_[4] table of Eq. (int)",
-            "fp64_r2_form": "float64 pairs, T(r)/r^3 from degree-6 segments over r^2 "
-                            "(64 per octave), pairs below r_cut/256 exact",
+            "fp64_r2_form": "float64 pairs, the r^2 form, which for r_cut <= 6 r_s reads the "
+                            "same table",
         },
         "roofline": {
             "bound": "alu",
