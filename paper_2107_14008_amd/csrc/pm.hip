@@ -1,7 +1,7 @@
 // Long-range part of the force split (Sec. 2) on a periodic mesh: cloud in
 // cell assignment, a 3D real FFT, the Gaussian-filtered Newtonian Green's
-// function, the spectral gradient, three inverse FFTs and cloud in cell
-// interpolation, in float64.
+// function, the spectral gradient, three inverse FFTs in one batch and cloud in
+// cell interpolation, in float64.
 //
 //   rho(g)  = (N / L)^3 sum_i m_i W(x_i - g L / N)        (CIC weights W)
 //   phi(k)  = -4 pi G rho(k) exp(-k^2 r_s^2) / k^2 / C(k)^2,  phi(0) = 0,
