@@ -1317,6 +1317,7 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
     a.items = ctx->d.items.as<int4>();
     a.queue = ctx->d.queue.as<int32_t>();
     a.n_items = (int32_t)ctx->n_items;
+    a.largest_leaf = pl.largest_leaf;
     a.counter = counter;
     a.partial = partial;
     a.boxes = ctx->d.boxes.as<pmfmm::BoxDev>();

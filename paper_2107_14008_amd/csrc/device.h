@@ -448,6 +448,7 @@ struct P2PArgs {
     const int4* items;
     const int32_t* queue;
     int32_t n_items;
+    int32_t largest_leaf;      // the most particles a leaf has
     int32_t* counter;
     double* partial;
     const BoxDev* boxes;

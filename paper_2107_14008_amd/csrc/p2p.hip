@@ -311,6 +311,42 @@ __device__ __forceinline__ void leaf_f32(const float4* __restrict__ src, int nj,
     }
 }
 
+// A leaf of at most 32 (16) targets leaves half (three quarters) of the lanes
+// idle, so they take the same targets again and every other (fourth) live
+// source: the wave's parts are added at the end of the item.  The sources then
+// differ between the lanes, so the live ones are packed into 64 places of the
+// wave's own in LDS, the places behind them taken by ones beyond any cutoff,
+// and read from there, a place per part (a broadcast).
+constexpr int kSplitLeaf = 32;
+constexpr int split_of(int ni) { return ni <= kSplitLeaf / 2 ? 4 : 2; }
+
+template <class V, class S>
+__device__ __forceinline__ int stage_live(V* __restrict__ buf, const V& q, uint64_t live, int lane, S far) {
+    const int below = __popcll(live & ((1ull << lane) - 1)), nl = __popcll(live);
+    const bool on = (live >> lane) & 1u;
+    V v = q;
+    if (!on) {
+        v.x = v.y = v.z = far;
+        v.w = 0;
+    }
+    // the wave's reads of the task before come first, its own after
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    buf[on ? below : nl + lane - below] = v;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return nl;
+}
+
+// The nl staged sources, two per lane at a time (2 split divides 64, so the
+// places read stay within them).
+template <class V, class F>
+__device__ __forceinline__ void staged_pairs(const V* __restrict__ buf, int nl, int split, int part, F pair) {
+    for (int k = part; k - part < nl; k += 2 * split) {
+        const V a = buf[k], b = buf[k + split];
+        pair(a);
+        pair(b);
+    }
+}
+
 // The pairs of one j leaf in the float32 r^2 form: four sources per 64-byte
 // scalar load, ahead of the masked table reads.  With a linear table
 // (LEVEL 1), the sources in `near` (those that may come closer than the
@@ -517,7 +553,13 @@ __device__ __forceinline__ void load_table(unsigned char* lds, const void* __res
     __syncthreads();
 }
 
-template <int MODE, int LEVEL, bool ACC32, int BITS>
+// The forms whose leaves of at most 32 targets are split (the linear r^2 form
+// comes back to its close sources by their places).
+constexpr bool splits(int mode, int level) {
+    return mode == kFP64F || (is_fp32(mode) && !(mode == kFP32R2 && level == 1));
+}
+
+template <int MODE, int LEVEL, bool ACC32, int BITS, bool SPLIT>
 __global__ void __launch_bounds__(p2p_max_threads(MODE), p2p_min_waves_per_simd(MODE))
 p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
            const int4* __restrict__ leaf, const double4* __restrict__ leafc,
@@ -531,6 +573,9 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                             (MODE == kFP64R2) || (MODE == kFP64F);
     if constexpr (kTable) load_table(lds, table, table_bytes);
     const int lane = threadIdx.x & 63;
+    using Staged = std::conditional_t<is_fp32(MODE), float4, double4>;
+    [[maybe_unused]] Staged* stage = reinterpret_cast<Staged*>(lds + (table_bytes + 15) / 16 * 16) +
+                    64 * uni((int)(threadIdx.x >> 6));
     const int dmax = n_tab - 1;
 
     ItemCursor cur = item_cursor();
@@ -542,7 +587,10 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
         const int il = uni(it.x), t0 = uni(it.y), t1 = uni(it.z);
         const int4 li = leaf[il];
         const int ni = uni(li.y);
-        const int pi = uni(li.x) + (lane < ni ? lane : 0);
+        const int split = SPLIT ? split_of(ni) : 1;
+        const int psh = split == 4 ? 4 : split == 2 ? 5 : 6;      // a part's lanes: 1 << psh
+        const int tgt = lane & ((1 << psh) - 1);
+        const int pi = uni(li.x) + (tgt < ni ? tgt : 0);
         const BoxDev bx = boxes[uni(li.z)];
         const double4 ci = leafc[il];
         double ax = 0.0, ay = 0.0, az = 0.0;
@@ -608,7 +656,19 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                 const float3 bhi = make_float3(hi.x - offx, hi.y - offy, hi.z - offz);
                 const uint64_t live = kLin ? live_near_f32(ql, nj, lane, blo, bhi, rc2, near2, near)
                                            : live_f32(ql, nj, lane, blo, bhi, rc2);
-                if constexpr (MODE == kFP32Exact) {
+                if constexpr (SPLIT) {
+                    const int nl = stage_live(stage, ql, live, lane, 1e18f);
+                    staged_pairs(stage, nl, split, lane >> psh, [&](const float4 q) {
+                        if constexpr (MODE == kFP32Exact)
+                            pair_f32_exact(q, px, py, pz, rc2, tiny, bx.alpha_f, fx, fy, fz);
+                        else if constexpr (MODE == kFP32Table)
+                            pair_f32_table<LEVEL, false>(q, px, py, pz, rc2, tiny, bx.tab_scale_f, rnd,
+                                                         lds, off23, off4, fx, fy, fz);
+                        else
+                            pair_f32_r2<LEVEL, false, BITS>(q, px, py, pz, rc2, smin, r2shift, r2boff,
+                                                            lds, fx, fy, fz);
+                    });
+                } else if constexpr (MODE == kFP32Exact) {
                     leaf_f32(src, nj, live, [&](const float4 q) {
                         pair_f32_exact(q, px, py, pz, rc2, tiny, bx.alpha_f, fx, fy, fz);
                     });
@@ -676,14 +736,23 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                     const double4 ql = qn;
                     const double4* __restrict__ src = x64 + jn;
                     const int nj = cn >> 5, s = cn & 31;
-                    const bool uni_mass = lane_of(tl.mass, k) != 0;
+                    const bool uni_mass = !SPLIT && lane_of(tl.mass, k) != 0;
                     if (k + 1 < nt) {
                         jn = lane_of(tl.first, k + 1);
                         cn = lane_of(tl.count_code, k + 1);
                         qn = x64[jn + min(lane, (cn >> 5) - 1)];
                     }
                     double fx = 0.0, fy = 0.0, fz = 0.0;
-                    if (s == 13) {
+                    if constexpr (SPLIT) {
+                        double sx, sy, sz;
+                        image_shift(s, bx.L, sx, sy, sz);
+                        const uint64_t live =
+                            live_f64<true>(ql, nj, lane, lo, hi, sx, sy, sz, T.rc2);
+                        const int nl = stage_live(stage, ql, live, lane, 1e150);
+                        staged_pairs(stage, nl, split, lane >> psh, [&](const double4& q) {
+                            pair_f64_F<false, true>(q, pv.x, pv.y, pv.z, sx, sy, sz, T, ax, ay, az);
+                        });
+                    } else if (s == 13) {
                         const uint64_t live =
                             live_f64<false>(ql, nj, lane, lo, hi, 0.0, 0.0, 0.0, T.rc2);
                         if (uni_mass)
@@ -789,6 +858,13 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                 az *= sig3;
             }
         }
+        if constexpr (SPLIT) {
+            for (int o = 32; o >= 64 / split; o >>= 1) {
+                ax += __shfl_xor(ax, o);
+                ay += __shfl_xor(ay, o);
+                az += __shfl_xor(az, o);
+            }
+        }
         double* dst = partial + (size_t)slot * 192;
         dst[lane] = ax;
         dst[64 + lane] = ay;
@@ -881,21 +957,49 @@ __global__ void zero_i32_kernel(int32_t* p, int32_t n) {
     if (i < n) p[i] = 0;
 }
 
+// LDS of the split form: the table, then 64 sources for each wave.  0 where the
+// form is not split: for plans with a leaf of more than kSplitLeaf targets (one
+// kernel with both ways had 64 VGPRs and spills for 55 in float32, 99 for 89 in
+// float64: 10^6 particles in leaves of 61, float64, 3925 -> 4205 us a step), and
+// where the staged sources would cost a resident workgroup.  P2P with leaves of
+// 32: 32^3 float64 / float32 r^2 212 / 138 -> 177 / 117 us, 40^3 365 / 195 ->
+// 279 / 170, 64^3 1264 / 526 -> 900 / 388.
+size_t split_lds(int mode, int level, int largest_leaf, int wg_waves, size_t lds) {
+    if (!splits(mode, level) || largest_leaf > kSplitLeaf) return 0;
+    constexpr size_t kCuLds = 160 * 1024, kCuWaves = 32;
+    const size_t table = (lds + 15) / 16 * 16;
+    const size_t all = table + (size_t)wg_waves * 64 * (is_fp32(mode) ? sizeof(float4) : sizeof(double4));
+    const size_t by_waves = std::max<size_t>(1, kCuWaves / wg_waves);
+    const size_t before = table == 0 ? by_waves : std::min(by_waves, kCuLds / table);
+    return std::min(by_waves, kCuLds / all) >= std::max<size_t>(1, before) ? all : 0;
+}
+
+template <int MODE, int LEVEL, bool ACC32, int BITS>
+hipError_t launch_form(const P2PArgs& a, int wg_waves, int grid_wgs, size_t lds, hipStream_t s) {
+    const int tb = (int)lds;
+    if constexpr (splits(MODE, LEVEL)) {
+        const size_t both = split_lds(MODE, LEVEL, a.largest_leaf, wg_waves, lds);
+        if (both != 0) {
+            hipLaunchKernelGGL((p2p_kernel<MODE, LEVEL, ACC32, BITS, true>), dim3(grid_wgs),
+                               dim3(64 * wg_waves), both, s, a.x64, a.x32, a.leaf, a.leafc, a.p2p_js,
+                               a.items, a.queue, a.n_items, a.counter, a.partial, a.boxes, a.table,
+                               a.n_tab, tb, a.round_floor);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((p2p_kernel<MODE, LEVEL, ACC32, BITS, false>), dim3(grid_wgs),
+                       dim3(64 * wg_waves), lds, s, a.x64, a.x32, a.leaf, a.leafc, a.p2p_js, a.items,
+                       a.queue, a.n_items, a.counter, a.partial, a.boxes, a.table, a.n_tab, tb,
+                       a.round_floor);
+    return hipGetLastError();
+}
+
 template <int MODE, int LEVEL, int BITS = 0>
 hipError_t launch_one(const P2PArgs& a, int wg_waves, int grid_wgs, size_t lds, hipStream_t s) {
-    const int tb = (int)lds;
     // the compensated float32 sums are a variant of the float32 kernels only
     if (is_fp32(MODE) && a.accum32)
-        hipLaunchKernelGGL((p2p_kernel<MODE, LEVEL, is_fp32(MODE), BITS>), dim3(grid_wgs),
-                           dim3(64 * wg_waves), lds, s, a.x64, a.x32, a.leaf, a.leafc, a.p2p_js,
-                           a.items, a.queue, a.n_items, a.counter, a.partial, a.boxes, a.table,
-                           a.n_tab, tb, a.round_floor);
-    else
-        hipLaunchKernelGGL((p2p_kernel<MODE, LEVEL, false, BITS>), dim3(grid_wgs),
-                           dim3(64 * wg_waves), lds, s, a.x64, a.x32, a.leaf, a.leafc, a.p2p_js,
-                           a.items, a.queue, a.n_items, a.counter, a.partial, a.boxes, a.table,
-                           a.n_tab, tb, a.round_floor);
-    return hipGetLastError();
+        return launch_form<MODE, LEVEL, is_fp32(MODE), BITS>(a, wg_waves, grid_wgs, lds, s);
+    return launch_form<MODE, LEVEL, false, BITS>(a, wg_waves, grid_wgs, lds, s);
 }
 
 // The float32 r^2 form at its segments per octave (n_tab = 2^BITS): 16 to
@@ -923,7 +1027,7 @@ hipError_t launch_r2(const P2PArgs& a, int wg_waves, int grid_wgs, size_t lds, h
 template <int MODE, int LEVEL>
 int occ_one(int wg_waves, size_t lds) {
     int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, p2p_kernel<MODE, LEVEL, false, MODE == kFP32R2 ? 6 : 0>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, p2p_kernel<MODE, LEVEL, false, MODE == kFP32R2 ? 6 : 0, false>,
                                                      64 * wg_waves, lds) != hipSuccess)
         return 1;
     return blocks > 0 ? blocks : 1;

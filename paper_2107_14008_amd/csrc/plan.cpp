@@ -350,11 +350,13 @@ std::string make_plan(Plan& plan, const std::vector<BoxParams>& boxes,
     clk.lap("orb");
     plan.leaf_first.resize(n_leaves);
     plan.leaf_count.resize(n_leaves);
+    plan.largest_leaf = 0;
     plan.leaf_box.resize(n_leaves);
     for (int64_t l = 0; l < n_leaves; ++l) {
         const Cell& c = plan.cells[plan.leaf_cell[l]];
         plan.leaf_first[l] = c.first;
         plan.leaf_count[l] = c.count;
+        plan.largest_leaf = std::max(plan.largest_leaf, (int32_t)c.count);
         plan.leaf_box[l] = c.box;
     }
 
@@ -533,11 +535,13 @@ void make_topology(Plan& plan, const std::vector<BoxParams>& boxes,
     }
     plan.leaf_first.resize(nl);
     plan.leaf_count.resize(nl);
+    plan.largest_leaf = 0;
     plan.leaf_box.resize(nl);
     for (int64_t l = 0; l < nl; ++l) {
         const Cell& c = plan.cells[plan.leaf_cell[l]];
         plan.leaf_first[l] = c.first;
         plan.leaf_count[l] = c.count;
+        plan.largest_leaf = std::max(plan.largest_leaf, (int32_t)c.count);
         plan.leaf_box[l] = c.box;
     }
     int max_depth = 0;

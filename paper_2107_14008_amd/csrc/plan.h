@@ -60,6 +60,7 @@ struct Plan {
     std::vector<Cell> cells;
     std::vector<int32_t> leaf_cell;           // leaf -> cell
     std::vector<int32_t> leaf_first, leaf_count, leaf_box;
+    int32_t largest_leaf = 0;      // the most particles a leaf has
     std::vector<int32_t> p2p_row, p2p_j, p2p_shift;
     std::vector<int32_t> m2l_row, m2l_src, m2l_shift;
     std::vector<int32_t> cell_first, cell_count, cell_child;  // views for the ABI
