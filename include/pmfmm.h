@@ -61,8 +61,8 @@ enum { PMFMM_FP64 = 0, PMFMM_FP32 = 1 };
  * r_cut / 256) through the library erfc/exp.  It needs one r_cut / r_s for
  * all boxes of a plan.  For r_cut <= 6 r_s in every box both float64 forms,
  * EXACT and R2, are evaluated from one built-in table of T / r^3 that is
- * within 3e-16 of it for r <= 5.6 r_s (3.4e-15 at 6 r_s), finer than any R2
- * table that can be asked for. */
+ * within 3e-16 of it for r <= 5.6 r_s and 8e-16 up to 6 r_s, finer than
+ * any R2 table that can be asked for. */
 enum { PMFMM_TRUNC_EXACT = 0, PMFMM_TRUNC_TABLE = 1, PMFMM_TRUNC_R2 = 2 };
 /* M2L acceptance against the cutoff (Sec. 2 truncates the kernel at
  * r_cut; where a cell pair straddles r_cut the paper does not say).

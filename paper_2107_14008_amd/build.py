@@ -30,6 +30,7 @@ HOST = ["-ffp-contract=off"]
 
 SOURCES = [
     ("plan.cpp", "gxx"),
+    ("f_table.cpp", "gxx"),
     ("abi.cpp", "hip-host"),
     ("p2p.hip", "hip"),
     ("far.hip", "hip"),

@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "device.h"
+#include "f_table.h"
 #include "gpu_plan.h"
 #include "plan.h"
 #include "pm.h"
@@ -121,7 +122,7 @@ int mode_of(const pmfmm_params& p) {
     return p.trunc == PMFMM_TRUNC_TABLE ? pmfmm::kFP32Table : pmfmm::kFP32Exact;
 }
 
-// The float64 exact form takes F from a table (device.h) when r_cut <= 6 r_s in
+// The float64 exact form takes F from a table (f_table.h) when r_cut <= 6 r_s in
 // every box, and the polynomial of truncation_T_f64 otherwise.
 bool exact64(const pmfmm_params& p) { return p.precision == PMFMM_FP64 && p.trunc == PMFMM_TRUNC_EXACT; }
 
@@ -129,6 +130,15 @@ bool within_f_table(const std::vector<pmfmm::BoxParams>& boxes) {
     for (const auto& b : boxes)
         if (!(b.r_cut / (2.0 * b.r_s) <= pmfmm::kFXcMax)) return false;
     return true;
+}
+
+// Whether the F table's last octave is in use.
+bool f_table_end(const std::vector<pmfmm::BoxParams>& boxes) {
+    for (const auto& b : boxes) {
+        const double xc = b.r_cut / (2.0 * b.r_s);
+        if (!(xc * xc < pmfmm::kFPlainMax)) return true;
+    }
+    return false;
 }
 
 bool uses_r2(const pmfmm_params& p) { return p.precision == PMFMM_FP32 && p.trunc == PMFMM_TRUNC_R2; }
@@ -351,74 +361,9 @@ std::vector<unsigned char> build_r2_table64(int per_octave, int deg, double xc) 
     return out;
 }
 
-// The F table of the float64 exact form (layout and ranges: device.h), built
-// once per process.  Per segment, with v = t / half width in [-1, 1]: the
-// Taylor coefficients of F about the middle to order kN from the equation
-//   y F' = -(3/2) F - (2 / sqrt(pi)) exp(-y)
-// (one erfc and one exp per segment, in long double), cut to degree 6 by
-// dropping the Chebyshev terms above it.
+// The F table of the float64 exact form, built once per process.
 const std::vector<unsigned char>& f_table() {
-    static const std::vector<unsigned char> table = [] {
-        constexpr int kN = 14, kD = 6;
-        using ld = long double;
-        // cheb[k][j]: coefficient of v^j in T_k; to_cheb: v^m in Chebyshev terms
-        ld cheb[kN + 1][kN + 1] = {}, low[kD + 1][kN + 1] = {};
-        cheb[0][0] = 1;
-        cheb[1][1] = 1;
-        for (int k = 2; k <= kN; ++k)
-            for (int j = 0; j <= kN; ++j)
-                cheb[k][j] = (j > 0 ? 2 * cheb[k - 1][j - 1] : 0) - cheb[k - 2][j];
-        for (int m = 0; m <= kN; ++m) {
-            // v^m = 2^(1-m) sum_q C(m, q) T_(m-2q), the T_0 term halved
-            ld binom = 1;
-            for (int q = 0; 2 * q <= m; ++q) {
-                const int k = m - 2 * q;
-                const ld w = std::ldexp(binom, 1 - m) * (k == 0 ? 0.5L : 1.0L);
-                if (k <= kD)
-                    for (int j = 0; j <= kD; ++j) low[j][m] += w * cheb[k][j];
-                binom = binom * (m - q) / (q + 1);
-            }
-        }
-        std::vector<unsigned char> out((size_t)pmfmm::kFAdjTableBytes, 0);
-        const ld two_sqrt_pi = 1.128379167095512573896158903121545172L;
-        for (int r = 0; r < pmfmm::kFUsedRows; ++r) {
-            const int e = pmfmm::kFEmin + (r >> pmfmm::kFBits), j = r & ((1 << pmfmm::kFBits) - 1);
-            const ld per = (ld)(1 << pmfmm::kFBits);
-            const ld y = std::ldexp(1 + (j + 0.5L) / per, e), half = std::ldexp(0.5L / per, e);
-            const ld x = std::sqrt(y), ey = std::exp(-y);
-            ld f[kN + 1];
-            f[0] = (std::erfc(x) + two_sqrt_pi * x * ey) / (y * x);
-            // (n + 1) f_(n+1) y = -(n + 3/2) f_n - (2 / sqrt(pi)) (-1)^n exp(-y) / n!
-            ld en = two_sqrt_pi * ey;
-            for (int n = 0; n < kN; ++n) {
-                f[n + 1] = -((n + 1.5L) * f[n] + en) / ((n + 1) * y);
-                en = -en / (n + 1);
-            }
-            ld hp = 1;
-            for (int n = 0; n <= kN; ++n) {
-                f[n] *= hp;
-                hp *= half;
-            }
-            hp = 1;
-            for (int k = 0; k <= kD; ++k) {
-                ld c = 0;
-                for (int n = 0; n <= kN; ++n) c += low[k][n] * f[n];
-                c /= hp;
-                hp *= half;
-                unsigned char* slot = out.data() + (size_t)8 * r;
-                if (k < 4) {
-                    const double v = (double)c;
-                    std::memcpy(slot + (size_t)(k + 2) * pmfmm::kFPlane, &v, 8);
-                } else {
-                    const float v = (float)c;
-                    std::memcpy(slot + (size_t)(k < 6 ? 0 : 1) * pmfmm::kFPlane + (k == 5 ? 4 : 0), &v, 4);
-                }
-            }
-            const double em = (double)ey;
-            std::memcpy(out.data() + (size_t)8 * r + (size_t)6 * pmfmm::kFPlane, &em, 8);
-        }
-        return out;
-    }();
+    static const std::vector<unsigned char> table = pmfmm::build_f_table();
     return table;
 }
 
@@ -1323,7 +1268,7 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
     a.boxes = ctx->d.boxes.as<pmfmm::BoxDev>();
     a.table = mode == pmfmm::kFP64F ? ctx->d.ftable.p : ctx->d.table.p;
     a.n_tab = ctx->p.table_size;
-    a.level = ctx->p.table_level;
+    a.level = mode == pmfmm::kFP64F ? (int)f_table_end(pl.boxes) : ctx->p.table_level;
     a.round_floor = ctx->p.table_round == PMFMM_ROUND_FLOOR;
     a.accum32 = ctx->p.accum == PMFMM_ACCUM_FP32_TWOSUM;
     const bool tab = mode == pmfmm::kFP32Table || mode == pmfmm::kFP64Table || mode == pmfmm::kFP32R2 ||
@@ -1646,6 +1591,7 @@ int pmfmm_adjoint(pmfmm_ctx* ctx, const double* w, double* grad_pos, double* gra
         int rc = upload_f_table(ctx, s);
         if (rc) return rc;
         a.table = ctx->d.ftable.p;
+        a.f_end = f_table_end(pl.boxes);
     }
     // 8 waves per workgroup share the tables of the r^2 form (measured on
     // the 64^3 clustered workload: 1.02 ms against 1.13 ms with 4 and

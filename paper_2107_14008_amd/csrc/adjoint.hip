@@ -10,7 +10,7 @@
 // the delta function of the hard cutoff being left out.  Same wavefront
 // mapping and work queue as the forward P2P kernel; the source records are
 // (x, m) and (w, 0), both read with wave-uniform addresses.  g and h are
-// evaluated exactly (float64: from the F table of device.h for r_cut <=
+// evaluated exactly (float64: from the F table of f_table.h for r_cut <=
 // 6 r_s, else truncation_T_f64; float32: erfcf and expf), or, in the float32
 // r^2 form, read from quadratic tables in r^2.  Measured on 64^3 clustered
 // particles, float32 r^2 tables: 932 us with one scalar load and wait per
@@ -136,16 +136,16 @@ __device__ __forceinline__ void adj_pair_f32(const float4 q, const float4 wl, fl
     }
 }
 
-// Float64 from the F table (device.h): g = F / (2 r_s)^3 and h = 2 F' /
+// Float64 from the F table (f_table.h): g = F / (2 r_s)^3 and h = 2 F' /
 // (2 r_s)^5, where y F' = -(3/2) F - (2 / sqrt(pi)) exp(-y) gives h without
 // another polynomial: every term has one sign, so nothing cancels.
 // exp(-y) = exp(-(segment middle)) exp(-t), the first factor from the table,
 // the second a Taylor polynomial (|t| <= y / 256 <= 0.036: the t^8 term left
 // out is below 6e-17).  A, B and gm carry the factor (2 r_s)^3.
-template <bool EQ, bool SHIFTED>
+template <bool EQ, bool SHIFTED, bool END>
 __device__ __forceinline__ void adj_pair_f64_F(const double4& q, const double4& wl, double xk,
                                                double yk, double zk, const double4& wk, double sx,
-                                               double sy, double sz, const FTab& T, double* A,
+                                               double sy, double sz, const FTab<END>& T, double* A,
                                                double* Bv, double& gm) {
     double dx, dy, dz, r2;
     {
@@ -228,11 +228,13 @@ enum AdjForm : int {
     kAdjF32 = 0,      // float32, erfcf / expf
     kAdjF32Tab = 1,   // float32, g and h tables in LDS (kAdjTableBytes)
     kAdjF64 = 2,      // float64, polynomial T
-    kAdjF64Tab = 3    // float64, F table in LDS (kFAdjTableBytes)
+    kAdjF64Tab = 3,   // float64, F table in LDS (kFAdjTableBytes)
+    kAdjF64End = 4    // the same, its last octave in use
 };
+constexpr bool adj_f_tab(int form) { return form == kAdjF64Tab || form == kAdjF64End; }
 constexpr bool adj_f32(int form) { return form == kAdjF32 || form == kAdjF32Tab; }
 constexpr int adj_lds(int form) {
-    return form == kAdjF32Tab ? kAdjTableBytes : form == kAdjF64Tab ? kFAdjTableBytes : 0;
+    return form == kAdjF32Tab ? kAdjTableBytes : adj_f_tab(form) ? kFAdjTableBytes : 0;
 }
 
 // Waves per SIMD to leave room for.  Float32: eight (64 VGPRs, a few
@@ -335,7 +337,7 @@ adjoint_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
         } else {
             const double4 pv = x64[pk];
             const double4 wk = w64[pk];
-            const FTab T = f_tab(adj_lds_mem, bx.rc2, bx.alpha);
+            const FTab<FORM == kAdjF64End> T = f_tab<FORM == kAdjF64End>(adj_lds_mem, bx.rc2, bx.alpha);
             double3 lo = make_double3(pv.x, pv.y, pv.z), hi = lo;
             wave_box(lo, hi);
             for (int tb = t0; tb < t1; tb += 64) {
@@ -362,8 +364,8 @@ adjoint_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                                 : live_f64<true>(ql, nj, lane, lo, hi, sx, sy, sz, bx.rc2);
                     auto pairs = [&](auto eqc, auto shc) {
                         constexpr bool kEq = decltype(eqc)::value, kSh = decltype(shc)::value;
-                        adj_leaf<FORM == kAdjF64Tab ? 2 : 1>(src, wsrc, nj, live, [&](const double4& q, const double4& w) {
-                            if constexpr (FORM == kAdjF64Tab)
+                        adj_leaf<adj_f_tab(FORM) ? 2 : 1>(src, wsrc, nj, live, [&](const double4& q, const double4& w) {
+                            if constexpr (adj_f_tab(FORM))
                                 adj_pair_f64_F<kEq, kSh>(q, w, pv.x, pv.y, pv.z, wk, sx, sy, sz, T, A,
                                                          Bv, gm);
                             else
@@ -380,7 +382,7 @@ adjoint_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
                     }
                 }
             }
-            if constexpr (FORM == kAdjF64Tab) {
+            if constexpr (adj_f_tab(FORM)) {
                 const double a3 = T.a2 * bx.alpha;
                 for (int c = 0; c < 3; ++c) {
                     A[c] *= a3;
@@ -478,7 +480,9 @@ hipError_t launch_adjoint(int mode, const AdjArgs& a, int wg_waves, int grid_wgs
         case kAdjF32: return launch_form<kAdjF32>(a, wg_waves, grid_wgs, s);
         case kAdjF32Tab: return launch_form<kAdjF32Tab>(a, wg_waves, grid_wgs, s);
         case kAdjF64: return launch_form<kAdjF64>(a, wg_waves, grid_wgs, s);
-        default: return launch_form<kAdjF64Tab>(a, wg_waves, grid_wgs, s);
+        default:
+            if (a.f_end) return launch_form<kAdjF64End>(a, wg_waves, grid_wgs, s);
+            return launch_form<kAdjF64Tab>(a, wg_waves, grid_wgs, s);
     }
 }
 

@@ -17,6 +17,7 @@
 
 #include <cstdint>
 
+#include "f_table.h"
 #include "plan.h"
 #include "truncation_poly.h"
 
@@ -83,31 +84,9 @@ constexpr int kAdjPlane = 1216;
 static_assert(((kR2Emax - kAdjEmin) << kAdjBits) + 1 <= kAdjPlane, "adjoint table rows");
 constexpr int kAdjTableBytes = 6 * kAdjPlane * 4;
 
-// Float64 exact form for cutoffs r_cut <= 6 r_s (x_c <= 3): with y = x^2 =
-// (r / 2 r_s)^2, T(x) / r^3 = F(y) / (2 r_s)^3, F(y) = T(sqrt(y)) y^(-3/2), one
-// function of y for every box.  F is tabulated on 2^kFBits segments per
-// octave of y from 2^kFEmin to 9 (indexed by the high word of y), each a
-// degree-6 polynomial in t = y - (segment middle) with c0 .. c3 in float64
-// and c4 .. c6 in float32: the terms from t^4 on are below 2e-8 of F (|t| <=
-// y / 256), so their float32 rounding is below 1e-15 / 1000 of F.  Measured
-// against 40-digit values the table gives F within 2.6e-16 (relative; rms
-// 7e-17) up to y = 8 and 3.4e-15 at y = 9, where T = 4e-4; the polynomial of
-// truncation_T_f64 with its square roots and products stays within 2e-15.
-// Layout: six arrays of kFRows eight-byte slots, (c4, c5), (c6, 0), (c0),
-// (c1), (c2) and (c3), a multiple of 512 bytes apart, so that a lookup is an
-// 8-byte, a 4-byte and two two-address LDS reads, all from one address
-// register; a seventh holds exp(-(segment middle)) for the adjoint.  Pairs closer than y = 2^kFEmin take
-// the series of F about y = 0.
-constexpr int kFBits = 7;
-constexpr int kFEmin = -16;
-constexpr int kFRows = 2496;
-constexpr int kFPlane = kFRows * 8;
-constexpr int kFTableBytes = 6 * kFPlane;
-constexpr int kFAdjTableBytes = 7 * kFPlane;
-constexpr int kFUsedRows = ((3 - kFEmin) << kFBits) + (1 << kFBits) / 8 + 1;   // y up to 9 and one more
-constexpr double kFXcMax = 3.0;
-static_assert(kFUsedRows <= kFRows && kFPlane % 512 == 0, "rows of the F table");
-
+// The table of f_table.h in LDS.  END: its last octave is in use (a box with
+// y up to more than kFPlainMax inside the cutoff).
+template <bool END>
 struct FTab {
     const unsigned char* tab;   // LDS
     double rc2, a2;             // r_cut^2, 1 / (2 r_s)^2
@@ -118,16 +97,18 @@ struct FTab {
 // The two constants are kept opaque (an empty asm on their registers): the
 // address is then one shift and one shift-add, with the arrays' offsets in
 // the reads themselves, and the segment middle one bit-field insert.
-__device__ __forceinline__ FTab f_tab(const unsigned char* lds, double rc2, double alpha) {
-    FTab T{lds, rc2, alpha * alpha, 0u - (((uint32_t)(1023 + kFEmin) << kFBits) << 3),
-           1u << (19 - kFBits)};
+template <bool END>
+__device__ __forceinline__ FTab<END> f_tab(const unsigned char* lds, double rc2, double alpha) {
+    FTab<END> T{lds, rc2, alpha * alpha, 0u - (((uint32_t)(1023 + kFEmin) << kFBits) << 3),
+                1u << (19 - kFBits)};
     asm volatile("" : "+s"(T.boff));
     asm volatile("" : "+v"(T.mid));
     return T;
 }
 
 // F(y) for 2^kFEmin <= y <= 9; hi: high word of y.  *t, *row as used.
-__device__ __forceinline__ double f_lookup(const FTab& T, double y, uint32_t hi, double* t_out,
+template <bool END>
+__device__ __forceinline__ double f_lookup(const FTab<END>& T, double y, uint32_t hi, double* t_out,
                                            const unsigned char** row_out) {
     constexpr int sh = 20 - kFBits;
     constexpr uint32_t m = ~((1u << sh) - 1u);
@@ -137,7 +118,8 @@ __device__ __forceinline__ double f_lookup(const FTab& T, double y, uint32_t hi,
     const float tf = (float)t;
     const float2 c45 = *reinterpret_cast<const float2*>(c);
     const float c6 = *reinterpret_cast<const float*>(c + kFPlane);
-    double F = (double)fmaf(fmaf(c6, tf, c45.y), tf, c45.x);
+    const float p = fmaf(c6, tf, c45.y);
+    double F = END ? fma((double)p, t, (double)c45.x) : (double)fmaf(p, tf, c45.x);
     F = fma(F, t, *reinterpret_cast<const double*>(c + 5 * kFPlane));
     F = fma(F, t, *reinterpret_cast<const double*>(c + 4 * kFPlane));
     F = fma(F, t, *reinterpret_cast<const double*>(c + 3 * kFPlane));
@@ -521,6 +503,7 @@ struct AdjArgs {
     double* partial;            // (slot, 4, 64): grad x, y, z, m
     const BoxDev* boxes;
     const void* table;          // tables of the form (launch_adjoint), or null
+    int f_end;                  // F table: its last octave is in use
 };
 
 struct AdjReduceArgs {

@@ -490,13 +490,13 @@ __device__ __forceinline__ void leaf_f64_r2(const double4* __restrict__ src, int
                 pair_f64_r2_close<SHIFTED>(src[k], xi, yi, zi, sx, sy, sz, T, ax, ay, az);
 }
 
-// float64 exact form from the F table (device.h).  The displacement, r^2 and
+// float64 exact form from the F table (f_table.h).  The displacement, r^2 and
 // the cutoff test are those of pair_f64_exact; only lanes inside the cutoff
 // read the table.  UNI: the j leaf's sources share one mass, applied once per
 // leaf.  The item's sums are multiplied by 1 / (2 r_s)^3 at the end.
-template <bool UNI, bool SHIFTED>
+template <bool UNI, bool SHIFTED, bool END>
 __device__ __forceinline__ void pair_f64_F(const double4 q, double xi, double yi, double zi,
-                                           double sx, double sy, double sz, const FTab& T,
+                                           double sx, double sy, double sz, const FTab<END>& T,
                                            double& ax, double& ay, double& az) {
     double dx, dy, dz;
     const double r2 = disp_r2<SHIFTED>(q, xi, yi, zi, sx, sy, sz, dx, dy, dz);
@@ -518,10 +518,10 @@ __device__ __forceinline__ void pair_f64_F(const double4 q, double xi, double yi
     }
 }
 
-template <bool UNI, bool SHIFTED>
+template <bool UNI, bool SHIFTED, bool END>
 __device__ __forceinline__ void leaf_f64_F(const double4* __restrict__ src, int nj, uint64_t live,
                                            double xi, double yi, double zi, double sx, double sy,
-                                           double sz, const FTab& T, double& ax, double& ay,
+                                           double sz, const FTab<END>& T, double& ax, double& ay,
                                            double& az) {
     for (int k = 0; k < nj; k += 4) {
         const uint32_t g4 = (uint32_t)(live >> k) & 0xFu;
@@ -724,7 +724,7 @@ p2p_kernel(const double4* __restrict__ x64, const float4* __restrict__ x32,
             az *= s2;
         } else if constexpr (MODE == kFP64F) {
             const double4 pv = x64[pi];
-            const FTab T = f_tab(lds, bx.rc2, bx.alpha);
+            const FTab<LEVEL != 0> T = f_tab<LEVEL != 0>(lds, bx.rc2, bx.alpha);
             double3 lo = make_double3(pv.x, pv.y, pv.z), hi = lo;
             wave_box(lo, hi);
             for (int tb = t0; tb < t1; tb += 64) {
@@ -1040,7 +1040,9 @@ hipError_t launch_p2p(int mode, const P2PArgs& a, int wg_waves, int grid_wgs, si
     if (a.n_items == 0) return hipSuccess;
     switch (mode) {
         case kFP64Exact: return launch_one<kFP64Exact, 0>(a, wg_waves, grid_wgs, 0, s);
-        case kFP64F: return launch_one<kFP64F, 0>(a, wg_waves, grid_wgs, lds, s);
+        case kFP64F:   // level 1: the table's last octave is in use
+            if (a.level == 1) return launch_one<kFP64F, 1>(a, wg_waves, grid_wgs, lds, s);
+            return launch_one<kFP64F, 0>(a, wg_waves, grid_wgs, lds, s);
         case kFP32Exact: return launch_one<kFP32Exact, 0>(a, wg_waves, grid_wgs, 0, s);
         case kFP32Table:
             switch (a.level) {

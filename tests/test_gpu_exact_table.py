@@ -63,3 +63,47 @@ def test_single_pairs_against_forty_digits(xc, mass_ratio):
             e = abs(np.linalg.norm(got[i]) - m * a)
             worst = max(worst, e / (m * a) if a else e)
     assert worst <= tol, (worst, tol)
+
+
+@pytest.mark.parametrize("max_leaf", [32, 64])
+@pytest.mark.parametrize("mass_ratio", [1.0, 0.37])
+@pytest.mark.parametrize("xc,y0", [(2.25, 4.0), (3.0, 8.0)])
+def test_outer_shell_in_small_and_full_leaves(xc, y0, mass_ratio, max_leaf):
+    """The pairs of the table's last rows, y from y0 to the cutoff, in leaves
+    of 32 (the form that splits a leaf's lanes) and of 64 (one mass or several
+    to a leaf), some of them across the box's faces."""
+    tol = (1.5 + xc * xc) * 3.4e-16 + 2e-15     # as above
+    rng = np.random.default_rng(29)
+    r_cut = 5.0
+    r_s = r_cut / (2.0 * xc)
+    y = rng.uniform(y0, xc * xc * (1 - 1e-9), 512)
+    y[:16] = 8.375 if y0 == 8.0 else 4.3126      # the float32 t^4 term's worst
+    y[:16] += rng.uniform(-1e-3, 1e-3, 16)
+    r = 2.0 * r_s * np.sqrt(y)
+    g = np.arange(8) * 12.5 + 10.0
+    c = np.stack(np.meshgrid(g, g, g, indexing="ij"), -1).reshape(-1, 3)
+    # into the positive octant: the particles of different pairs stay 7.5 apart
+    v = np.abs(rng.standard_normal((512, 3)))
+    v /= np.linalg.norm(v, axis=1)[:, None]
+    pos = np.concatenate([c, c + r[:, None] * v]) % 100.0
+    mass = np.concatenate([np.full(512, 1.0), np.full(512, mass_ratio)])
+    print(f"case: outer shell, x_c {xc}, mass ratio {mass_ratio}, leaves of {max_leaf}", flush=True)
+    ctx = B.Context(box=100.0, r_s=r_s, r_cut=r_cut, max_leaf=max_leaf, order=-1)
+    ctx.build(torch.tensor(pos, device="cuda"), torch.tensor(mass, device="cuda"))
+    assert (np.diff(np.append(ctx.lists()["leaf_first"], 1024)) == max_leaf).all()
+    out = torch.empty((1024, 3), dtype=torch.float64, device="cuda")
+    ctx.forward(out)
+    got = out.cpu().numpy()
+    d = pos[512:] - pos[:512]
+    assert (np.abs(d) > 50).any()
+    d = np.where(d > 50, d - 100.0, np.where(d < -50, d + 100.0, d))
+    mpmath.mp.dps = 40
+    worst = 0.0
+    for k in range(512):
+        r2 = sum(mpmath.mpf(float(a)) ** 2 for a in d[k])
+        x = mpmath.sqrt(r2) / (2 * mpmath.mpf(r_s))
+        t = mpmath.erfc(x) + 2 * x / mpmath.sqrt(mpmath.pi) * mpmath.exp(-x * x)
+        a = float(t / r2)
+        for i, m in ((k, mass_ratio), (k + 512, 1.0)):
+            worst = max(worst, abs(np.linalg.norm(got[i]) - m * a) / (m * a))
+    assert worst <= tol, (worst, tol)
