@@ -768,15 +768,6 @@ int do_upload(pmfmm_ctx* ctx, const double* pos, const double* mass, int32_t on_
     return PMFMM_OK;
 }
 
-// Table forms: 16 waves share one LDS copy of the table (a 2048-segment r^2
-// table is 33 KB; with 4-wave groups LDS would cap a CU at 16 waves).
-int default_wg_waves(int mode) {
-    return (mode == pmfmm::kFP64Table || mode == pmfmm::kFP32Table || mode == pmfmm::kFP32R2 ||
-            mode == pmfmm::kFP64R2)
-               ? 16
-               : 4;
-}
-
 // Workgroups of a persistent launch: the caller's, or as many as are resident
 // (`resident`), but no more than there are items in every queue segment.
 int launch_grid(const pmfmm_ctx* ctx, int resident) {
@@ -1275,10 +1266,9 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
                      mode == pmfmm::kFP64R2;
     const size_t lds = mode == pmfmm::kFP64F ? (size_t)pmfmm::kFTableBytes : tab ? ctx->table_host.size() : 0;
     // one workgroup of the F table's size fits a CU: it always has 16 waves
-    const int wg = mode == pmfmm::kFP64F
-                       ? 16
-                       : std::min(ctx->p.wg_waves > 0 ? ctx->p.wg_waves : default_wg_waves(mode),
-                                  pmfmm::p2p_max_threads(mode) / 64);
+    const bool asked = ctx->p.wg_waves > 0 && mode != pmfmm::kFP64F;
+    const int wg = std::min(asked ? ctx->p.wg_waves : pmfmm::default_wg_waves(mode),
+                            pmfmm::p2p_max_threads(mode) / 64);
     const int grid = launch_grid(ctx, ctx->n_cu * pmfmm::p2p_blocks_per_cu(mode, wg, lds));
     if (pmfmm::queue_counts((int32_t)ctx->n_items, grid, wg))
         HIP_TRY(pmfmm::launch_zero_i32(counter, pmfmm::kQueueSegs * pmfmm::kCounterStride, s));

@@ -42,6 +42,10 @@ constexpr bool is_fp32(int mode) {
 // record in registers and is compiled for 4-wave workgroups (up to 512 VGPRs
 // per lane instead of 128).
 constexpr int p2p_max_threads(int mode) { return mode == kFP64Exact ? 256 : 1024; }
+// Waves per workgroup when the caller leaves the choice to the library.  Table
+// forms: 16 share one LDS copy of the table (a 2048-segment r^2 table is 33 KB;
+// with 4-wave groups LDS would cap a CU at 16 waves).
+constexpr int default_wg_waves(int mode) { return mode == kFP64Exact || mode == kFP32Exact ? 4 : 16; }
 // Waves per SIMD the float32 forms must leave room for: two 16-wave
 // workgroups per CU (their tables fit twice in LDS), so at most 64 VGPRs and
 // the matching scalar registers per wave.

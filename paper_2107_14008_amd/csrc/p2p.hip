@@ -957,31 +957,37 @@ __global__ void zero_i32_kernel(int32_t* p, int32_t n) {
     if (i < n) p[i] = 0;
 }
 
-// LDS of the split form: the table, then 64 sources for each wave.  0 where the
-// form is not split: for plans with a leaf of more than kSplitLeaf targets (one
-// kernel with both ways had 64 VGPRs and spills for 55 in float32, 99 for 89 in
-// float64: 10^6 particles in leaves of 61, float64, 3925 -> 4205 us a step), and
-// where the staged sources would cost a resident workgroup.  P2P with leaves of
-// 32: 32^3 float64 / float32 r^2 212 / 138 -> 177 / 117 us, 40^3 365 / 195 ->
-// 279 / 170, 64^3 1264 / 526 -> 900 / 388.
-size_t split_lds(int mode, int level, int largest_leaf, int wg_waves, size_t lds) {
-    if (!splits(mode, level) || largest_leaf > kSplitLeaf) return 0;
+// Whether a plan's items are summed by the split form: not with a leaf of more
+// than kSplitLeaf targets (one kernel with both ways had 64 VGPRs and spills for
+// 55 in float32, 99 for 89 in float64: 10^6 particles in leaves of 61, float64,
+// 3925 -> 4205 us a step), and not where the staged sources (64 for each wave,
+// behind the table) would cost the default launch a resident workgroup.  The
+// split sums are in another order, so the rule looks at the form, its table and
+// the plan alone: the launch's own waves and grid leave the results bitwise
+// alone.  P2P with leaves of 32: 32^3 float64 / float32 r^2 212 / 138 -> 177 /
+// 117 us, 40^3 365 / 195 -> 279 / 170, 64^3 1264 / 526 -> 900 / 388.
+size_t split_lds(int mode, int wg_waves, size_t lds) {
+    return (lds + 15) / 16 * 16 + (size_t)wg_waves * 64 * (is_fp32(mode) ? sizeof(float4) : sizeof(double4));
+}
+
+bool split_plan(int mode, int level, int largest_leaf, size_t lds) {
+    if (!splits(mode, level) || largest_leaf > kSplitLeaf) return false;
     constexpr size_t kCuLds = 160 * 1024, kCuWaves = 32;
-    const size_t table = (lds + 15) / 16 * 16;
-    const size_t all = table + (size_t)wg_waves * 64 * (is_fp32(mode) ? sizeof(float4) : sizeof(double4));
-    const size_t by_waves = std::max<size_t>(1, kCuWaves / wg_waves);
-    const size_t before = table == 0 ? by_waves : std::min(by_waves, kCuLds / table);
-    return std::min(by_waves, kCuLds / all) >= std::max<size_t>(1, before) ? all : 0;
+    const int waves = default_wg_waves(mode);
+    const size_t by_waves = kCuWaves / waves;
+    const size_t before = lds == 0 ? by_waves : std::min(by_waves, kCuLds / lds);
+    // (16 waves, the most a workgroup has, must fit)
+    return split_lds(mode, 16, lds) <= kCuLds &&
+           std::min(by_waves, kCuLds / split_lds(mode, waves, lds)) >= std::max<size_t>(1, before);
 }
 
 template <int MODE, int LEVEL, bool ACC32, int BITS>
 hipError_t launch_form(const P2PArgs& a, int wg_waves, int grid_wgs, size_t lds, hipStream_t s) {
     const int tb = (int)lds;
     if constexpr (splits(MODE, LEVEL)) {
-        const size_t both = split_lds(MODE, LEVEL, a.largest_leaf, wg_waves, lds);
-        if (both != 0) {
+        if (split_plan(MODE, LEVEL, a.largest_leaf, lds)) {
             hipLaunchKernelGGL((p2p_kernel<MODE, LEVEL, ACC32, BITS, true>), dim3(grid_wgs),
-                               dim3(64 * wg_waves), both, s, a.x64, a.x32, a.leaf, a.leafc, a.p2p_js,
+                               dim3(64 * wg_waves), split_lds(MODE, wg_waves, lds), s, a.x64, a.x32, a.leaf, a.leafc, a.p2p_js,
                                a.items, a.queue, a.n_items, a.counter, a.partial, a.boxes, a.table,
                                a.n_tab, tb, a.round_floor);
             return hipGetLastError();

@@ -63,3 +63,34 @@ def test_every_launch_shape_gives_the_same_bits(form, n):
             ctx.close()
             want = want or got
             assert all(np.array_equal(a, b) for a, b in zip(got, want))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("form", [dict(precision=B.PMFMM_FP32, trunc=B.TRUNC_R2, table_size=64,
+                                       table_level=2),
+                                  dict(precision=B.PMFMM_FP32, trunc=B.TRUNC_TABLE,
+                                       table_size=512, table_level=2),
+                                  dict(precision=B.PMFMM_FP32, trunc=B.TRUNC_TABLE,
+                                       table_size=4096, table_level=4),
+                                  dict(precision=B.PMFMM_FP32), dict(precision=B.PMFMM_FP64)])
+@pytest.mark.parametrize("max_leaf", [16, 32])
+def test_workgroup_size_leaves_small_leaves_bits_alone(form, max_leaf):
+    """Leaves of at most 32, whose lanes may be split over the sources: the
+    choice of that form, which adds in another order, must not hang on the
+    workgroup's size, whatever the table's size leaves of a CU's LDS."""
+    import torch
+    n = 16 ** 3
+    w = inputs.clustered_small(16, 7, max_leaf=max_leaf, order=-1)
+    pos, mass = torch.tensor(w.pos, device="cuda"), torch.tensor(w.mass, device="cuda")
+    want = None
+    for wg in (0, 1, 2, 4, 8, 16):
+        print(f"case: leaves of {max_leaf}, {form}, wg {wg}", flush=True)
+        ctx = B.Context(box=w.box, r_s=w.r_s, r_cut=w.r_cut, max_leaf=max_leaf, order=-1, wg_waves=wg,
+                        **form)
+        ctx.build(pos, mass)
+        out = torch.empty((n, 3), dtype=torch.float64, device="cuda")
+        ctx.forward(out)
+        got = out.cpu().numpy()
+        ctx.close()
+        want = got if want is None else want
+        assert np.array_equal(got, want)
