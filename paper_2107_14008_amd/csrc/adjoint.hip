@@ -33,6 +33,8 @@ __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlan
 // and target leaf have the same mass m everywhere, the rule in equal-mass
 // sets) the two position terms combine to m [g u + h (d.u) d], u = w_l - w_k,
 // added to A alone; otherwise A (times m_k at the end) and B take them apart.
+// Not called for d = 0, the particle itself included: g = h = 0 would still
+// make 0 times its own cotangent NaN where that is not finite.
 template <bool EQ, class R, class V>
 __device__ __forceinline__ void adj_sums(const V& q, const V& wl, const V& wk, R dx, R dy, R dz, R g,
                                          R h, R* A, R* Bv, R& gm) {
@@ -119,8 +121,10 @@ __device__ __forceinline__ void adj_pair_f32(const float4 q, const float4 wl, fl
                                              float* Bv, float& gm) {
     const float dx = q.x - px, dy = q.y - py, dz = q.z - pz;
     const float r2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-    if (r2 < rc2) {
-        float g = 0.f, h = 0.f;
+    // 0 < r2 < rc2 in one comparison (positive floats are ordered as their bits:
+    // 64^3 exact form 1478 -> 1445 us against the two)
+    if (__float_as_uint(r2) - 1u < __float_as_uint(rc2) - 1u) {
+        float g, h;
         if (TAB && r2 >= smin) {
             // (g c0, g c1), (h c0, h c1), (g c2, h c2) pairs of the row
             const unsigned char* c = tab + (((__float_as_uint(r2) >> (23 - kAdjBits)) << 3) + boff);
@@ -129,7 +133,7 @@ __device__ __forceinline__ void adj_pair_f32(const float4 q, const float4 wl, fl
             const float2 c2 = *reinterpret_cast<const float2*>(c + 16 * kAdjPlane);
             g = fmaf(fmaf(c2.x, r2, g01.y), r2, g01.x);
             h = fmaf(fmaf(c2.y, r2, h01.y), r2, h01.x);
-        } else if (r2 > 0.f) {
+        } else {
             adj_gh_f32(TAB ? fmaxf(r2, tiny) : r2, alpha, g, h);
         }
         adj_sums<EQ, float, float4>(q, wl, wk, dx, dy, dz, g, h, A, Bv, gm);
@@ -160,10 +164,10 @@ __device__ __forceinline__ void adj_pair_f64_F(const double4& q, const double4& 
         }
         r2 = (dx * dx + dy * dy) + dz * dz;
     }
-    if (r2 < T.rc2) {
+    if ((r2 > 0.0) & (r2 < T.rc2)) {
         const double y = r2 * T.a2;
         const uint32_t hi = (uint32_t)__double2hiint(y);
-        double g = 0.0, e = 0.0;
+        double g, e;
         if (hi >= (uint32_t)(1023 + kFEmin) << 20) {
             double t;
             const unsigned char* row;
@@ -176,15 +180,13 @@ __device__ __forceinline__ void adj_pair_f64_F(const double4& q, const double4& 
             p = fma(t, p, -1.0);
             p = fma(t, p, 1.0);
             e = *reinterpret_cast<const double*>(row + 6 * kFPlane) * p;
-        } else if (r2 > 0.0) {
+        } else {
             g = f_close(y);
             e = 1.0 - y;
         }
-        // 1 / y (r2 = 0: g = e = 0 and 1 / 1)
-        const double yy = r2 > 0.0 ? y : 1.0;
-        double iy = __builtin_amdgcn_rcp(yy);
-        iy = fma(iy, fma(-yy, iy, 1.0), iy);
-        iy = fma(iy, fma(-yy, iy, 1.0), iy);
+        double iy = __builtin_amdgcn_rcp(y);   // 1 / y
+        iy = fma(iy, fma(-y, iy, 1.0), iy);
+        iy = fma(iy, fma(-y, iy, 1.0), iy);
         const double h = -T.a2 * iy * fma(kFourOverSqrtPi, e, 3.0 * g);
         adj_sums<EQ, double, double4>(q, wl, wk, dx, dy, dz, g, h, A, Bv, gm);
     }

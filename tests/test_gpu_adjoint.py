@@ -331,3 +331,37 @@ def test_autograd_with_far_field(far_case):
     ex = scaled(pos.grad.cpu().numpy(), gx, sx + np.abs(fx).max())
     em = scaled(mass.grad.cpu().numpy(), gm, sm + np.abs(fm).max())
     assert ex["max"] <= 1e-12 and em["max"] <= 1e-12, (ex, em)
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("form,reach", [(dict(precision=B.PMFMM_FP64), 4.5),
+                                        (dict(precision=B.PMFMM_FP64), 5.9),
+                                        (dict(precision=B.PMFMM_FP64), 7.0),
+                                        (dict(precision=B.PMFMM_FP32), 4.5),
+                                        (dict(precision=B.PMFMM_FP32, trunc=B.TRUNC_R2, table_size=64,
+                                              table_level=2), 4.5)])
+def test_non_finite_cotangent_stays_with_its_neighbours(form, reach, mixed, bad):
+    """A particle's own cotangent is in none of its mass gradient's terms, and
+    in no gradient beyond the cutoff: both are bit for bit those with that
+    cotangent zero."""
+    w = inputs.clustered_small(12, 21, max_leaf=64, order=-1)
+    n = len(w.mass)
+    m = w.mass * (np.random.default_rng(2).uniform(0.5, 1.5, n) if mixed else 1.0)
+    wv = inputs.cotangent(n, 6)
+    k, r_s = 77, 0.5 * w.r_s
+    print(f"case: cotangent {bad}, mixed {mixed}, r_cut {reach} r_s, {form}", flush=True)
+    sr = api.ShortRange(box=w.box, r_s=r_s, r_cut=reach * r_s, max_leaf=64, order=-1, theta=0.0,
+                        **form)
+    sr.build(torch.tensor(w.pos, device="cuda"), torch.tensor(m, device="cuda"))
+    got = []
+    for v in (0.0, bad):
+        wv[k] = v
+        got.append([t.cpu().numpy() for t in sr.adjoint(torch.tensor(wv, device="cuda"))])
+    d = w.pos - w.pos[k]
+    d -= w.box * np.round(d / w.box)
+    apart = np.linalg.norm(d, axis=1) > 1.001 * reach * r_s
+    assert apart.any()
+    assert np.array_equal(got[0][0][apart], got[1][0][apart])
+    assert np.array_equal(got[0][1][apart], got[1][1][apart])
+    assert np.isfinite(got[1][1][k]) and got[0][1][k] == got[1][1][k]
