@@ -18,10 +18,10 @@ struct PMPlan {
     double* gk[3] = {nullptr, nullptr, nullptr};     // gradient spectra
     double* field[3] = {nullptr, nullptr, nullptr};  // (n, n, n) accelerations
     // block deposit: sorted records, caller indices, bin counts and offsets,
-    // tiles; grown to the largest particle count seen
+    // tiles; grown to the largest particle count seen.  The bin counts are zero
+    // between calls: cleared where they are allocated, and by pm_bin_scan
     void* blk[4] = {nullptr, nullptr, nullptr, nullptr};
     size_t blk_bytes[4] = {0, 0, 0, 0};
-    bool blk_cleared = false;     // the bin counts are zero
     std::vector<void*> retired;   // outgrown buffers, freed by pm_release
 };
 

@@ -17,6 +17,7 @@
 #include "pm.h"
 
 #include <cmath>
+#include <new>
 
 namespace pmfmm {
 namespace {
@@ -143,7 +144,7 @@ pm_bin_count(const double* __restrict__ pos, int64_t np, double L, PmBlocks b,
 }
 
 // start[k]: first sorted particle of bin k; cstart[k]: first deposit chunk of
-// bin k (both with a total at [bins]); clears count for the next call.  One
+// bin k (both with a total at [bins]); clears count for the next launch.  One
 // workgroup, four bins per thread.
 __global__ void __launch_bounds__(1024)
 pm_bin_scan(int bins, uint32_t* __restrict__ count, uint32_t* __restrict__ start,
@@ -451,6 +452,16 @@ PmBlocks pm_blocks(int n) {
 // being captured.
 constexpr int64_t kPmMinParticles = 16384;
 
+// Room for one more retired buffer.
+bool pm_may_retire(PMPlan& p) {
+    try {
+        p.retired.reserve(p.retired.size() + 1);
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+    return true;
+}
+
 bool pm_block_buffers(PMPlan& p, int64_t np, hipStream_t s) {
     if (p.n > 256 || np < kPmMinParticles || np > (int64_t)UINT32_MAX) return false;
     if (4 * np < (int64_t)p.n * p.n * p.n) return false;
@@ -461,7 +472,7 @@ bool pm_block_buffers(PMPlan& p, int64_t np, hipStream_t s) {
     const size_t bytes[4] = {(size_t)np * 32, (size_t)np * 4, words * 4, chunks * b.tile * 8};
     bool fits = true;
     for (int k = 0; k < 4; ++k) fits = fits && p.blk_bytes[k] >= bytes[k];
-    if (fits) return true;
+    if (fits) return pm_may_retire(p);   // room to set the counts aside if a launch fails
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
     for (int k = 0; k < 4; ++k) {
@@ -471,16 +482,26 @@ bool pm_block_buffers(PMPlan& p, int64_t np, hipStream_t s) {
         // most twice the newest)
         const size_t want = p.blk[k] ? bytes[k] + bytes[k] / 2 : bytes[k];
         void* q = nullptr;
+        if (!pm_may_retire(p)) return false;
         if (hipMalloc(&q, want) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
+        if (k == 2) {
+            // here, where nothing is being captured and whatever comes of the
+            // call: no later one has to know whether the counts are clear
+            hipLaunchKernelGGL(pm_zero, dim3(blocks_of((int64_t)(bins + 1) / 2)), dim3(256), 0, s,
+                               static_cast<double*>(q), (int64_t)((bins + 1) / 2));
+            if (hipGetLastError() != hipSuccess) {
+                (void)hipFree(q);
+                return false;
+            }
+        }
         if (p.blk[k]) p.retired.push_back(p.blk[k]);
         p.blk[k] = q;
         p.blk_bytes[k] = want;
-        if (k == 2) p.blk_cleared = false;
     }
-    return true;
+    return pm_may_retire(p);
 }
 
 }  // namespace
@@ -557,9 +578,6 @@ hipError_t pm_long_range(PMPlan& p, const double* pos, const double* mass, int64
         uint32_t* base = cstart + bins + 8;
         const unsigned wgs = (unsigned)((np + kPmPer - 1) / kPmPer);
         const unsigned chunks = (unsigned)(bins + np / kPmChunk + 1);
-        if (!p.blk_cleared)
-            hipLaunchKernelGGL(pm_zero, dim3(blocks_of((bins + 8) / 2 + 1)), dim3(256), 0, s,
-                               reinterpret_cast<double*>(count), (int64_t)((bins + 1) / 2));
         hipLaunchKernelGGL(pm_bin_count, dim3(wgs), dim3(kPmThreads), 0, s, pos, np, L, b, count, base);
         hipLaunchKernelGGL(pm_bin_scan, dim3(1), dim3(1024), 0, s, bins, count, start, cstart);
         hipLaunchKernelGGL(pm_bin_scatter, dim3(wgs), dim3(kPmThreads), 0, s, pos, mass, np, L, b, start, base,
@@ -568,8 +586,13 @@ hipError_t pm_long_range(PMPlan& p, const double* pos, const double* mass, int64
                            start, cstart, static_cast<double*>(p.blk[3]));
         hipLaunchKernelGGL(pm_tile_sum, dim3(n, n), dim3(128), 0, s, b, cstart,
                            static_cast<const double*>(p.blk[3]), p.rho);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        p.blk_cleared = true;   // pm_bin_scan leaves the counts zero
+        if ((e = hipGetLastError()) != hipSuccess) {
+            // the counts may have been added to and not cleared
+            p.retired.push_back(p.blk[2]);
+            p.blk[2] = nullptr;
+            p.blk_bytes[2] = 0;
+            return e;
+        }
     } else {
         hipLaunchKernelGGL(pm_zero, dim3(blocks_of(n3)), dim3(256), 0, s, p.rho, n3);
         if (np > 0)
