@@ -59,10 +59,11 @@ enum { PMFMM_FP64 = 0, PMFMM_FP32 = 1 };
  * covers the octaves [2^-35, 2^11) with degree 1 or 2; float64 covers
  * [2^-5, 2^11) with degree 4 to 6 and takes pairs closer than that (below
  * r_cut / 256) through the library erfc/exp.  It needs one r_cut / r_s for
- * all boxes of a plan.  For r_cut <= 6 r_s in every box both float64 forms,
- * EXACT and R2, are evaluated from one built-in table of T / r^3 that is
- * within 3e-16 of it for r <= 5.6 r_s and 8e-16 up to 6 r_s, finer than
- * any R2 table that can be asked for. */
+ * all boxes of a plan.  For r_cut <= 6 r_s in every box float64 EXACT, and
+ * float64 R2 of degree 6 or in plans whose leaves hold at most 32 particles,
+ * are evaluated from one built-in table of T / r^3 that is within 6e-16 of it
+ * for r <= 5.6 r_s and 8e-16 up to 6 r_s, finer than any R2 table that can be
+ * asked for. */
 enum { PMFMM_TRUNC_EXACT = 0, PMFMM_TRUNC_TABLE = 1, PMFMM_TRUNC_R2 = 2 };
 /* M2L acceptance against the cutoff (Sec. 2 truncates the kernel at
  * r_cut; where a cell pair straddles r_cut the paper does not say).
@@ -110,10 +111,11 @@ typedef struct pmfmm_params {
     /* scheduling of the P2P work (no effect on results) */
     int32_t chunk;       /* j-leaves per work item, 0 = automatic                 */
     int32_t wg_waves;    /* wavefronts per workgroup of the P2P and adjoint launches,
-                            0 = auto; the float64 exact P2P and every float64
-                            adjoint run 16 for r_cut <= 6 r_s whatever is asked
-                            (their table takes a compute unit's LDS) and at
-                            most 4 beyond                                      */
+                            0 = auto; what reads the built-in float64 table
+                            (see TRUNC; every float64 adjoint for r_cut <= 6
+                            r_s) runs 16 whatever is asked (the table takes a
+                            compute unit's LDS); the float64 exact P2P and
+                            every float64 adjoint run at most 4 beyond         */
     int32_t grid_wgs;    /* workgroups of the persistent launch, 0 = auto         */
     int32_t timing;      /* 1: time each phase with HIP events (see get_timings)  */
     int32_t threads;     /* host threads of the host planner, 0 = all             */

@@ -588,14 +588,21 @@ int upload_items(pmfmm_ctx* ctx, hipStream_t s) {
     return PMFMM_OK;
 }
 
-// The pair form the current plan is evaluated with.  The float64 r^2 form
-// reads the F table as well: its lookup (44 bytes) costs no more LDS than any
-// r^2 row but the smallest (40 to 56 bytes), it covers closer pairs, and it is
-// closer to the exact factor than any r^2 table that can be asked for (128^3
-// forward 6.9 ms with degree-6 rows, 5.67 ms from F).
+// The pair form the current plan is evaluated with.  The float64 r^2 form reads
+// the F table too where that is faster; it is closer to the exact factor than
+// any r^2 table that can be asked for.  A row of degree 6 is 56 bytes to its 44:
+// P2P at 128^3 with 16 / 32 / 64 rows an octave 6.15 / 6.54 / 6.87 ms, from F
+// 5.57.  Rows of degree 4 and 5 (40 and 48 bytes, one read path) are faster than
+// F in the ordinary kernel, 128^3 5.37 to 5.59 and 5.19 to 5.22 ms, 64^3 775 to
+// 805 and 747 to 757 us against 812, but are not split over the lanes of small
+// leaves: 64^3 in leaves of 32 1206 to 1230 us, 870 from F; 24^3 115, 93.
 int form_mode(const pmfmm_ctx* ctx) {
-    const bool f = ctx->p.precision == PMFMM_FP64 && ctx->p.trunc != PMFMM_TRUNC_TABLE;
-    return f && within_f_table(ctx->plan.boxes) ? (int)pmfmm::kFP64F : mode_of(ctx->p);
+    const pmfmm_params& p = ctx->p;
+    const bool f = p.precision == PMFMM_FP64 &&
+                   (p.trunc == PMFMM_TRUNC_EXACT ||
+                    (p.trunc == PMFMM_TRUNC_R2 &&
+                     (p.table_level == 6 || ctx->plan.largest_leaf <= pmfmm::kSplitLeaf)));
+    return f && within_f_table(ctx->plan.boxes) ? (int)pmfmm::kFP64F : mode_of(p);
 }
 
 // The F table, on the device from its first use by the context on.

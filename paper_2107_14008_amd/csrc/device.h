@@ -46,6 +46,8 @@ constexpr int p2p_max_threads(int mode) { return mode == kFP64Exact ? 256 : 1024
 // forms: 16 share one LDS copy of the table (a 2048-segment r^2 table is 33 KB;
 // with 4-wave groups LDS would cap a CU at 16 waves).
 constexpr int default_wg_waves(int mode) { return mode == kFP64Exact || mode == kFP32Exact ? 4 : 16; }
+// Largest leaf whose targets' lanes are split over the sources (p2p.hip).
+constexpr int kSplitLeaf = 32;
 // Waves per SIMD the float32 forms must leave room for: two 16-wave
 // workgroups per CU (their tables fit twice in LDS), so at most 64 VGPRs and
 // the matching scalar registers per wave.

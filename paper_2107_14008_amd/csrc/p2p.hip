@@ -317,7 +317,6 @@ __device__ __forceinline__ void leaf_f32(const float4* __restrict__ src, int nj,
 // differ between the lanes, so the live ones are packed into 64 places of the
 // wave's own in LDS, the places behind them taken by ones beyond any cutoff,
 // and read from there, a place per part (a broadcast).
-constexpr int kSplitLeaf = 32;
 constexpr int split_of(int ni) { return ni <= kSplitLeaf / 2 ? 4 : 2; }
 
 template <class V, class S>

@@ -404,3 +404,22 @@ def test_fp32_twosum_accumulation(trunc, size, level):
     d = metrics.error_summary(res[B.ACCUM_FP32_TWOSUM], res[B.ACCUM_FP64])
     print("  vs float64 accumulation:", d, flush=True)
     assert d["max"] <= 1e-6
+
+
+@pytest.mark.parametrize("degree,per_octave,max_leaf,built_in",
+                         [(4, 32, 64, False), (5, 64, 64, False), (6, 64, 64, True),
+                          (4, 32, 32, True), (5, 64, 32, True)])
+def test_fp64_r2_rows_or_the_built_in_table(clustered, degree, per_octave, max_leaf, built_in):
+    """For r_cut <= 6 r_s the float64 r^2 form of degree 6, or of any degree in
+    leaves of at most 32, is the exact form's table bit for bit; degree 4 and 5
+    are evaluated from the rows asked for in larger leaves, where those are
+    faster, and keep their error (the bounds above)."""
+    w, ref = clustered
+    print(f"case: float64 r^2 degree {degree}, leaves of {max_leaf}", flush=True)
+    acc, _ = gpu_forward(w.pos, w.mass, w.box, w.r_s, w.r_cut, max_leaf, precision=B.PMFMM_FP64,
+                         trunc=B.TRUNC_R2, table_size=per_octave, table_level=degree)
+    exact, _ = gpu_forward(w.pos, w.mass, w.box, w.r_s, w.r_cut, max_leaf)
+    assert np.array_equal(acc, exact) == built_in
+    tol = {4: 1e-9, 5: 1e-12, 6: 1e-13}[degree]
+    e = metrics.error_summary(acc, ref)
+    assert e["max"] <= 100 * tol and e["p999"] <= tol, e
