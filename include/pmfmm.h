@@ -330,13 +330,15 @@ typedef struct pmfmm_schedule {
  * on `stream`; applies the fastest as pmfmm_set_eval would (the other
  * evaluation fields and `timing` stay as they were).
  * cands / n_cands: schedules to try; NULL for the default 24 (chunk 0, 8,
- * 16, 32, 64, 2^20 x wg_waves 2, 4, 8, 16, grid automatic; wg_waves above
- * what the form runs, see pmfmm_params, are skipped).  results (optional,
+ * 16, 32, 64, 2^20 x wg_waves 2, 4, 8, 16, grid automatic; wg_waves above 4
+ * are skipped for float64 EXACT).  Candidates that make the same launch (a
+ * form may set its waves itself, see pmfmm_params) are timed once.  results (optional,
  * n_cands or 24 entries): each schedule with its time (p2p_ms < 0 when it
  * was skipped or not timed).  cache_path (optional): a text file of lines
  * "key chunk wg_waves grid_wgs p2p_ms", key = device architecture, compute
- * units, pair form and a coarse size signature of the plan (boxes, leaves
- * / 1024, sqrt of the P2P task count / 32); on a hit the cached schedule is
+ * units, pair form, a coarse size signature of the plan (boxes, leaves
+ * / 1024, sqrt of the P2P task count / 32), and marks for plans that read the
+ * built-in float64 table and for leaves of at most 32; on a hit the cached schedule is
  * applied without timing, on a miss the winner is appended.  *best
  * receives the applied schedule.  Synchronises `stream`.
  * Errors: EINVAL (null acc or best, repeats or n_cands out of range, an

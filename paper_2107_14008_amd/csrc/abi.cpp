@@ -775,6 +775,13 @@ int do_upload(pmfmm_ctx* ctx, const double* pos, const double* mass, int32_t on_
     return PMFMM_OK;
 }
 
+// Waves per workgroup of a P2P launch: the caller's, or the form's own.  One
+// workgroup of the F table's size fits a CU: it always has 16.
+int p2p_waves(int mode, int asked) {
+    const int waves = asked > 0 && mode != pmfmm::kFP64F ? asked : pmfmm::default_wg_waves(mode);
+    return std::min(waves, pmfmm::p2p_max_threads(mode) / 64);
+}
+
 // Workgroups of a persistent launch: the caller's, or as many as are resident
 // (`resident`), but no more than there are items in every queue segment.
 int launch_grid(const pmfmm_ctx* ctx, int resident) {
@@ -1272,10 +1279,7 @@ int forward_launch(pmfmm_ctx* ctx, double* acc, hipStream_t s, int32_t* counter,
     const bool tab = mode == pmfmm::kFP32Table || mode == pmfmm::kFP64Table || mode == pmfmm::kFP32R2 ||
                      mode == pmfmm::kFP64R2;
     const size_t lds = mode == pmfmm::kFP64F ? (size_t)pmfmm::kFTableBytes : tab ? ctx->table_host.size() : 0;
-    // one workgroup of the F table's size fits a CU: it always has 16 waves
-    const bool asked = ctx->p.wg_waves > 0 && mode != pmfmm::kFP64F;
-    const int wg = std::min(asked ? ctx->p.wg_waves : pmfmm::default_wg_waves(mode),
-                            pmfmm::p2p_max_threads(mode) / 64);
+    const int wg = p2p_waves(mode, ctx->p.wg_waves);
     const int grid = launch_grid(ctx, ctx->n_cu * pmfmm::p2p_blocks_per_cu(mode, wg, lds));
     if (pmfmm::queue_counts((int32_t)ctx->n_items, grid, wg))
         HIP_TRY(pmfmm::launch_zero_i32(counter, pmfmm::kQueueSegs * pmfmm::kCounterStride, s));
@@ -1340,7 +1344,9 @@ int pmfmm_forward_static(pmfmm_ctx* ctx, double* acc, void* stream) {
 
 namespace {
 
-// Cache key of the autotuner: device, pair form, coarse size of the plan.
+// Cache key of the autotuner: device, pair form, coarse size of the plan, and
+// which of the parameters' kernels it runs (the F table's; leaves that may be
+// split over the lanes).
 std::string tune_key(const pmfmm_ctx* ctx) {
     hipDeviceProp_t prop{};
     std::string arch = "unknown";
@@ -1352,7 +1358,9 @@ std::string tune_key(const pmfmm_ctx* ctx) {
     return arch + "|" + std::to_string(ctx->n_cu) + "|" + std::to_string(p.precision) + "|" +
            std::to_string(p.trunc) + "|" + std::to_string(p.table_size) + "|" + std::to_string(p.table_level) +
            "|" + std::to_string(p.accum) + "|" + std::to_string(ctx->plan.boxes.size()) + "|" +
-           std::to_string(ctx->plan.leaf_count.size() / 1024) + "|" + std::to_string(bucket);
+           std::to_string(ctx->plan.leaf_count.size() / 1024) + "|" + std::to_string(bucket) +
+           (form_mode(ctx) == pmfmm::kFP64F ? "|f" : "") +
+           (ctx->plan.largest_leaf <= pmfmm::kSplitLeaf ? "|small" : "");
 }
 
 bool tune_cache_find(const char* path, const std::string& key, pmfmm_schedule& out) {
@@ -1421,11 +1429,21 @@ int pmfmm_autotune(pmfmm_ctx* ctx, double* acc, const pmfmm_schedule* cands, int
         return PMFMM_OK;
     }
     const int max_waves = pmfmm::p2p_max_threads(mode_of(ctx->p)) / 64;
+    const int mode = form_mode(ctx);
     int win = -1;
     for (size_t i = 0; i < todo.size(); ++i) {
         pmfmm_schedule& sc = todo[i];
         sc.p2p_ms = -1.0;
-        if (sc.wg_waves > max_waves) continue;   // the launch would run max_waves anyway
+        if (sc.wg_waves > max_waves) continue;   // (float64 exact: 4, whatever the launch runs)
+        // candidates of one launch (the form may set its waves itself) are timed once
+        const auto same = std::find_if(todo.begin(), todo.begin() + i, [&](const pmfmm_schedule& o) {
+            return o.p2p_ms >= 0.0 && o.chunk == sc.chunk && o.grid_wgs == sc.grid_wgs &&
+                   p2p_waves(mode, o.wg_waves) == p2p_waves(mode, sc.wg_waves);
+        });
+        if (same != todo.begin() + i) {
+            sc.p2p_ms = same->p2p_ms;
+            continue;
+        }
         int rc = apply_schedule(ctx, sc, 1);
         if (!rc) rc = pmfmm_forward(ctx, acc, stream);
         double sum = 0.0;

@@ -77,3 +77,42 @@ def test_autotune_default_candidates_through_the_abi(tmp_path):
     if best["chunk"] == 0:
         assert np.array_equal(a, b)
     assert np.max(np.linalg.norm(a - b, axis=1) / np.linalg.norm(b, axis=1)) <= 1e-12
+
+
+@pytest.mark.parametrize("form,ran_per_chunk", [(dict(precision=B.PMFMM_FP64), 2),
+                                                (dict(precision=B.PMFMM_FP64, trunc=B.TRUNC_R2,
+                                                      table_size=64, table_level=6), 4)])
+def test_schedules_of_one_launch_are_timed_once(form, ran_per_chunk):
+    """The forms of the built-in float64 table run 16 waves whatever is asked:
+    schedules that differ in wg_waves alone are one launch and have one time."""
+    w = inputs.clustered_small(16, 9)
+    ctx = B.Context(box=w.box, r_s=w.r_s, r_cut=w.r_cut, max_leaf=64, order=-1, **form)
+    ctx.build(torch.tensor(w.pos, device="cuda"), torch.tensor(w.mass, device="cuda"))
+    out = torch.empty((len(w.mass), 3), dtype=torch.float64, device="cuda")
+    _, timed = ctx.autotune(out, repeats=1)
+    times = {}
+    for r in timed:
+        if r["p2p_ms"] >= 0:
+            times.setdefault(r["chunk"], []).append(r["p2p_ms"])
+    assert len(times) == 6
+    assert all(len(t) == ran_per_chunk and len(set(t)) == 1 for t in times.values()), times
+
+
+def test_cached_schedule_is_of_the_kernel_that_runs(tmp_path):
+    """A schedule tuned for the built-in float64 table is not taken for the
+    polynomial form of a wider cutoff, nor one of full leaves for small ones,
+    in plans of one coarse size."""
+    rng = np.random.default_rng(4)
+    n, box, r_s = 512, 100.0, 3.0
+    pos = torch.tensor(rng.uniform(0, box, (n, 3)), device="cuda")
+    mass = torch.full((n,), 1.0 / n, dtype=torch.float64, device="cuda")
+    out = torch.empty((n, 3), dtype=torch.float64, device="cuda")
+    cache = str(tmp_path / "tune.txt")
+    for k, (reach, leaf) in enumerate([(4.5, 64), (7.0, 64), (4.5, 32), (7.0, 32)]):
+        ctx = B.Context(box=box, r_s=r_s, r_cut=reach * r_s, max_leaf=leaf, order=-1,
+                        precision=B.PMFMM_FP64)
+        ctx.build(pos, mass)
+        for timed_now in (True, False):       # the second time from the cache
+            _, timed = ctx.autotune(out, cands=[(0, 2, 0), (0, 4, 0)], repeats=1, cache_path=cache)
+            assert (len(timed) > 0) == timed_now
+        assert open(cache).read().count("\n") == k + 1
