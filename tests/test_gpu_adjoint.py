@@ -365,3 +365,24 @@ def test_non_finite_cotangent_stays_with_its_neighbours(form, reach, mixed, bad)
     assert np.array_equal(got[0][0][apart], got[1][0][apart])
     assert np.array_equal(got[0][1][apart], got[1][1][apart])
     assert np.isfinite(got[1][1][k]) and got[0][1][k] == got[1][1][k]
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("max_leaf", [7, 64])
+@pytest.mark.parametrize("reach", [5.9, 7.0])
+def test_adjoint_fp64_of_a_wide_cutoff(reach, max_leaf, mixed):
+    """The table's last octave (5.9 r_s) and the polynomial form beyond the
+    table (7 r_s), one mass and several, with images."""
+    w = inputs.clustered_small(16, 55, halo_frac=0.3, n_halos=4)
+    n = len(w.mass)
+    m = w.mass * (np.random.default_rng(1).uniform(0.5, 1.5, n) if mixed else 1.0)
+    wv = inputs.cotangent(n, seed=15013)
+    r_s = 0.5 * w.r_s
+    print(f"case: adjoint fp64, r_cut {reach} r_s, leaves of {max_leaf}, mixed {mixed}", flush=True)
+    gx, gm, sx, sm = direct.gradient(w.pos, m, wv, w.box, r_s, reach * r_s, with_scale=True)
+    sr = api.ShortRange(box=w.box, r_s=r_s, r_cut=reach * r_s, max_leaf=max_leaf, order=-1, theta=0.0,
+                        precision=B.PMFMM_FP64)
+    sr.build(torch.tensor(w.pos, device="cuda"), torch.tensor(m, device="cuda"))
+    gp, gmass = (t.cpu().numpy() for t in sr.adjoint(torch.tensor(wv, device="cuda")))
+    assert scaled(gp, gx, sx)["max"] <= 1e-12
+    assert scaled(gmass, gm, sm)["max"] <= 1e-12

@@ -107,3 +107,23 @@ def test_outer_shell_in_small_and_full_leaves(xc, y0, mass_ratio, max_leaf):
         for i, m in ((k, mass_ratio), (k + 512, 1.0)):
             worst = max(worst, abs(np.linalg.norm(got[i]) - m * a) / (m * a))
     assert worst <= tol, (worst, tol)
+
+
+@pytest.mark.parametrize("xc", [0.4, 2.25, 3.0])
+@pytest.mark.parametrize("mass_ratio", [1.0, 0.37])
+def test_full_leaves_agree_with_small_ones_in_every_octave(xc, mass_ratio):
+    """The pairs of the first test in leaves of 64 (one mass to a leaf, or
+    several) against leaves of 7, whose kernel splits a leaf's lanes: one
+    lookup, then at most four roundings of the products each (9e-16)."""
+    pos, mass, r_s, r_cut = _pairs(xc, 3, mass_ratio)
+    got = []
+    for max_leaf, largest in ((7, 4), (64, 64)):
+        print(f"case: single pairs, x_c {xc}, mass ratio {mass_ratio}, leaves of {max_leaf}", flush=True)
+        ctx = B.Context(box=100.0, r_s=r_s, r_cut=r_cut, max_leaf=max_leaf, order=-1)
+        ctx.build(torch.tensor(pos, device="cuda"), torch.tensor(mass, device="cuda"))
+        assert np.diff(np.append(ctx.lists()["leaf_first"], 1024)).max() == largest
+        out = torch.empty((1024, 3), dtype=torch.float64, device="cuda")
+        ctx.forward(out)
+        got.append(out.cpu().numpy())
+    d = np.linalg.norm(got[0] - got[1], axis=1)
+    assert (d <= 1e-15 * np.linalg.norm(got[0], axis=1)).all()

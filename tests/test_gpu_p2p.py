@@ -11,6 +11,7 @@ Tolerances (relative force error e_i = |a_i - a_ref| / |a_ref|):
 
 import numpy as np
 import pytest
+from scipy.special import erfc
 
 torch = pytest.importorskip("torch")
 
@@ -423,3 +424,66 @@ def test_fp64_r2_rows_or_the_built_in_table(clustered, degree, per_octave, max_l
     tol = {4: 1e-9, 5: 1e-12, 6: 1e-13}[degree]
     e = metrics.error_summary(acc, ref)
     assert e["max"] <= 100 * tol and e["p999"] <= tol, e
+
+
+def r2_rows_sum(pos, m, box, r_s, r_cut, degree, per_octave):
+    """The pair sum with the float64 r^2 table's rows: on each of per_octave
+    segments of an octave of s = r^2 2^11 / r_cut^2 the polynomial through
+    T / s^(3/2) at the segment's Chebyshev nodes (here by the barycentric
+    formula), for s in [2^-5, 2^11); closer pairs exactly."""
+    def F(s):
+        x = np.sqrt(s * (r_cut / (2 * r_s)) ** 2 / 2048)
+        return (erfc(x) + 2 / np.sqrt(np.pi) * x * np.exp(-x * x)) / s ** 1.5
+    k = np.arange(degree + 1)
+    node = 0.5 - 0.5 * np.cos(np.pi * (k + 0.5) / (degree + 1))
+    weight = (-1.0) ** k * np.sin(np.pi * (k + 0.5) / (degree + 1))
+    acc = np.zeros_like(pos)
+    for i in range(len(pos)):
+        d = pos - pos[i]
+        d -= box * np.round(d / box)
+        r2 = (d * d).sum(1)
+        on = (r2 > 0) & (r2 < r_cut * r_cut)
+        d, mj, sc = d[on], m[on], r2[on] * (2048 / (r_cut * r_cut))
+        step = 2.0 ** np.floor(np.log2(sc)) / per_octave
+        t = sc / step % 1.0
+        num = den = 0.0
+        with np.errstate(divide="ignore", invalid="ignore"):
+            for a, b in zip(node, weight):
+                num = num + b / (t - a) * F((np.floor(sc / step) + a) * step)
+                den = den + b / (t - a)
+            f = np.where(sc < 2.0 ** -5, F(sc), num / den)
+        acc[i] = (mj * f * (2048 / (r_cut * r_cut)) ** 1.5) @ d
+    return acc
+
+
+@pytest.mark.parametrize("max_leaf", [16, 64])
+@pytest.mark.parametrize("degree,per_octave", [(6, 64), (5, 64), (6, 32), (4, 32), (4, 16)])
+def test_fp64_r2_rows_of_a_wide_cutoff(degree, per_octave, max_leaf):
+    """Cutoffs beyond the built-in float64 table (r_cut > 6 r_s) are evaluated
+    from the rows asked for whatever their degree and the leaves: their sum to
+    the float64 rounding (the bound of the float64 table's own sum)."""
+    w = inputs.clustered_small(12, 77, halo_frac=0.3, n_halos=6)
+    r_s = 0.5 * w.r_s
+    print(f"case: r_cut 7 r_s, fp64 r^2 table {per_octave}/octave degree {degree}, leaves of {max_leaf}",
+          flush=True)
+    ref = r2_rows_sum(w.pos, w.mass, w.box, r_s, 7.0 * r_s, degree, per_octave)
+    acc, _ = gpu_forward(w.pos, w.mass, w.box, r_s, 7.0 * r_s, max_leaf, precision=B.PMFMM_FP64,
+                         trunc=B.TRUNC_R2, table_size=per_octave, table_level=degree)
+    assert metrics.error_summary(acc, ref)["max"] <= 1e-12
+
+
+def test_fp64_r2_close_pairs_of_a_wide_cutoff():
+    """Pairs below the rows' range (1e-4 .. 1e-2 r_cut) and coincident ones,
+    which the built-in table answers up to 6 r_s."""
+    rng = np.random.default_rng(17)
+    box, r_s, r_cut = 20.0, 0.6, 4.2
+    base = rng.uniform(0, box, (800, 3))
+    close = base[:200] + rng.normal(0, 1, (200, 3)) * rng.uniform(1e-4, 1e-2, (200, 1)) * r_cut
+    pos = inputs.wrap(np.concatenate([base, close, base[:5]]), box)
+    m = rng.uniform(0.5, 1.5, len(pos))
+    print("case: r_cut 7 r_s, fp64 r^2 table, close pairs", flush=True)
+    ref, _ = direct.brute_force(pos, m, box, r_s, r_cut)
+    acc, _ = gpu_forward(pos, m, box, r_s, r_cut, 16, precision=B.PMFMM_FP64, trunc=B.TRUNC_R2,
+                         table_size=64, table_level=6)
+    e = metrics.error_summary(acc, ref)
+    assert e["max"] <= 1e-11, e
