@@ -82,7 +82,7 @@ PEAK_FP64_TFLOPS = 78.6
 
 def _profile_values(name):
     """key = value pairs of a committed profiles/ summary, or None when the
-    file is missing or the P2P source (p2p.hip, device.h) has changed since
+    file is missing or the P2P source (p2p.hip, device.h, f_table.h) has changed since
     its counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", name)
@@ -103,7 +103,7 @@ def p2p_source_hash():
     """First 16 hex digits of sha256 over the P2P kernel sources."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("p2p.hip", "device.h"):
+    for f in ("p2p.hip", "device.h", "f_table.h"):
         h.update(open(os.path.join(ROOT, "paper_2107_14008_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

@@ -18,8 +18,9 @@
 // Dual walk: level-synchronous over a frontier of cell pairs (the canonical
 // half of the symmetric walk); one thread per pair classifies it and appends
 // P2P keys, M2L keys (each with its mirror) or child pairs with one atomic
-// per wavefront.  The keys (i << 32 | j << 5 | shift) are then sorted,
-// which yields the canonical (i, j, shift) order and the CSR rows.
+// per counter and workgroup.  The keys (i, j << 5 | shift) are counted per
+// row i and placed into CSR rows, and each row is sorted (k_row_*), which
+// yields the canonical (i, j, shift) order.
 #include <algorithm>
 #include <chrono>
 #include <cstdio>

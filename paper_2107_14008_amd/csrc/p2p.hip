@@ -7,7 +7,9 @@
 // Sources are read with wave-uniform addresses, so the compiler turns them
 // into scalar loads broadcast from SGPRs instead of staging each j leaf
 // through LDS; LDS holds the interpolation table of Eq. (int) instead (the
-// paper keeps T_i and E_i in shared memory, Sec. 3.3).  Before the pairs
+// paper keeps T_i and E_i in shared memory, Sec. 3.3).  Only where a plan's
+// leaves hold at most kSplitLeaf particles do the lanes of a wave take
+// different sources, which then come from LDS (SPLIT).  Before the pairs
 // of a j leaf the wave culls the sources that reach none of its targets
 // (device.h).  Work items (i leaf, a range of its j leaves) are pulled by a
 // persistent grid from per-XCD segments of the queue (plan.h), longest
